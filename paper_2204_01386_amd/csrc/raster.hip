@@ -34,6 +34,18 @@
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63); }
 
+// Pixels between the vertex box hb (shb0 | shb1 as TriSetup's hbox0, hbox1)
+// and the rectangle [x0, x1] x [y0, y1] in the L-infinity sense: 0 when the
+// triangle can cover a pixel centre of it; every pixel centre of the
+// rectangle is more than (gap - 1) pixels from the triangle.
+__device__ __forceinline__ int lo16(int v) { return (int)(short)(v & 0xffff); }
+__device__ __forceinline__ int hi16(int v) { return v >> 16; }
+__device__ __forceinline__ int box_gap(int hb0, int hb1, int x0, int x1, int y0, int y1) {
+    const int gx = max(max(lo16(hb0) - x1, x0 - hi16(hb0)), 0);
+    const int gy = max(max(lo16(hb1) - y1, y0 - hi16(hb1)), 0);
+    return max(gx, gy);
+}
+
 // next tile of a lane's tile rectangle in row-major order, -1 when done
 __device__ __forceinline__ int next_tile(int cur, int tx0, int tx1, int ty1, int ntx) {
     int ty = cur / ntx, tx = cur - ty * ntx;
@@ -45,12 +57,22 @@ __device__ __forceinline__ int next_tile(int cur, int tx0, int tx1, int ty1, int
 // One pass: every triangle is set up and appended to the bins of the tiles
 // its box covers.  Each bin has a fixed capacity; its counter (kept at zero
 // between calls, reset by the rasterizer after reading it) gives the slot.
+//
+// SOFT: a bin has two ends.  Triangles whose vertex box comes within RL_NEAR
+// pixels of the tile fill it from slot 0 (counts[tile]), the others, which
+// only a pixel far from every covering triangle looks at, from its last slot
+// down (counts[B nt + tile]); the rasterizer reports an overflow, since only
+// the sum of both tells.  The 16 bytes that its culling needs go to `cullq`.
+#define RL_NEAR 2
+template <bool SOFT>
 __global__ void k_setup_bin(const float4 *__restrict__ pos_clip, const int32_t *__restrict__ tris,
                             Viewports vp, int B, int V, int T, int H, int W, int cull, int margin, int ntx,
-                            int nt, int cap, TriSetup *__restrict__ setup, int32_t *__restrict__ counts,
-                            int32_t *__restrict__ bins, unsigned long long *__restrict__ status) {
+                            int nt, int cap, TriSetup *__restrict__ setup, int4 *__restrict__ cullq,
+                            int32_t *__restrict__ counts, int32_t *__restrict__ bins,
+                            unsigned long long *__restrict__ status) {
     int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int cur = -1, tx0 = 0, tx1 = 0, ty1 = 0, b = 0, t = 0;
+    int hb0 = 0, hb1 = 0;
     if (gid < (int64_t)B * T) {
         b = (int)(gid / T);
         t = (int)(gid - (int64_t)b * T);
@@ -66,6 +88,11 @@ __global__ void k_setup_bin(const float4 *__restrict__ pos_clip, const int32_t *
             s = dr_setup(pos_clip + (int64_t)b * V, v0, v1, v2, q.w, q.z, q.x, q.y, cull, margin);
         }
         setup[gid] = s;
+        if (SOFT) {
+            cullq[gid] = make_int4(s.hbox0, s.hbox1, s.zlb, 0);
+            hb0 = s.hbox0;
+            hb1 = s.hbox1;
+        }
         if (s.meta & 1) {
             tx0 = (s.box0 & 0xffff) / DRESSI_TILE;
             tx1 = (s.box0 >> 16) / DRESSI_TILE;
@@ -83,12 +110,18 @@ __global__ void k_setup_bin(const float4 *__restrict__ pos_clip, const int32_t *
     unsigned long long active = __ballot(cur >= 0);
     while (active) {
         int leader = -1, rank = 0, gsize = 0;
+        // the end of the bin is part of the group's key
+        int end = b;
+        if (SOFT && cur >= 0) {
+            const int ty = cur / ntx, x0 = (cur - ty * ntx) * DRESSI_TILE, y0 = ty * DRESSI_TILE;
+            if (box_gap(hb0, hb1, x0, x0 + DRESSI_TILE - 1, y0, y0 + DRESSI_TILE - 1) > RL_NEAR) end = ~b;
+        }
         unsigned long long todo = active;
         while (todo) {
             int src = __ffsll((long long)todo) - 1;
             int key_tile = __shfl(cur, src, 64);
-            int key_b = __shfl(b, src, 64);
-            unsigned long long same = __ballot(cur >= 0 && cur == key_tile && b == key_b);
+            int key_b = __shfl(end, src, 64);
+            unsigned long long same = __ballot(cur >= 0 && cur == key_tile && end == key_b);
             if ((same >> lane_id()) & 1ull) {
                 leader = src;
                 rank = __popcll(same & below);
@@ -98,18 +131,18 @@ __global__ void k_setup_bin(const float4 *__restrict__ pos_clip, const int32_t *
         }
         int base = 0;
         if (cur >= 0 && leader == lane_id())
-            base = atomicAdd(&counts[(int64_t)b * nt + cur], gsize);
+            base = atomicAdd(&counts[(int64_t)b * nt + cur + (SOFT && end < 0 ? (int64_t)B * nt : 0)], gsize);
         base = __shfl(base, leader < 0 ? 0 : leader, 64);
         if (cur >= 0) {
             int64_t bt = (int64_t)b * nt + cur;
             int slot = base + rank;
-            if (slot < cap) bins[bt * cap + slot] = t;
-            else worst = max(worst, slot + 1);
+            if (slot < cap) bins[bt * cap + (SOFT && end < 0 ? cap - 1 - slot : slot)] = t;
+            else if (!SOFT) worst = max(worst, slot + 1);
             cur = next_tile(cur, tx0, tx1, ty1, ntx);
         }
         active = __ballot(cur >= 0);
     }
-    if (worst > 0) {
+    if (!SOFT && worst > 0) {
         atomicMax(&status[0], 1ull);
         atomicMax(&status[1], (unsigned long long)worst);
     }
@@ -127,9 +160,7 @@ __global__ void k_setup_bin(const float4 *__restrict__ pos_clip, const int32_t *
 // ---------------------------------------------------------------------------
 #define RS_EMPTY 0xffffffffffffffffull
 
-template <bool SOFT>
 __device__ __forceinline__ void raster_tri_in_tile(const TriSetup &s, int t, int tx, int ty,
-                                                   float r, float dscale,
                                                    unsigned long long *slot, const float *prev) {
     int x0 = max(s.box0 & 0xffff, tx * DRESSI_TILE), x1 = min(s.box0 >> 16, tx * DRESSI_TILE + DRESSI_TILE - 1);
     int y0 = max(s.box1 & 0xffff, ty * DRESSI_TILE), y1 = min(s.box1 >> 16, ty * DRESSI_TILE + DRESSI_TILE - 1);
@@ -145,19 +176,10 @@ __device__ __forceinline__ void raster_tri_in_tile(const TriSetup &s, int t, int
                 bool own = (s.meta >> (1 + i)) & 1;
                 in = in && (E[i] > 0 || (E[i] == 0 && own));
             }
-            float key;
-            if (in) {
-                float z = dr_depth(s, E);
-                if (!(z > 0.0f && z < 1.0f)) continue;
-                key = 0.5f * z;
-            } else {
-                if (!SOFT) continue;
-                int ne;
-                float dn = dr_distnorm(s.X, s.Y, px, py, E, dscale, ne);
-                if (!(dn <= r)) continue;
-                float h = 0.5f * dn;
-                key = h + 0.5f;
-            }
+            if (!in) continue;
+            float z = dr_depth(s, E);
+            if (!(z > 0.0f && z < 1.0f)) continue;
+            const float key = 0.5f * z;
             int p = (y - ty * DRESSI_TILE) * DRESSI_TILE + (x - tx * DRESSI_TILE);
             if (!(key > prev[p])) continue;
             unsigned long long v = ((unsigned long long)__float_as_uint(key) << 32) | (unsigned)t;
@@ -215,12 +237,11 @@ __device__ __forceinline__ void resolve_store(const TriSetup *__restrict__ sv, c
     }
 }
 
-template <int K, bool SOFT>
+template <int K>
 __global__ void __launch_bounds__(DRESSI_TILE_PIX)
     k_raster(const TriSetup *__restrict__ setup, int32_t *__restrict__ counts,
              const int32_t *__restrict__ bins, int cap, int T, int H, int W, int ntx, int nt,
-             float r, int32_t *__restrict__ tri_id, float2 *__restrict__ bary,
-             float *__restrict__ dist) {
+             int32_t *__restrict__ tri_id, float2 *__restrict__ bary) {
     __shared__ unsigned long long slot[DRESSI_TILE_PIX];
     __shared__ float prev[DRESSI_TILE_PIX];
     const int bt = (int)xcd_block();
@@ -231,7 +252,6 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX)
     const int y = ty * DRESSI_TILE + (p / DRESSI_TILE);
     const int px = DRESSI_SUBPIX * x + DRESSI_SUBPIX / 2;
     const int py = DRESSI_SUBPIX * y + DRESSI_SUBPIX / 2;
-    const float dscale = (float)W * 256.0f;
     const TriSetup *sv = setup + (int64_t)b * T;
     const int32_t *bin = bins + (int64_t)bt * cap;
     // the bin's first entries are read beside its count, not after it (in
@@ -252,7 +272,7 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX)
             if (c0 + p < nbin) {
                 int t = c0 == 0 ? t_first : bin[c0 + p];
                 TriSetup s = sv[t];
-                raster_tri_in_tile<SOFT>(s, t, tx, ty, r, dscale, slot, prev);
+                raster_tri_in_tile(s, t, tx, ty, slot, prev);
             }
         }
         __syncthreads();
@@ -268,32 +288,15 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX)
         __syncthreads();
     }
     if (p == 0) counts[bt] = 0;   // every lane has read it before the first barrier
-    resolve_store<K, SOFT>(sv, key, id, b, x, y, px, py, H, W, dscale, tri_id, bary, dist);
+    resolve_store<K, false>(sv, key, id, b, x, y, px, py, H, W, 0.0f, tri_id, bary, nullptr);
 }
 
 // ---------------------------------------------------------------------------
-// soft rasterizer (r > 0): one 16x16 tile per workgroup, one lane per pixel,
-// each wavefront a 16x4 strip.  Each lane keeps its pixel's list of the K
-// smallest distinct keys (smallest id at each key), sorted in registers: one
-// pass over the tile's triangles selects exactly what K passes of depth
-// peeling select, with no atomics.  A soft reach of several pixels gives every
-// binned triangle many candidate pixels in the tile, which suits
-// pixel-parallel evaluation.
+// pixel-parallel rasterizers: each lane keeps its pixel's list of the K
+// smallest distinct keys (smallest id at each key), sorted in registers, while
+// triangles stream through LDS.  One pass selects exactly what K passes of
+// depth peeling select, in any visiting order, with no atomics.
 //
-// The tile's bin is staged through LDS, 256 triangles at a time, with the
-// per-tile data the tests need.  A wavefront then tests 64 staged triangles at
-// once (one per lane) and evaluates only the survivors, one at a time across
-// its 64 pixels.  The bin is walked three times, nearest triangles first, so
-// that the lists fill with near fragments early and cull more of the rest:
-// (0) triangles whose vertex box covers pixel centres of the strip, (1) those
-// at most RL_NEAR pixels away, (2) the others.  Every culling test is exact by
-// construction (bounds carry rounding margins):
-//  * the soft box misses the strip;
-//  * the smallest key the triangle can give the strip (half its lowest vertex
-//    depth in walk 0, else the soft key of the L-infinity pixel gap between
-//    its vertex box and the strip) is above every lane's current K-th key;
-//  * per lane, a soft candidate is dropped before its segment distances when
-//    the line distance of an edge it lies outside of already rules it out.
 // Edge functions (and the segment-distance products) are evaluated with
 // 24-bit integer multiplies when staging has shown that every pixel-to-vertex
 // difference over the tile and every edge vector is below 2^15 in magnitude
@@ -303,16 +306,12 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX)
 // neighbouring tiles are read through one L2.
 // ---------------------------------------------------------------------------
 #define RL_BATCH 256
-#define RL_NEAR 2
 
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
     return v;
 }
-
-__device__ __forceinline__ int lo16(int v) { return (int)(short)(v & 0xffff); }
-__device__ __forceinline__ int hi16(int v) { return v >> 16; }
 
 // Smallest segment distance (fixed-point units) from the pixel centre to the
 // triangle: the same value as the minimum of the three segment distances in
@@ -369,8 +368,6 @@ __device__ __forceinline__ float rl_segmin_i(const int *qx, const int *qy, const
     return best;
 }
 
-// Merges the candidate fragment of triangle t at this lane's pixel.  MAYHARD
-// is false when no pixel centre of the wavefront can be inside the triangle.
 // Edge vectors of the 32-bit path: edge i (opposite vertex i) runs from
 // vertex i+1 to vertex i+2 (mod 3); every component is below 2^15 there.
 __device__ __forceinline__ void rl_edges(const TriSetup &s, int *ex, int *ey) {
@@ -442,6 +439,38 @@ __device__ __forceinline__ void rl_tri_in_tile(int e, const int2 *sfi, const int
     }
 }
 
+// Puts (kf, t) into a sorted list of the K smallest distinct keys.
+template <int K>
+__device__ __forceinline__ void rl_insert(float kf, int t, float *key, int *id) {
+    if (!(kf <= key[K - 1])) return;
+    bool same = false;
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        if (kf == key[k]) {
+            id[k] = min(id[k], t);
+            same = true;
+        }
+    }
+    if (same) return;
+    // insert below the first larger key; the largest entry drops out
+#pragma unroll
+    for (int k = K - 1; k > 0; k--) {
+        if (kf < key[k - 1]) {
+            key[k] = key[k - 1];
+            id[k] = id[k - 1];
+        } else if (kf < key[k]) {
+            key[k] = kf;
+            id[k] = t;
+        }
+    }
+    if (kf < key[0]) {
+        key[0] = kf;
+        id[0] = t;
+    }
+}
+
+// Merges the candidate fragment of triangle t at this lane's pixel.  MAYHARD
+// is false when no pixel centre of the wavefront can be inside the triangle.
 template <int K, bool MAYHARD, typename TE, bool SOFT = true>
 __device__ __forceinline__ void rl_merge(const TriSetup &s, const TE *E, const float *el, int t, int px,
                                          int py, float dscale, float r, float reach, float *key, int *id,
@@ -484,31 +513,7 @@ __device__ __forceinline__ void rl_merge(const TriSetup &s, const TE *E, const f
         float h = 0.5f * dn;
         kf = h + 0.5f;
     }
-    if (!(kf <= key[K - 1])) return;
-    bool same = false;
-#pragma unroll
-    for (int k = 0; k < K; k++) {
-        if (kf == key[k]) {
-            id[k] = min(id[k], t);
-            same = true;
-        }
-    }
-    if (same) return;
-    // insert below the first larger key; the largest entry drops out
-#pragma unroll
-    for (int k = K - 1; k > 0; k--) {
-        if (kf < key[k - 1]) {
-            key[k] = key[k - 1];
-            id[k] = id[k - 1];
-        } else if (kf < key[k]) {
-            key[k] = kf;
-            id[k] = t;
-        }
-    }
-    if (kf < key[0]) {
-        key[0] = kf;
-        id[0] = t;
-    }
+    rl_insert<K>(kf, t, key, id);
 }
 
 // HYB (hard, K = 1): every staged batch is rasterized either pixel-parallel
@@ -535,31 +540,32 @@ __device__ __forceinline__ int wave_max_i(int v) {
     return v;
 }
 
-// Edge-band soft rasterization (BAND != 0).  Outside the blend's edge mask E
-// the image is S^H C_1 and the silhouette S^H (§3.4.3), so only the front
-// hard fragment of a pixel reaches the image or a gradient there.  The
-// banded contract keeps, outside E, layer 0 if it is hard and nothing else,
-// and the full K layers inside E.  BAND = 1 is its first pass: every tile,
-// covering triangles only, hard fragments only, writing layer 0 (the front
-// hard fragment, with its distance) and empty layers 1..K-1; E is then built
-// from that layer 0 (its S^H equals the full form's); BAND = 2 is the second
-// pass: tiles with a pixel in E rasterize fully (the full form's walks) and
-// write the K layers of their E pixels; other tiles exit at once.
-template <int K, bool SOFT, bool HYB = false, int BAND = 0>
-__global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_per_eu(SOFT ? 7 : 5)))
+// FRONT (HYB): the first pass of the edge-band soft rasterization.  Outside
+// the blend's edge mask E the image is S^H C_1 and the silhouette S^H
+// (§3.4.3), so only the front hard fragment of a pixel reaches the image or a
+// gradient there.  The banded contract keeps, outside E, layer 0 if it is
+// hard and nothing else, and the full K layers inside E.  This pass takes the
+// near end of the soft bins (a covering triangle is always near), merges hard
+// fragments only and writes layer 0 (the front hard fragment, with its
+// distance) and empty layers 1..K-1; E is then built from that layer 0 (its
+// S^H equals the full form's); k_raster_soft in its banded form then rewrites
+// the E pixels.
+//
+// A hard bin's triangles are tested 64 at a time (one per lane) against the
+// wavefront's 16 x 4 strip: the vertex box must cover one of its pixel centres
+// and half the lowest vertex depth must not exceed every lane's K-th key.
+template <int K, bool HYB = false, bool FRONT = false>
+__global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_per_eu(5)))
     k_raster_list(const TriSetup *__restrict__ setup, int32_t *__restrict__ counts,
                   const int32_t *__restrict__ bins, int cap, int T, int H, int W, int ntx, int nt,
-                  float r, int32_t *__restrict__ tri_id, float2 *__restrict__ bary,
-                  float *__restrict__ dist, int hyb_w, const uint8_t *__restrict__ band, int keep_counts) {
-    static_assert(BAND == 0 || SOFT, "banding is for soft rasterization");
-    constexpr bool SM = SOFT && BAND != 1;   // soft fragments merged
-    constexpr int KL = BAND == 1 ? 1 : K;    // layers kept in registers
+                  int32_t *__restrict__ tri_id, float2 *__restrict__ bary, float *__restrict__ dist, int hyb_w,
+                  int keep_counts, int64_t far_counts, unsigned long long *__restrict__ status) {
+    static_assert(!FRONT || HYB, "the front pass takes either strategy per batch");
+    constexpr int KL = FRONT ? 1 : K;    // layers kept in registers
     // staged triangles (structure of arrays)
     __shared__ int2 sfi[RL_BATCH];      // meta | 32-bit-exact flag << 16, triangle id
-    __shared__ int2 sbox[RL_BATCH];     // soft box
-    __shared__ int2 shb[RL_BATCH];      // pixels with centres in the vertex box
+    __shared__ int2 sbox[RL_BATCH];     // pixels with centres in the vertex box, in the view
     __shared__ int szlb[RL_BATCH];      // lower bound of the hard keys (float bits)
-    __shared__ float4 sel[RL_BATCH];    // sqrtf of the squared edge lengths
     __shared__ int4 sxy0[RL_BATCH];     // X0 X1 X2 Y0
     __shared__ int2 sxy1[RL_BATCH];     // Y1 Y2
     __shared__ float4 sz[RL_BATCH];     // zn0 zn1 zn2 Af
@@ -567,7 +573,7 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
     // double-buffered by batch parity
     __shared__ unsigned long long sslot[HYB ? DRESSI_TILE_PIX : 1];
     __shared__ int scost[2][2];
-    static_assert(!HYB || (K == 1 && !SOFT), "the hybrid strategy is for one hard layer");
+    static_assert(!HYB || KL == 1, "the hybrid strategy is for one hard layer");
     const int bt = (int)xcd_block();
     const int b = bt / nt, tile = bt - b * nt;
     const int tx = tile % ntx, ty = tile / ntx;
@@ -579,7 +585,6 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
     const int px = DRESSI_SUBPIX * x + DRESSI_SUBPIX / 2;
     const int py = DRESSI_SUBPIX * y + DRESSI_SUBPIX / 2;
     const float dscale = (float)W * 256.0f;
-    const float reach = r * dscale * 1.001f;   // conservative, in fixed-point units
     const TriSetup *__restrict__ sv = setup + (int64_t)b * T;
     const int32_t *__restrict__ bin = bins + (int64_t)bt * cap;
     // this lane's wavefront: pixels [wx0, wx1] x [wy0, wy1]
@@ -591,16 +596,14 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
     // the first batch of the bin is read beside its count (as in k_raster)
     const int t_first = p < cap ? bin[p] : -1;
     int nbin = counts[bt];
-    if (nbin > cap) nbin = cap;
-    bool inE = true;   // this lane's pixel is in the edge mask (the second banded pass)
-    if (BAND == 2) {
-        inE = x < W && y < H && band[((int64_t)b * H + y) * W + x] != 0;
-        if (!__syncthreads_or(inE)) {
-            if (p == 0) counts[bt] = 0;
-            return;
+    if (FRONT && p == 0) {
+        const int total = nbin + counts[far_counts + bt];
+        if (total > cap) {
+            atomicMax(&status[0], 1ull);
+            atomicMax(&status[1], (unsigned long long)total);
         }
     }
-    const bool waveE = BAND != 2 || __ballot(inE) != 0ull;
+    if (nbin > cap) nbin = cap;
 
     float key[KL];
     int id[KL];
@@ -610,159 +613,127 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
         id[k] = -1;
     }
     int wmax_bits = __float_as_int(2.0f);   // bound on the strip's K-th keys (they only decrease)
-    int gap_max = 0x3fffffff;               // soft-only triangles farther (pixels) than this are culled
     if (HYB) {
         sslot[p] = RS_EMPTY;
         if (p < 4) scost[p >> 1][p & 1] = 0;
     }
 
-    for (int walk = 0; walk < (SM ? 3 : 1); walk++) {   // hard only: covering triangles
-        for (int c0 = 0; c0 < nbin; c0 += RL_BATCH) {
-            const int n = min(RL_BATCH, nbin - c0);
-            const int par = (c0 / RL_BATCH) & 1;
-            bool use_tp = false;
-            if (walk == 0 || nbin > RL_BATCH) {   // a single batch stays staged
-                __syncthreads();
-                // the other parity's costs were read before this barrier
-                if (HYB && p < 2) scost[par ^ 1][p] = 0;
-                int tp_pix = 0, pp_steps = 0;
-                bool stage = p < n;
-                if (BAND == 1 && stage) {
-                    // the first banded pass takes covering triangles only: one
-                    // whose vertex box misses this tile is marked far away
-                    // (never wanted by the covering walk) without loading
-                    // the rest of its record
-                    const int2 hb = *reinterpret_cast<const int2 *>(&sv[c0 == 0 ? t_first : bin[c0 + p]].hbox0);
-                    const int ty0 = ty * DRESSI_TILE, ty1 = ty0 + DRESSI_TILE - 1;
-                    if (hi16(hb.x) < wx0 || lo16(hb.x) > wx1 || hi16(hb.y) < ty0 || lo16(hb.y) > ty1) {
-                        shb[p] = make_int2((int)0x80008000u, (int)0x80008000u);
-                        sbox[p] = make_int2(0, 0);
-                        szlb[p] = 0;
-                        stage = false;
-                    }
+    for (int c0 = 0; c0 < nbin; c0 += RL_BATCH) {
+        const int n = min(RL_BATCH, nbin - c0);
+        const int par = (c0 / RL_BATCH) & 1;
+        bool use_tp = false;
+        __syncthreads();
+        // the other parity's costs were read before this barrier
+        if (HYB && p < 2) scost[par ^ 1][p] = 0;
+        int tp_pix = 0, pp_steps = 0;
+        bool stage = p < n;
+        if (FRONT && stage) {
+            // a near triangle whose vertex box misses this tile is staged as
+            // an empty box, without loading the rest of its record
+            const int2 hb = *reinterpret_cast<const int2 *>(&sv[c0 == 0 ? t_first : bin[c0 + p]].hbox0);
+            const int ty0 = ty * DRESSI_TILE, ty1 = ty0 + DRESSI_TILE - 1;
+            if (hi16(hb.x) < wx0 || lo16(hb.x) > wx1 || hi16(hb.y) < ty0 || lo16(hb.y) > ty1) {
+                sfi[p] = make_int2(0, -1);
+                sbox[p] = make_int2(1, 1);
+                szlb[p] = 0;
+                stage = false;
+            }
+        }
+        if (stage) {
+            const int t = c0 == 0 ? t_first : bin[c0 + p];
+            const TriSetup s = sv[t];
+            // 32-bit integer path: every pixel-to-vertex difference over the
+            // tile and every edge vector below 2^15 in magnitude
+            const int lim15 = 1 << 15, span = DRESSI_SUBPIX * (DRESSI_TILE - 1);
+            bool small = true;
+#pragma unroll
+            for (int i = 0; i < 3; i++) {
+                small = small && abs(px0 - s.X[i]) < lim15 && abs(px0 + span - s.X[i]) < lim15 &&
+                        abs(py0 - s.Y[i]) < lim15 && abs(py0 + span - s.Y[i]) < lim15;
+                const int a = (i + 1) % 3, c = (i + 2) % 3;
+                const int ex = s.X[c] - s.X[a], ey = s.Y[c] - s.Y[a];
+                small = small && abs(ex) < lim15 && abs(ey) < lim15;
+            }
+            // a soft record's box has the reach's margin: the vertex box then
+            int2 bx = make_int2(s.box0, s.box1);
+            if (FRONT)
+                bx = make_int2(max(lo16(s.hbox0), 0) | (min(hi16(s.hbox0), W - 1) << 16),
+                               max(lo16(s.hbox1), 0) | (min(hi16(s.hbox1), H - 1) << 16));
+            sfi[p] = make_int2((s.meta & 0xffff) | (small ? 0x10000 : 0), t);
+            sbox[p] = bx;
+            szlb[p] = s.zlb;
+            sxy0[p] = make_int4(s.X[0], s.X[1], s.X[2], s.Y[0]);
+            sxy1[p] = make_int2(s.Y[1], s.Y[2]);
+            sz[p] = make_float4(s.zn[0], s.zn[1], s.zn[2], s.Af);
+            if (HYB && (s.meta & 1)) {
+                const int bx0 = max(bx.x & 0xffff, wx0), bx1 = min(bx.x >> 16, wx1);
+                const int by0 = max(bx.y & 0xffff, ty * DRESSI_TILE);
+                const int by1 = min(bx.y >> 16, ty * DRESSI_TILE + DRESSI_TILE - 1);
+                if (bx0 <= bx1 && by0 <= by1) {
+                    tp_pix = (bx1 - bx0 + 1) * (by1 - by0 + 1);
+                    const int strip = 64 / DRESSI_TILE;   // rows per wavefront
+                    pp_steps = (by1 - ty * DRESSI_TILE) / strip - (by0 - ty * DRESSI_TILE) / strip + 1;
                 }
-                if (stage) {
-                    const int t = c0 == 0 ? t_first : bin[c0 + p];
-                    const TriSetup s = sv[t];
-                    // 32-bit integer path: every pixel-to-vertex difference over the
-                    // tile and every edge vector below 2^15 in magnitude
-                    const int lim15 = 1 << 15, span = DRESSI_SUBPIX * (DRESSI_TILE - 1);
-                    bool small = true;
+            }
+        }
+        if (HYB) {
+            tp_pix = wave_max_i(tp_pix);
+            pp_steps = wave_sum_i(pp_steps);
+            if (lane == 0) {
+                atomicAdd(&scost[par][0], tp_pix);
+                atomicAdd(&scost[par][1], pp_steps);
+            }
+        }
+        __syncthreads();
+        if (HYB) use_tp = 16 * scost[par][0] < hyb_w * scost[par][1];
+        if (HYB && use_tp) {
+            if (p < n) rl_tri_in_tile(p, sfi, sbox, sxy0, sxy1, sz, tx, ty, sslot);
+            continue;
+        }
+        for (int c = 0; c < n; c += 64) {
+            // 64 triangles tested at once, one per lane
+            const int e = c + lane;
+            bool want = false;
+            if (e < n) {
+                const int2 bx = sbox[e];
+                want = (bx.x >> 16) >= wx0 && (bx.x & 0xffff) <= wx1 && (bx.y >> 16) >= wy0 &&
+                       (bx.y & 0xffff) <= wy1 && (bx.x & 0xffff) <= (bx.x >> 16) && (bx.y & 0xffff) <= (bx.y >> 16) &&
+                       szlb[e] <= wmax_bits;
+            }
+            unsigned long long todo = __ballot(want);
+            while (todo) {
+                const int j = c + __ffsll((long long)todo) - 1;
+                todo &= todo - 1ull;
+                const int2 fi = sfi[j];
+                const int fl = fi.x, t = fi.y;
+                const int4 q0 = sxy0[j];
+                const int2 q1 = sxy1[j];
+                const float4 z4 = sz[j];
+                TriSetup s;
+                s.X[0] = q0.x; s.X[1] = q0.y; s.X[2] = q0.z;
+                s.Y[0] = q0.w; s.Y[1] = q1.x; s.Y[2] = q1.y;
+                s.zn[0] = z4.x; s.zn[1] = z4.y; s.zn[2] = z4.z;
+                s.Af = z4.w;
+                s.meta = fl & 0xffff;
+                if (fl >> 16) {
+                    // exact in 32-bit integers (see the staging test)
+                    int ex[3], ey[3], E[3];
+                    rl_edges(s, ex, ey);
 #pragma unroll
                     for (int i = 0; i < 3; i++) {
-                        small = small && abs(px0 - s.X[i]) < lim15 && abs(px0 + span - s.X[i]) < lim15 &&
-                                abs(py0 - s.Y[i]) < lim15 && abs(py0 + span - s.Y[i]) < lim15;
-                        const int a = (i + 1) % 3, c = (i + 2) % 3;
-                        const int ex = s.X[c] - s.X[a], ey = s.Y[c] - s.Y[a];
-                        small = small && abs(ex) < lim15 && abs(ey) < lim15;
+                        const int a = (i + 1) % 3;
+                        E[i] = __mul24(ex[i], py - s.Y[a]) - __mul24(ey[i], px - s.X[a]);
                     }
-                    sel[p] = make_float4(s.elen[0], s.elen[1], s.elen[2], 0.0f);
-                    sfi[p] = make_int2((s.meta & 0xffff) | (small ? 0x10000 : 0), t);
-                    sbox[p] = make_int2(s.box0, s.box1);
-                    shb[p] = make_int2(s.hbox0, s.hbox1);
-                    szlb[p] = s.zlb;
-                    sxy0[p] = make_int4(s.X[0], s.X[1], s.X[2], s.Y[0]);
-                    sxy1[p] = make_int2(s.Y[1], s.Y[2]);
-                    sz[p] = make_float4(s.zn[0], s.zn[1], s.zn[2], s.Af);
-                    if (HYB && (s.meta & 1)) {
-                        const int bx0 = max(s.box0 & 0xffff, wx0), bx1 = min(s.box0 >> 16, wx1);
-                        const int by0 = max(s.box1 & 0xffff, ty * DRESSI_TILE);
-                        const int by1 = min(s.box1 >> 16, ty * DRESSI_TILE + DRESSI_TILE - 1);
-                        if (bx0 <= bx1 && by0 <= by1) {
-                            tp_pix = (bx1 - bx0 + 1) * (by1 - by0 + 1);
-                            const int strip = 64 / DRESSI_TILE;   // rows per wavefront
-                            pp_steps = (by1 - ty * DRESSI_TILE) / strip - (by0 - ty * DRESSI_TILE) / strip + 1;
-                        }
-                    }
+                    rl_merge<KL, true, int, false>(s, E, nullptr, t, px, py, dscale, 0.0f, 0.0f, key, id);
+                } else {
+                    double E[3];
+#pragma unroll
+                    for (int i = 0; i < 3; i++) E[i] = dr_edge(s.X, s.Y, i, px, py);
+                    rl_merge<KL, true, double, false>(s, E, nullptr, t, px, py, dscale, 0.0f, 0.0f, key, id);
                 }
-                if (HYB) {
-                    tp_pix = wave_max_i(tp_pix);
-                    pp_steps = wave_sum_i(pp_steps);
-                    if (lane == 0) {
-                        atomicAdd(&scost[par][0], tp_pix);
-                        atomicAdd(&scost[par][1], pp_steps);
-                    }
-                }
-                __syncthreads();
             }
-            if (HYB) use_tp = 16 * scost[par][0] < hyb_w * scost[par][1];
-            if (HYB && use_tp) {
-                if (p < n) rl_tri_in_tile(p, sfi, sbox, sxy0, sxy1, sz, tx, ty, sslot);
-                continue;
-            }
-            for (int c = 0; c < n; c += 64) {
-                // 64 triangles tested at once, one per lane
-                const int e = c + lane;
-                bool want = false;
-                if (e < n) {
-                    const int2 bx = sbox[e];
-                    const bool hit = !(hi16(bx.x) < wx0 || (bx.x & 0xffff) > wx1 || hi16(bx.y) < wy0 ||
-                                       (bx.y & 0xffff) > wy1);
-                    const int2 hb = shb[e];
-                    const int gx = max(max(lo16(hb.x) - wx1, wx0 - hi16(hb.x)), 0);
-                    const int gy = max(max(lo16(hb.y) - wy1, wy0 - hi16(hb.y)), 0);
-                    const int g = max(gx, gy);
-                    if (walk == 0) want = hit && g == 0 && szlb[e] <= wmax_bits;
-                    else if (walk == 1) want = waveE && hit && g > 0 && g <= RL_NEAR && g <= gap_max;
-                    else want = waveE && hit && g > RL_NEAR && g <= gap_max;
-                }
-                unsigned long long todo = __ballot(want);
-                while (todo) {
-                    const int j = c + __ffsll((long long)todo) - 1;
-                    todo &= todo - 1ull;
-                    const int2 fi = sfi[j];
-                    const int fl = fi.x, t = fi.y;
-                    const float4 e4 = sel[j];
-                    const int4 q0 = sxy0[j];
-                    const int2 q1 = sxy1[j];
-                    const float4 z4 = sz[j];
-                    TriSetup s;
-                    s.X[0] = q0.x; s.X[1] = q0.y; s.X[2] = q0.z;
-                    s.Y[0] = q0.w; s.Y[1] = q1.x; s.Y[2] = q1.y;
-                    s.zn[0] = z4.x; s.zn[1] = z4.y; s.zn[2] = z4.z;
-                    s.Af = z4.w;
-                    s.meta = fl & 0xffff;
-                    const float el[3] = {e4.x, e4.y, e4.z};
-                    if (BAND == 2 && !inE) continue;
-                    if (fl >> 16) {
-                        // exact in 32-bit integers (see the staging test)
-                        int ex[3], ey[3], len2[3];
-                        rl_edges(s, ex, ey);
-#pragma unroll
-                        for (int i = 0; i < 3; i++) len2[i] = __mul24(ex[i], ex[i]) + __mul24(ey[i], ey[i]);
-                        int qx[3], qy[3], E[3];
-#pragma unroll
-                        for (int v = 0; v < 3; v++) {
-                            qx[v] = px - s.X[v];
-                            qy[v] = py - s.Y[v];
-                        }
-#pragma unroll
-                        for (int i = 0; i < 3; i++) {
-                            const int a = (i + 1) % 3;
-                            E[i] = __mul24(ex[i], qy[a]) - __mul24(ey[i], qx[a]);
-                        }
-                        if (walk == 0)
-                            rl_merge<KL, true, int, SM>(s, E, el, t, px, py, dscale, r, reach, key, id, qx, qy, ex,
-                                                        ey, len2);
-                        else
-                            rl_merge<KL, false, int, SM>(s, E, el, t, px, py, dscale, r, reach, key, id, qx, qy, ex,
-                                                         ey, len2);
-                    } else {
-                        double E[3];
-#pragma unroll
-                        for (int i = 0; i < 3; i++) E[i] = dr_edge(s.X, s.Y, i, px, py);
-                        if (walk == 0) rl_merge<KL, true, double, SM>(s, E, el, t, px, py, dscale, r, reach, key, id);
-                        else rl_merge<KL, false, double, SM>(s, E, el, t, px, py, dscale, r, reach, key, id);
-                    }
-                }
-                // keys only decrease: refresh the strip's bounds
-                const float wm = wave_max(BAND == 2 && !inE ? 0.0f : key[KL - 1]);
-                wmax_bits = __float_as_int(wm);
-                // a soft candidate needs dn <= 2 (wmax - 0.5) + one key rounding;
-                // a pixel gap g (L-infinity, whole pixels) gives dn > (g - 1) / W
-                const float dp = (2.0f * (wm - 0.5f) + 1e-7f) * (float)W * 1.001f;
-                gap_max = (int)floorf(fminf(dp, 1.0e9f)) + 1;
-            }
+            // keys only decrease: refresh the strip's bound
+            wmax_bits = __float_as_int(wave_max(key[KL - 1]));
         }
     }
     __syncthreads();
@@ -777,10 +748,12 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
             }
         }
     }
-    if (p == 0 && !keep_counts) counts[bt] = 0;   // every lane has read it before the first barrier
-    if (BAND == 2 && !inE) return;
+    if (p == 0 && !keep_counts) {   // every lane has read them before the first barrier
+        counts[bt] = 0;
+        if (FRONT) counts[far_counts + bt] = 0;
+    }
     if constexpr (KL == K) {
-        resolve_store<K, SOFT>(sv, key, id, b, x, y, px, py, H, W, dscale, tri_id, bary, dist);
+        resolve_store<K, FRONT>(sv, key, id, b, x, y, px, py, H, W, dscale, tri_id, bary, dist);
     } else {
         float kk[K];
         int ii[K];
@@ -789,7 +762,364 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
             kk[k] = k < KL ? key[k] : 2.0f;
             ii[k] = k < KL ? id[k] : -1;
         }
-        resolve_store<K, SOFT>(sv, kk, ii, b, x, y, px, py, H, W, dscale, tri_id, bary, dist);
+        resolve_store<K, FRONT>(sv, kk, ii, b, x, y, px, py, H, W, dscale, tri_id, bary, dist);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// soft rasterizer (r > 0): four workgroups per 16 x 16 tile, one for each
+// 8 x 8 quadrant; each wavefront owns a 4 x 4 block of pixels, and its four
+// slices of 16 lanes test four triangles at a time against the same 16 pixels.
+//
+// What bounds it is the number of (wavefront, triangle) steps, each some 150
+// VALU instructions: a step's cost does not depend on how many of its pixels
+// the triangle reaches.  A triangle of side s within d pixels of a block has
+// to be tested by all blocks in (side + 2 d + s)^2 pixels around it, so the
+// smaller block needs fewer: at s = 1.5, d = 2, a 16 x 4 strip sees the
+// triangles of 230 square pixels one after another, a 4 x 4 block those of
+// 90, four at a time.  Measured against strips of 16 x 4 that walked the whole
+// bin three times: 21.5 -> 12.4 ms (8 views 2048^2, 1 M triangles, K = 3),
+// 1.40 -> 0.58 ms (16 views 512^2, 82 k triangles, K = 3, banded; front pass
+// 0.36 -> 0.13), 0.20 -> 0.055 ms (6 views 256^2, 5 k triangles, banded).
+//
+// Triangles are visited nearest first, so that the lists fill with near
+// fragments early and cull the rest (gap: L-infinity pixel distance from the
+// block to the vertex box):
+//  0. gap 0 (the triangle may cover a pixel centre of the block),
+//  1. gap up to RL_NEAR,
+//  2. the others, only while the block's K-th keys leave room, ring by ring of
+//     the quadrant's gap; the rings' bounds come from a histogram of the gaps,
+//     about RS_RING triangles each.
+// 0 and 1 read the near end of the tile's bin only; most quadrants end there.
+// A quadrant's triangles are compacted from the bin by their 16-byte culling
+// entry before their records are loaded and staged in LDS.  After every 64
+// staged triangles the four slices merge their lists, so that each again holds
+// the block's true list.
+//
+// Every culling test is exact by construction (bounds carry rounding margins):
+//  * the smallest key a triangle can give the block (half its lowest vertex
+//    depth, or the soft key of the gap) is above every pixel's K-th key;
+//  * per lane, a soft candidate is dropped before its segment distances when
+//    the line distance of an edge it lies outside of already rules it out.
+//
+// BANDED: only pixels of the edge mask `band` are searched and written (the
+// second pass of the edge-band form; see k_raster_list's FRONT).
+// ---------------------------------------------------------------------------
+#define RS_CAP 384   // staged triangles: one compacted load of 256 beside what waits
+#define RS_RING 96
+
+struct SoftStage {
+    int4 xy0[RS_CAP];     // X0 X1 X2 Y0
+    int4 xy1[RS_CAP];     // Y1 Y2, meta | 32-bit-exact flag << 16, triangle id
+    float4 z[RS_CAP];     // zn0 zn1 zn2 Af
+    float4 el[RS_CAP];    // sqrtf of the squared edge lengths, the hard keys' lower bound
+    int2 hb[RS_CAP];      // pixels with centres in the vertex box
+};
+
+// A block's search state: uniform over its wavefront except key and id.
+template <int K> struct SoftBlock {
+    float key[K];
+    int id[K];
+    int px, py;          // this lane's pixel centre
+    bool on;             // this lane's pixel is searched
+    int x0, y0;          // the block's first pixel
+    int gap_max;         // triangles farther (pixels) than this are culled
+    int wmax_bits;       // bound on the pixels' K-th keys
+};
+
+// Tests the cnt staged triangles of walk WALK against the wavefront's block.
+template <int K, int WALK>
+__device__ __forceinline__ void soft_block(const SoftStage &sg, int cnt, SoftBlock<K> &a, float dscale, float r,
+                                           float reach, int W) {
+    const int lane = lane_id(), slice = lane >> 4;
+    for (int c = 0; c < cnt; c += 64) {
+        // 64 triangles tested at once, one per lane
+        const int e = c + lane;
+        bool want = false;
+        if (e < cnt) {
+            const int2 hb = sg.hb[e];
+            const int g = box_gap(hb.x, hb.y, a.x0, a.x0 + 3, a.y0, a.y0 + 3);
+            if (WALK == 0) want = g == 0 && __float_as_int(sg.el[e].w) <= a.wmax_bits;
+            else if (WALK == 1) want = g > 0 && g <= RL_NEAR && g <= a.gap_max;
+            else want = g > RL_NEAR && g <= a.gap_max;
+        }
+        unsigned long long todo = __ballot(want);
+        if (!todo) continue;
+        while (todo) {
+            // the next four, one for each slice
+            const int j0 = __ffsll((long long)todo) - 1;
+            todo &= todo - 1ull;
+            const int j1 = todo ? __ffsll((long long)todo) - 1 : -1;
+            todo &= todo - 1ull;   // 0 stays 0
+            const int j2 = todo ? __ffsll((long long)todo) - 1 : -1;
+            todo &= todo - 1ull;
+            const int j3 = todo ? __ffsll((long long)todo) - 1 : -1;
+            todo &= todo - 1ull;
+            int j = slice < 2 ? (slice == 0 ? j0 : j1) : (slice == 2 ? j2 : j3);
+            if (j < 0 || !a.on) continue;
+            j += c;
+            const int4 q0 = sg.xy0[j], q1 = sg.xy1[j];
+            const float4 e4 = sg.el[j];
+            TriSetup s;
+            s.X[0] = q0.x; s.X[1] = q0.y; s.X[2] = q0.z;
+            s.Y[0] = q0.w; s.Y[1] = q1.x; s.Y[2] = q1.y;
+            s.meta = q1.z & 0xffff;
+            if (WALK == 0) {
+                const float4 z4 = sg.z[j];
+                s.zn[0] = z4.x; s.zn[1] = z4.y; s.zn[2] = z4.z;
+                s.Af = z4.w;
+            }
+            const float el[3] = {e4.x, e4.y, e4.z};
+            if (q1.z >> 16) {
+                // exact in 32-bit integers (see the staging test)
+                int ex[3], ey[3], len2[3], qx[3], qy[3], E[3];
+                rl_edges(s, ex, ey);
+#pragma unroll
+                for (int i = 0; i < 3; i++) {
+                    len2[i] = __mul24(ex[i], ex[i]) + __mul24(ey[i], ey[i]);
+                    qx[i] = a.px - s.X[i];
+                    qy[i] = a.py - s.Y[i];
+                }
+#pragma unroll
+                for (int i = 0; i < 3; i++) {
+                    const int v = (i + 1) % 3;
+                    E[i] = __mul24(ex[i], qy[v]) - __mul24(ey[i], qx[v]);
+                }
+                rl_merge<K, WALK == 0, int>(s, E, el, q1.w, a.px, a.py, dscale, r, reach, a.key, a.id, qx, qy, ex, ey,
+                                            len2);
+            } else {
+                double E[3];
+#pragma unroll
+                for (int i = 0; i < 3; i++) E[i] = dr_edge(s.X, s.Y, i, a.px, a.py);
+                rl_merge<K, WALK == 0, double>(s, E, el, q1.w, a.px, a.py, dscale, r, reach, a.key, a.id);
+            }
+        }
+        // the slices' lists become one
+#pragma unroll
+        for (int o = 16; o < 64; o <<= 1) {
+            float kk[K];
+            int ii[K];
+#pragma unroll
+            for (int k = 0; k < K; k++) {
+                kk[k] = __shfl_xor(a.key[k], o, 64);
+                ii[k] = __shfl_xor(a.id[k], o, 64);
+            }
+#pragma unroll
+            for (int k = 0; k < K; k++)
+                if (kk[k] < 2.0f) rl_insert<K>(kk[k], ii[k], a.key, a.id);
+        }
+        // keys only decrease: refresh the block's bounds
+        float wm = a.on ? a.key[K - 1] : 0.0f;
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) wm = fmaxf(wm, __shfl_xor(wm, o, 64));
+        wm = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(wm)));
+        a.wmax_bits = __float_as_int(wm);
+        // a soft candidate needs dn <= 2 (wmax - 0.5) + one key rounding;
+        // a pixel gap g (L-infinity, whole pixels) gives dn > (g - 1) / W
+        const float dp = (2.0f * (wm - 0.5f) + 1e-7f) * (float)W * 1.001f;
+        a.gap_max = min(a.gap_max, (int)floorf(fminf(dp, 1.0e9f)) + 1);
+    }
+}
+
+template <int K, bool BANDED>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
+    k_raster_soft(const TriSetup *__restrict__ setup, const int4 *__restrict__ cullq, int32_t *__restrict__ counts,
+                  const int32_t *__restrict__ bins, int cap, int T, int H, int W, int ntx, int nt, int64_t n_tiles,
+                  float r, int margin, int32_t *__restrict__ tri_id, float2 *__restrict__ bary,
+                  float *__restrict__ dist, const uint8_t *__restrict__ band,
+                  unsigned long long *__restrict__ status) {
+    __shared__ SoftStage sg;
+    __shared__ int wcnt[2][4], sgap[4], hist[64];
+    const int64_t blk = xcd_block();
+    const int bt = (int)(blk >> 2), q = (int)(blk & 3);
+    const int b = bt / nt, tile = bt - b * nt;
+    const int tx = tile % ntx, ty = tile / ntx;
+    const int p = threadIdx.x, lane = p & 63, w = p >> 6;
+    const int qx0 = tx * DRESSI_TILE + (q & 1) * 8, qy0 = ty * DRESSI_TILE + (q >> 1) * 8;
+    SoftBlock<K> a;
+    a.x0 = __builtin_amdgcn_readfirstlane(qx0 + (w & 1) * 4);
+    a.y0 = __builtin_amdgcn_readfirstlane(qy0 + (w >> 1) * 4);
+    const int x = a.x0 + (lane & 3), y = a.y0 + ((lane >> 2) & 3);
+    a.px = DRESSI_SUBPIX * x + DRESSI_SUBPIX / 2;
+    a.py = DRESSI_SUBPIX * y + DRESSI_SUBPIX / 2;
+    const float dscale = (float)W * 256.0f;
+    const float reach = r * dscale * 1.001f;   // conservative, in fixed-point units
+    const TriSetup *__restrict__ sv = setup + (int64_t)b * T;
+    const int4 *__restrict__ cq = cullq + (int64_t)b * T;
+    const int32_t *__restrict__ bin = bins + (int64_t)bt * cap;
+    int n = counts[bt], nf = counts[n_tiles + bt];
+    if (!BANDED && q == 0 && p == 0 && n + nf > cap) {   // the front pass reports it in the banded form
+        atomicMax(&status[0], 1ull);
+        atomicMax(&status[1], (unsigned long long)(n + nf));
+    }
+    n = min(n, cap);
+    nf = min(nf, cap);
+    a.on = x < W && y < H;
+    if (BANDED) a.on = a.on && band[((int64_t)b * H + y) * W + x] != 0;
+    // (the counts are an operand: every lane has them before the barrier)
+    const int any = __syncthreads_or(a.on || n < 0 || nf < 0);
+    // the tile's four workgroups have read its counts once each has passed
+    // its barrier; the last one to say so sets them back to zero
+    if (p == 0 && atomicAdd(&counts[2 * n_tiles + bt], 1) == 3) {
+        counts[bt] = 0;
+        counts[n_tiles + bt] = 0;
+        counts[2 * n_tiles + bt] = 0;
+    }
+    if (!any) return;
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        a.key[k] = 2.0f;   // empty: above every fragment key
+        a.id[k] = -1;
+    }
+    // a block with no pixel to search wants nothing
+    const bool block_on = __ballot(a.on) != 0ull;
+    a.gap_max = block_on ? margin : -1;
+    a.wmax_bits = block_on ? __float_as_int(2.0f) : -1;
+
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int cnt = 0, par = 0;
+    bool several = false;   // the staged triangles went through in more than one batch
+    // Compacts the entries [0, m) of the bin (near end, then far end) whose
+    // gap to the quadrant is in [lo, hi] into the stage, running walk WALK on
+    // it whenever the next ones do not fit; the rest stays staged.
+    auto gather = [&](auto walk, int m, int lo, int hi) {
+        constexpr int WALK = decltype(walk)::value;
+        cnt = 0;
+        several = false;
+        for (int c0 = 0; c0 < m; c0 += 256) {
+            const int e = c0 + p;
+            bool want = false;
+            int t = 0;
+            int4 c = make_int4(0, 0, 0, 0);
+            if (e < m) {
+                t = bin[e < n ? e : cap - 1 - (e - n)];
+                c = cq[t];
+                const int g = box_gap(c.x, c.y, qx0, qx0 + 7, qy0, qy0 + 7);
+                want = g >= lo && g <= hi;
+            }
+            const unsigned long long bal = __ballot(want);
+            if (lane == 0) wcnt[par][w] = __popcll(bal);
+            __syncthreads();
+            const int n0 = wcnt[par][0], n1 = wcnt[par][1], n2 = wcnt[par][2], n3 = wcnt[par][3];
+            par ^= 1;
+            const int tot = n0 + n1 + n2 + n3;
+            if (cnt + tot > RS_CAP) {
+                soft_block<K, WALK>(sg, cnt, a, dscale, r, reach, W);
+                several = true;
+                cnt = 0;
+                __syncthreads();
+            }
+            if (want) {
+                const int at = cnt + (w > 0 ? n0 : 0) + (w > 1 ? n1 : 0) + (w > 2 ? n2 : 0) + __popcll(bal & below);
+                const TriSetup s = sv[t];
+                // 32-bit integer path: every pixel-to-vertex difference over the
+                // quadrant and every edge vector below 2^15 in magnitude
+                const int lim15 = 1 << 15, span = DRESSI_SUBPIX * 7;
+                const int px0 = DRESSI_SUBPIX * qx0 + DRESSI_SUBPIX / 2, py0 = DRESSI_SUBPIX * qy0 + DRESSI_SUBPIX / 2;
+                bool small = true;
+#pragma unroll
+                for (int i = 0; i < 3; i++) {
+                    small = small && abs(px0 - s.X[i]) < lim15 && abs(px0 + span - s.X[i]) < lim15 &&
+                            abs(py0 - s.Y[i]) < lim15 && abs(py0 + span - s.Y[i]) < lim15;
+                    const int v = (i + 1) % 3, u = (i + 2) % 3;
+                    small = small && abs(s.X[u] - s.X[v]) < lim15 && abs(s.Y[u] - s.Y[v]) < lim15;
+                }
+                sg.xy0[at] = make_int4(s.X[0], s.X[1], s.X[2], s.Y[0]);
+                sg.xy1[at] = make_int4(s.Y[1], s.Y[2], (s.meta & 0xffff) | (small ? 0x10000 : 0), t);
+                sg.z[at] = make_float4(s.zn[0], s.zn[1], s.zn[2], s.Af);
+                sg.el[at] = make_float4(s.elen[0], s.elen[1], s.elen[2], __int_as_float(c.z));
+                sg.hb[at] = make_int2(c.x, c.y);
+            }
+            cnt += tot;
+        }
+        __syncthreads();
+    };
+    auto run = [&](auto walk) {
+        soft_block<K, decltype(walk)::value>(sg, cnt, a, dscale, r, reach, W);
+    };
+    // the largest gap that a block of the quadrant still looks at
+    auto widest = [&]() {
+        if (lane == 0) sgap[w] = a.gap_max;
+        __syncthreads();
+        return max(max(sgap[0], sgap[1]), max(sgap[2], sgap[3]));
+    };
+    using W0 = std::integral_constant<int, 0>;
+    using W1 = std::integral_constant<int, 1>;
+    using W2 = std::integral_constant<int, 2>;
+    // covering triangles; the near ones are staged with them and stay if all fit
+    gather(W0{}, n, 0, RL_NEAR);
+    run(W0{});
+    int G = widest();
+    if (G > 0) {
+        if (several) gather(W1{}, n, 0, min(RL_NEAR, G));
+        run(W1{});
+        __syncthreads();
+        G = widest();
+        if (G > RL_NEAR) {
+            if (p < 64) hist[p] = 0;
+            __syncthreads();
+            const int m = n + nf;
+            for (int e = p; e < m; e += 256) {
+                const int4 c = cq[bin[e < n ? e : cap - 1 - (e - n)]];
+                const int g = box_gap(c.x, c.y, qx0, qx0 + 7, qy0, qy0 + 7);
+                if (g <= G) atomicAdd(&hist[min(g, 63)], 1);
+            }
+            __syncthreads();
+            // this lane: the number of triangles with a gap of at most `lane`
+            int cum = hist[lane];
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int v = __shfl_up(cum, o, 64);
+                if (lane >= o) cum += v;
+            }
+            int done = -1, goal = RS_RING;
+            while (done < G) {
+                const unsigned long long reached = __ballot(cum >= goal);
+                int hi = reached ? __ffsll((long long)reached) - 1 : G;
+                if (hi >= 63 || hi > G) hi = G;   // the last bin holds every larger gap
+                hi = max(hi, min(RL_NEAR + 1, G));
+                if (hi <= done) {
+                    goal += RS_RING;
+                    continue;
+                }
+                gather(W2{}, m, done + 1, hi);
+                run(W2{});
+                __syncthreads();
+                done = hi;
+                goal = __shfl(cum, min(hi, 63), 64) + 4 * RS_RING;
+                G = widest();
+            }
+        }
+    }
+    // the quadrant's lists to LDS, then one lane per (pixel, layer) resolves
+    // them (a wavefront writes rows of eight pixels of one layer)
+    __syncthreads();
+    float *fkey = reinterpret_cast<float *>(sg.xy0);
+    int *fid = reinterpret_cast<int *>(sg.xy1);
+    if (lane < 16) {
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            fkey[k * 64 + w * 16 + lane] = a.on ? a.key[k] : -1.0f;
+            fid[k * 64 + w * 16 + lane] = a.id[k];
+        }
+    }
+    __syncthreads();
+    const int rx = lane & 7, ry = lane >> 3;
+    const int ox = qx0 + rx, oy = qy0 + ry;
+    const int from = ((ry >> 2) * 2 + (rx >> 2)) * 16 + (ry & 3) * 4 + (rx & 3);
+    for (int k = w; k < K; k += 4) {
+        const float kf = fkey[k * 64 + from];
+        const int t = fid[k * 64 + from];
+        if (kf < 0.0f) continue;   // not this pass's pixel
+        const int64_t o = (((int64_t)b * K + k) * H + oy) * W + ox;
+        if (t < 0) {
+            tri_id[o] = -1;
+            bary[o] = make_float2(0.0f, 0.0f);
+            dist[o] = 0.0f;
+            continue;
+        }
+        resolve_frag<true>(sv[t], t, DRESSI_SUBPIX * ox + DRESSI_SUBPIX / 2, DRESSI_SUBPIX * oy + DRESSI_SUBPIX / 2,
+                           kf, dscale, o, tri_id, bary, dist);
     }
 }
 
@@ -854,21 +1184,34 @@ __global__ void k_raster_direct_resolve(const float4 *__restrict__ pos_clip, con
 // with LDS atomics (small triangles) or pixel-parallel with register lists
 // (large triangles); dressi_tune picks one per context.
 template <int K>
-static void launch_raster_k(bool soft, int hard_pix, int hyb_w, dim3 g, hipStream_t st, const TriSetup *setup,
+static void launch_raster_k(int hard_pix, int hyb_w, dim3 g, hipStream_t st, const TriSetup *setup,
                             int32_t *counts, const int32_t *bins, int cap, int T, int H, int W, int ntx, int nt,
-                            float r, int32_t *tid, float2 *bary, float *dist) {
-    if (soft)
-        DR_LAUNCH("k_raster_list", (k_raster_list<K, true>), g, DRESSI_TILE_PIX, 0, st, setup, counts, bins, cap,
-                  T, H, W, ntx, nt, r, tid, bary, dist, 0, nullptr, 0);
-    else if (hard_pix == 2 && K == 1)
-        DR_LAUNCH("k_raster_list", (k_raster_list<1, false, true>), g, DRESSI_TILE_PIX, 0, st, setup, counts,
-                  bins, cap, T, H, W, ntx, nt, r, tid, bary, dist, hyb_w, nullptr, 0);
+                            int32_t *tid, float2 *bary) {
+    if (hard_pix == 2 && K == 1)
+        DR_LAUNCH("k_raster_list", (k_raster_list<1, true>), g, DRESSI_TILE_PIX, 0, st, setup, counts, bins, cap, T,
+                  H, W, ntx, nt, tid, bary, nullptr, hyb_w, 0, 0, nullptr);
     else if (hard_pix == 1 || hard_pix == 2)
-        DR_LAUNCH("k_raster_list", (k_raster_list<K, false>), g, DRESSI_TILE_PIX, 0, st, setup, counts, bins,
-                  cap, T, H, W, ntx, nt, r, tid, bary, dist, 0, nullptr, 0);
+        DR_LAUNCH("k_raster_list", (k_raster_list<K>), g, DRESSI_TILE_PIX, 0, st, setup, counts, bins, cap, T, H, W,
+                  ntx, nt, tid, bary, nullptr, 0, 0, 0, nullptr);
     else
-        DR_LAUNCH("k_raster", (k_raster<K, false>), g, DRESSI_TILE_PIX, 0, st, setup, counts, bins, cap, T, H,
-                  W, ntx, nt, r, tid, bary, dist);
+        DR_LAUNCH("k_raster", (k_raster<K>), g, DRESSI_TILE_PIX, 0, st, setup, counts, bins, cap, T, H, W, ntx, nt,
+                  tid, bary);
+}
+
+// The soft layers of every pixel (edge == NULL) or of the edge mask's pixels.
+template <int K>
+static void launch_soft_k(const uint8_t *edge, int B, hipStream_t st, const TriSetup *setup, const int4 *cullq,
+                          int32_t *counts, const int32_t *bins, int cap, int T, int H, int W, int ntx, int nt,
+                          float r, int margin, int32_t *tid, float2 *bary, float *dist,
+                          unsigned long long *status) {
+    const int64_t tiles = (int64_t)B * nt;
+    const dim3 g((unsigned)(4 * tiles));
+    if (edge)
+        DR_LAUNCH("k_raster_soft", (k_raster_soft<K, true>), g, 256, 0, st, setup, cullq, counts, bins, cap, T, H, W,
+                  ntx, nt, tiles, r, margin, tid, bary, dist, edge, status);
+    else
+        DR_LAUNCH("k_raster_soft", (k_raster_soft<K, false>), g, 256, 0, st, setup, cullq, counts, bins, cap, T, H,
+                  W, ntx, nt, tiles, r, margin, tid, bary, dist, edge, status);
 }
 
 static int soft_margin(float r, int W) {
@@ -891,9 +1234,10 @@ static int tile_capacity(const dressi_ctx *ctx, int B, int T, int nt, int margin
     return cap;
 }
 
-static size_t raster_scratch(int B, int T, int nt, int cap, Carver &c, size_t *o) {
+static size_t raster_scratch(int B, int T, int nt, int cap, bool soft, Carver &c, size_t *o) {
     o[0] = c.take(sizeof(TriSetup) * (size_t)B * T);            // setup
     o[1] = c.take(sizeof(int32_t) * (size_t)B * nt * cap);      // bins
+    o[2] = soft ? c.take(sizeof(int4) * (size_t)B * T) : 0;     // culling entries
     return c.off;
 }
 
@@ -942,24 +1286,33 @@ static int rasterize_impl(dressi_ctx *ctx, const float *pos_clip, const int32_t 
     int cap = tile_capacity(ctx, B, T, nt, margin);
     const bool banded = soft && band >= -1;
     Carver c;
-    size_t o[2];
-    raster_scratch(B, T, nt, cap, c, o);
+    size_t o[3];
+    raster_scratch(B, T, nt, cap, soft, c, o);
     const size_t o_band = banded ? c.take(3 * (size_t)B * H * W) : 0;   // boundary, rows, edge mask
     rc = dressi_scratch(ctx, c.off, st);
     if (rc) return rc;
-    rc = dressi_counters(ctx, (size_t)B * nt, st);
+    rc = dressi_counters(ctx, (size_t)B * nt * (soft ? 3 : 1), st);   // soft: near, far, workgroups done
     if (rc) return rc;
     void *S = ctx->scratch;
     TriSetup *setup = at<TriSetup>(S, o[0]);
     int32_t *bins = at<int32_t>(S, o[1]);
     int32_t *counts = ctx->counters;
     int64_t ntri = (int64_t)B * T;
-    if (ntri > 0)
-        DR_LAUNCH("k_setup_bin", (k_setup_bin), (int)((ntri + 255) / 256), 256, 0, st,
-                  reinterpret_cast<const float4 *>(pos_clip), tris, vp, B, V, T, H, W, cull, margin, ntx,
-                  nt, cap, setup, counts, bins, reinterpret_cast<unsigned long long *>(ctx->status));
+    int4 *cullq = soft ? at<int4>(S, o[2]) : nullptr;
+    unsigned long long *status = reinterpret_cast<unsigned long long *>(ctx->status);
+    const float4 *pc4 = reinterpret_cast<const float4 *>(pos_clip);
+    if (ntri > 0) {
+        const int gb = (int)((ntri + 255) / 256);
+        if (soft)
+            DR_LAUNCH("k_setup_bin", (k_setup_bin<true>), gb, 256, 0, st, pc4, tris, vp, B, V, T, H, W, cull, margin,
+                      ntx, nt, cap, setup, cullq, counts, bins, status);
+        else
+            DR_LAUNCH("k_setup_bin", (k_setup_bin<false>), gb, 256, 0, st, pc4, tris, vp, B, V, T, H, W, cull, margin,
+                      ntx, nt, cap, setup, cullq, counts, bins, status);
+    }
     dim3 g((unsigned)(B * nt));
     float2 *b2 = reinterpret_cast<float2 *>(bary);
+    const uint8_t *mask = nullptr;
     if (banded) {
         // first pass: the front hard fragment of every pixel (the bins are
         // read again by the second pass, so their counts are kept)
@@ -967,37 +1320,21 @@ static int rasterize_impl(dressi_ctx *ctx, const float *pos_clip, const int32_t 
         uint8_t *rows = bnd + (size_t)B * H * W, *edge = rows + (size_t)B * H * W;
         const int keep = band >= 0 ? 1 : 0;
         switch (K) {
-#define DR_BAND1(KK)                                                                                       \
-    case KK:                                                                                               \
-        DR_LAUNCH("k_raster_list_band1", (k_raster_list<KK, true, false, 1>), g, DRESSI_TILE_PIX, 0, st, setup, \
-                  counts, bins, cap, T, H, W, ntx, nt, r, tri_id, b2, dist, 0, nullptr, keep);            \
-        break;
-            DR_BAND1(1) DR_BAND1(2) DR_BAND1(3) DR_BAND1(4) DR_BAND1(5)
-#undef DR_BAND1
+#define DR_FRONT(KK)                                                                                                 case KK:                                                                                                             DR_LAUNCH("k_raster_front", (k_raster_list<KK, true, true>), g, DRESSI_TILE_PIX, 0, st, setup, counts,                     bins, cap, T, H, W, ntx, nt, tri_id, b2, dist, ctx->hybrid_weight, keep, (int64_t)B * nt,                        status);                                                                                               break;
+            DR_FRONT(1) DR_FRONT(2) DR_FRONT(3) DR_FRONT(4) DR_FRONT(5)
+#undef DR_FRONT
         }
-        if (band >= 0) {
-            dressi_edge_mask(tri_id, dist, B, K, H, W, band, bnd, rows, edge, st);
-            switch (K) {
-#define DR_BAND2(KK)                                                                                       \
-    case KK:                                                                                               \
-        DR_LAUNCH("k_raster_list", (k_raster_list<KK, true, false, 2>), g, DRESSI_TILE_PIX, 0, st, setup,    \
-                  counts, bins, cap, T, H, W, ntx, nt, r, tri_id, b2, dist, 0, edge, 0);                  \
-        break;
-                DR_BAND2(1) DR_BAND2(2) DR_BAND2(3) DR_BAND2(4) DR_BAND2(5)
-#undef DR_BAND2
-            }
-        }
-        return dressi_launch_check(ctx, "rasterize_banded");
+        if (band < 0) return dressi_launch_check(ctx, "rasterize_banded");
+        dressi_edge_mask(tri_id, dist, B, K, H, W, band, bnd, rows, edge, st);
+        mask = edge;
     }
     const int hp = ctx->hard_raster, hw = ctx->hybrid_weight;
     switch (K) {
-    case 1: launch_raster_k<1>(soft, hp, hw, g, st, setup, counts, bins, cap, T, H, W, ntx, nt, r, tri_id, b2, dist); break;
-    case 2: launch_raster_k<2>(soft, hp, hw, g, st, setup, counts, bins, cap, T, H, W, ntx, nt, r, tri_id, b2, dist); break;
-    case 3: launch_raster_k<3>(soft, hp, hw, g, st, setup, counts, bins, cap, T, H, W, ntx, nt, r, tri_id, b2, dist); break;
-    case 4: launch_raster_k<4>(soft, hp, hw, g, st, setup, counts, bins, cap, T, H, W, ntx, nt, r, tri_id, b2, dist); break;
-    default: launch_raster_k<5>(soft, hp, hw, g, st, setup, counts, bins, cap, T, H, W, ntx, nt, r, tri_id, b2, dist); break;
+#define DR_RASTER(KK)                                                                                                case KK:                                                                                                             if (soft)                                                                                                            launch_soft_k<KK>(mask, B, st, setup, cullq, counts, bins, cap, T, H, W, ntx, nt, r, margin, tri_id,                               b2, dist, status);                                                                         else                                                                                                                 launch_raster_k<KK>(hp, hw, g, st, setup, counts, bins, cap, T, H, W, ntx, nt, tri_id, b2);                  break;
+        DR_RASTER(1) DR_RASTER(2) DR_RASTER(3) DR_RASTER(4) DR_RASTER(5)
+#undef DR_RASTER
     }
-    return dressi_launch_check(ctx, "rasterize");
+    return dressi_launch_check(ctx, banded ? "rasterize_banded" : "rasterize");
 }
 
 extern "C" int dressi_rasterize(dressi_ctx *ctx, const float *pos_clip, const int32_t *tris, int B,
@@ -2043,8 +2380,8 @@ size_t dr_need_raster(const dressi_limits &l, int64_t cap) {
     size_t need = 0;
     {
         Carver c;
-        size_t o[2];
-        raster_scratch(B, T, nt, (int)cap, c, o);
+        size_t o[3];
+        raster_scratch(B, T, nt, (int)cap, l.r > 0.0f, c, o);
         if (l.r > 0.0f) c.take(3 * (size_t)B * H * W);
         need = std::max(need, c.off);
     }
@@ -2096,7 +2433,7 @@ extern "C" int dressi_reserve_limits(dressi_ctx *ctx, const dressi_limits *l) {
     int rc = dressi_reserve(ctx, bytes, cap);
     if (rc) return rc;
     const size_t nt = (size_t)tiles_x(l->W) * tiles_y(l->H);
-    size_t nc = std::max((size_t)std::max(l->B, 1) * nt, (size_t)std::max(l->B, 1) * std::max(l->T, 0));
+    size_t nc = std::max((size_t)std::max(l->B, 1) * nt * (l->r > 0.0f ? 3 : 1), (size_t)std::max(l->B, 1) * std::max(l->T, 0));
     // one layer: the binless hard rasterizer's per-pixel keys (two counters a
     // pixel; after the record counters when it builds the fragment index too)
     if (l->K <= 1)
@@ -2115,8 +2452,8 @@ extern "C" size_t dressi_scratch_bytes(int B, int V, int T, int H, int W, int K,
     auto upd = [&](size_t v) { need = v > need ? v : need; };
     {
         Carver c;
-        size_t o[2];
-        raster_scratch(B, T, nt, default_tile_capacity(B, T, nt, margin), c, o);
+        size_t o[3];
+        raster_scratch(B, T, nt, default_tile_capacity(B, T, nt, margin), r > 0.0f, c, o);
         upd(c.off);
     }
     {   // a backward call that builds its own fragment index and adjacency
