@@ -62,12 +62,13 @@ __device__ __forceinline__ int next_tile(int cur, int tx0, int tx1, int ty1, int
 // pixels of the tile fill it from slot 0 (counts[tile]), the others, which
 // only a pixel far from every covering triangle looks at, from its last slot
 // down (counts[B nt + tile]); the rasterizer reports an overflow, since only
-// the sum of both tells.  The 16 bytes that its culling needs go to `cullq`.
+// the sum of both tells.  The vertex boxes, which its culling needs, go to
+// `boxes` (x0, x1, y0, y1 in fixed point).
 #define RL_NEAR 2
 template <bool SOFT>
 __global__ void k_setup_bin(const float4 *__restrict__ pos_clip, const int32_t *__restrict__ tris,
                             Viewports vp, int B, int V, int T, int H, int W, int cull, int margin, int ntx,
-                            int nt, int cap, TriSetup *__restrict__ setup, int4 *__restrict__ cullq,
+                            int nt, int cap, TriSetup *__restrict__ setup, int4 *__restrict__ boxes,
                             int32_t *__restrict__ counts, int32_t *__restrict__ bins,
                             unsigned long long *__restrict__ status) {
     int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -89,7 +90,9 @@ __global__ void k_setup_bin(const float4 *__restrict__ pos_clip, const int32_t *
         }
         setup[gid] = s;
         if (SOFT) {
-            cullq[gid] = make_int4(s.hbox0, s.hbox1, s.zlb, 0);
+            boxes[gid] = !(s.meta & 1) ? make_int4(0, 0, 0, 0)
+                                       : make_int4(min(min(s.X[0], s.X[1]), s.X[2]), max(max(s.X[0], s.X[1]), s.X[2]),
+                                                   min(min(s.Y[0], s.Y[1]), s.Y[2]), max(max(s.Y[0], s.Y[1]), s.Y[2]));
             hb0 = s.hbox0;
             hb1 = s.hbox1;
         }
@@ -439,9 +442,19 @@ __device__ __forceinline__ void rl_tri_in_tile(int e, const int2 *sfi, const int
     }
 }
 
-// Puts (kf, t) into a sorted list of the K smallest distinct keys.
-template <int K>
-__device__ __forceinline__ void rl_insert(float kf, int t, float *key, int *id) {
+// Merges the hard fragment of triangle t at this lane's pixel, if it has one.
+template <int K, typename TE>
+__device__ __forceinline__ void rl_merge(const TriSetup &s, const TE *E, int t, float *key, int *id) {
+    bool in = true;
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        bool own = (s.meta >> (1 + i)) & 1;
+        in = in && (E[i] > 0 || (E[i] == 0 && own));
+    }
+    if (!in) return;
+    const float z = dr_depth(s, E);
+    if (!(z > 0.0f && z < 1.0f)) return;
+    const float kf = 0.5f * z;
     if (!(kf <= key[K - 1])) return;
     bool same = false;
 #pragma unroll
@@ -467,53 +480,6 @@ __device__ __forceinline__ void rl_insert(float kf, int t, float *key, int *id) 
         key[0] = kf;
         id[0] = t;
     }
-}
-
-// Merges the candidate fragment of triangle t at this lane's pixel.  MAYHARD
-// is false when no pixel centre of the wavefront can be inside the triangle.
-template <int K, bool MAYHARD, typename TE, bool SOFT = true>
-__device__ __forceinline__ void rl_merge(const TriSetup &s, const TE *E, const float *el, int t, int px,
-                                         int py, float dscale, float r, float reach, float *key, int *id,
-                                         const int *qx = nullptr, const int *qy = nullptr,
-                                         const int *ex = nullptr, const int *ey = nullptr,
-                                         const int *len2 = nullptr) {
-    bool in = MAYHARD;
-    if (MAYHARD) {
-#pragma unroll
-        for (int i = 0; i < 3; i++) {
-            bool own = (s.meta >> (1 + i)) & 1;
-            in = in && (E[i] > 0 || (E[i] == 0 && own));
-        }
-    }
-    float kf;
-    if (in) {
-        float z = dr_depth(s, E);
-        if (!(z > 0.0f && z < 1.0f)) return;
-        kf = 0.5f * z;
-    } else {
-        if (!SOFT) return;
-        // The distance to the triangle is at least the distance -E_i / |e_i|
-        // to the line of any edge the pixel lies outside of.  A soft fragment
-        // enters the list only if its key 0.5 + dn/2 is at most the list's
-        // last key, so it needs dn <= 2 (last - 0.5) (+ one rounding of the
-        // key) and dn <= r.  The bound is compared with a relative margin far
-        // above the float rounding of either side, so every fragment dropped
-        // here would also fail the exact tests below.
-        const float lim = fminf(reach, (2.0f * (key[K - 1] - 0.5f) + 2.4e-7f) * dscale * 1.001f);
-        if ((E[0] < 0 && (float)(-E[0]) > lim * el[0]) || (E[1] < 0 && (float)(-E[1]) > lim * el[1]) ||
-            (E[2] < 0 && (float)(-E[2]) > lim * el[2]))
-            return;
-        float best;
-        if constexpr (std::is_integral<TE>::value)
-            best = rl_segmin_i(qx, qy, ex, ey, len2, E, el);
-        else
-            best = rl_segmin(s, E, el, px, py);
-        float dn = best / dscale;
-        if (!(dn <= r)) return;
-        float h = 0.5f * dn;
-        kf = h + 0.5f;
-    }
-    rl_insert<K>(kf, t, key, id);
 }
 
 // HYB (hard, K = 1): every staged batch is rasterized either pixel-parallel
@@ -724,12 +690,12 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
                         const int a = (i + 1) % 3;
                         E[i] = __mul24(ex[i], py - s.Y[a]) - __mul24(ey[i], px - s.X[a]);
                     }
-                    rl_merge<KL, true, int, false>(s, E, nullptr, t, px, py, dscale, 0.0f, 0.0f, key, id);
+                    rl_merge<KL>(s, E, t, key, id);
                 } else {
                     double E[3];
 #pragma unroll
                     for (int i = 0; i < 3; i++) E[i] = dr_edge(s.X, s.Y, i, px, py);
-                    rl_merge<KL, true, double, false>(s, E, nullptr, t, px, py, dscale, 0.0f, 0.0f, key, id);
+                    rl_merge<KL>(s, E, t, key, id);
                 }
             }
             // keys only decrease: refresh the strip's bound
@@ -768,184 +734,295 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
 
 // ---------------------------------------------------------------------------
 // soft rasterizer (r > 0): four workgroups per 16 x 16 tile, one for each
-// 8 x 8 quadrant; each wavefront owns a 4 x 4 block of pixels, and its four
-// slices of 16 lanes test four triangles at a time against the same 16 pixels.
+// 8 x 8 quadrant; each wavefront owns a 4 x 4 block of pixels.
 //
-// What bounds it is the number of (wavefront, triangle) steps, each some 150
-// VALU instructions: a step's cost does not depend on how many of its pixels
-// the triangle reaches.  A triangle of side s within d pixels of a block has
-// to be tested by all blocks in (side + 2 d + s)^2 pixels around it, so the
-// smaller block needs fewer: at s = 1.5, d = 2, a 16 x 4 strip sees the
-// triangles of 230 square pixels one after another, a 4 x 4 block those of
-// 90, four at a time.  Measured against strips of 16 x 4 that walked the whole
-// bin three times: 21.5 -> 12.4 ms (8 views 2048^2, 1 M triangles, K = 3),
-// 1.40 -> 0.58 ms (16 views 512^2, 82 k triangles, K = 3, banded; front pass
-// 0.36 -> 0.13), 0.20 -> 0.055 ms (6 views 256^2, 5 k triangles, banded).
+// A (pixel, triangle) pair costs some 150 to 230 VALU instructions where it
+// is evaluated exactly, and few pairs are worth it: on a dense mesh most
+// triangles near a block are farther from most of its pixels than the K
+// fragments those already have.  So a wavefront first tests 64 triangles at a
+// time (one per lane) against its 16 pixels with the distance to the
+// triangle's vertex box, some six instructions a pixel, pushes the pairs that
+// pass onto a queue in LDS, and evaluates them 64 at a time, every lane busy.
+// Each pixel's K smallest distinct keys live in LDS; an evaluated pair goes
+// down the list with a 64-bit atomicMin of (key bits << 32 | triangle id) per
+// layer, carrying what it displaces and dropping what equals another key.
+// The lists do not depend on the order: a layer's entry only ever decreases,
+// so fragments of one key meet at the layer where they stop, and the smaller
+// id stays.
 //
 // Triangles are visited nearest first, so that the lists fill with near
-// fragments early and cull the rest (gap: L-infinity pixel distance from the
-// block to the vertex box):
-//  0. gap 0 (the triangle may cover a pixel centre of the block),
-//  1. gap up to RL_NEAR,
-//  2. the others, only while the block's K-th keys leave room, ring by ring of
-//     the quadrant's gap; the rings' bounds come from a histogram of the gaps,
-//     about RS_RING triangles each.
+// fragments early and cull the rest:
+//  0. triangles whose vertex box contains the pixel centre (the only ones
+//     that can cover it),
+//  1. those whose box is at most RL_NEAR pixels away,
+//  2. the others, only while some pixel's K-th key leaves room, ring by ring
+//     of their distance from the quadrant; the rings come from a histogram,
+//     the first holds at least RS_RING triangles.
 // 0 and 1 read the near end of the tile's bin only; most quadrants end there.
-// A quadrant's triangles are compacted from the bin by their 16-byte culling
-// entry before their records are loaded and staged in LDS.  After every 64
-// staged triangles the four slices merge their lists, so that each again holds
-// the block's true list.
+// A quadrant lists the triangles it wants by their 16-byte boxes before it
+// loads and stages their records, 256 at a time.
 //
 // Every culling test is exact by construction (bounds carry rounding margins):
-//  * the smallest key a triangle can give the block (half its lowest vertex
-//    depth, or the soft key of the gap) is above every pixel's K-th key;
-//  * per lane, a soft candidate is dropped before its segment distances when
-//    the line distance of an edge it lies outside of already rules it out.
+//  * the smallest key a triangle can give a pixel (half its lowest vertex
+//    depth, or the soft key of its box's distance) is above the K-th key;
+//  * a soft candidate is dropped before its segment distances when the line
+//    distance of an edge it lies outside of already rules it out.
+//
+// Measured (kernel; strips of 16 x 4 pixels walking the whole bin three times,
+// then 4 x 4 blocks evaluating four triangles a step, then this): 21.5, 12.4,
+// 6.7 ms for 8 views 2048^2, 1 M triangles, K = 3 (the pairs evaluated fell
+// from 2.0 G to 0.19 G); 1.40, 0.58, 0.34 ms for 16 views 512^2, 82 k triangles,
+// K = 3, banded (front pass 0.36 -> 0.14); 524, 146, 97 us for 2 views 640 x 480,
+// 20 k triangles, K = 2; 197, 55, 42 us for 6 views 256^2, 5 k triangles, banded.
+// What is left is latency: the chain bin -> boxes -> records of each list.
 //
 // BANDED: only pixels of the edge mask `band` are searched and written (the
 // second pass of the edge-band form; see k_raster_list's FRONT).
 // ---------------------------------------------------------------------------
-#define RS_CAP 384   // staged triangles: one compacted load of 256 beside what waits
-#define RS_RING 96
+#define RS_CAP 256     // staged triangles, one a lane
+#define RS_LIST 1536   // listed triangles
+#define RS_SEGMENT 1024   // bin entries a scan takes at once where a list may not hold all it wants
+#define RS_QUEUE 320   // queued pairs of a wavefront: fewer than 64 waiting, 4 pixels x 64 triangles
+#define RS_RING 24
+#define RS_RINGS 4096  // bin entries whose ring is kept in LDS
+#define RS_NEAR2 ((float)(RL_NEAR * DRESSI_SUBPIX) * (float)(RL_NEAR * DRESSI_SUBPIX))
 
 struct SoftStage {
     int4 xy0[RS_CAP];     // X0 X1 X2 Y0
     int4 xy1[RS_CAP];     // Y1 Y2, meta | 32-bit-exact flag << 16, triangle id
     float4 z[RS_CAP];     // zn0 zn1 zn2 Af
-    float4 el[RS_CAP];    // sqrtf of the squared edge lengths, the hard keys' lower bound
-    int2 hb[RS_CAP];      // pixels with centres in the vertex box
+    float4 el[RS_CAP];    // sqrtf of the squared edge lengths; a lower bound of its keys in a pixel of its box
 };
 
-// A block's search state: uniform over its wavefront except key and id.
-template <int K> struct SoftBlock {
-    float key[K];
-    int id[K];
-    int px, py;          // this lane's pixel centre
+// A block's search state.  Lane i (mod 16) keeps pixel i's bounds.
+struct SoftBlock {
+    int px0, py0;        // the block's first pixel centre
     bool on;             // this lane's pixel is searched
-    int x0, y0;          // the block's first pixel
-    int gap_max;         // triangles farther (pixels) than this are culled
-    int wmax_bits;       // bound on the pixels' K-th keys
+    int khi;             // bits of the pixel's K-th key (empty: above every key; not searched: -1)
+    float lim2;          // squared distance (fixed point) that can still enter its list; -1: none
+    int queued;          // pairs waiting
+    uint16_t *queue;     // staged triangle | pixel << 9
+    unsigned long long *list;   // [16][K] (key bits << 32 | id), ascending
 };
 
-// Tests the cnt staged triangles of walk WALK against the wavefront's block.
+// The squared distance (fixed point) between intervals [a0, a1] and [b0, b1]
+// of one axis; float, exact up to one rounding.
+__device__ __forceinline__ float axis_dist2(int a0, int a1, int b0, int b1) {
+    const float d = (float)max(max(a0 - b1, b0 - a1), 0);
+    return d * d;
+}
+__device__ __forceinline__ int min3i(int a, int b, int c) { return min(min(a, b), c); }
+__device__ __forceinline__ int max3i(int a, int b, int c) { return max(max(a, b), c); }
+
+// This lane's pixel bounds from its list.
+template <int K> __device__ __forceinline__ void soft_refresh(SoftBlock &a, float dscale, float reach) {
+    const unsigned hi = (unsigned)(a.list[(lane_id() & 15) * K + K - 1] >> 32);
+    // a soft candidate needs dn <= 2 (last - 0.5) + one key rounding, and dn <= r
+    const float key = __uint_as_float(hi);
+    float lim = hi == 0xffffffffu ? reach : fminf(reach, (2.0f * (key - 0.5f) + 2.4e-7f) * dscale * 1.001f);
+    a.khi = !a.on ? -1 : hi == 0xffffffffu ? 0x7fffffff : (int)hi;
+    a.lim2 = a.on && lim >= 0.0f ? lim * lim * 1.0001f : -1.0f;
+}
+
+// The key of a (pixel, triangle) pair and its place in the pixel's list.
+template <int K>
+__device__ __forceinline__ void soft_pair(const SoftStage &sg, const SoftBlock &a, int pair, float dscale, float r,
+                                          float reach) {
+    const int j = pair & 511, pi = pair >> 9;
+    unsigned long long *list = a.list + pi * K;
+    const unsigned last = (unsigned)(list[K - 1] >> 32);
+    const int px = a.px0 + (pi & 3) * DRESSI_SUBPIX, py = a.py0 + (pi >> 2) * DRESSI_SUBPIX;
+    const int4 q0 = sg.xy0[j], q1 = sg.xy1[j];
+    const float4 e4 = sg.el[j];
+    const float el[3] = {e4.x, e4.y, e4.z};
+    TriSetup s;
+    s.X[0] = q0.x; s.X[1] = q0.y; s.X[2] = q0.z;
+    s.Y[0] = q0.w; s.Y[1] = q1.x; s.Y[2] = q1.y;
+    s.meta = q1.z & 0xffff;
+    const float lim = last == 0xffffffffu
+                          ? reach
+                          : fminf(reach, (2.0f * (__uint_as_float(last) - 0.5f) + 2.4e-7f) * dscale * 1.001f);
+    // The distance to the triangle is at least the distance -E_i / |e_i| to
+    // the line of any edge the pixel lies outside of, compared with a relative
+    // margin far above the float rounding of either side, so every fragment
+    // dropped here would also fail the exact tests below.
+    bool in = true, out = false;
+    float kf;
+    const auto sides = [&](const auto *E) {
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            const bool own = (s.meta >> (1 + i)) & 1;
+            in = in && (E[i] > 0 || (E[i] == 0 && own));
+            out = out || (E[i] < 0 && (float)(-E[i]) > lim * el[i]);
+        }
+        return in || !out;
+    };
+    const auto depth_key = [&](const auto *E) {
+        const float4 z4 = sg.z[j];
+        s.zn[0] = z4.x; s.zn[1] = z4.y; s.zn[2] = z4.z;
+        s.Af = z4.w;
+        const float z = dr_depth(s, E);
+        kf = 0.5f * z;
+        return z > 0.0f && z < 1.0f;
+    };
+    float best;
+    if (q1.z >> 16) {
+        // exact in 32-bit integers (see the staging test)
+        int ex[3], ey[3], qx[3], qy[3], E[3];
+        rl_edges(s, ex, ey);
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            qx[i] = px - s.X[i];
+            qy[i] = py - s.Y[i];
+        }
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            const int v = (i + 1) % 3;
+            E[i] = __mul24(ex[i], qy[v]) - __mul24(ey[i], qx[v]);
+        }
+        if (!sides(E)) return;
+        if (in) {
+            if (!depth_key(E)) return;
+        } else {
+            int len2[3];
+#pragma unroll
+            for (int i = 0; i < 3; i++) len2[i] = __mul24(ex[i], ex[i]) + __mul24(ey[i], ey[i]);
+            best = rl_segmin_i(qx, qy, ex, ey, len2, E, el);
+        }
+    } else {
+        double E[3];
+#pragma unroll
+        for (int i = 0; i < 3; i++) E[i] = dr_edge(s.X, s.Y, i, px, py);
+        if (!sides(E)) return;
+        if (in) {
+            if (!depth_key(E)) return;
+        } else {
+            best = rl_segmin(s, E, el, px, py);
+        }
+    }
+    if (!in) {
+        const float dn = best / dscale;
+        if (!(dn <= r)) return;
+        const float h = 0.5f * dn;
+        kf = h + 0.5f;
+    }
+    const unsigned bits = __float_as_uint(kf);
+    if (bits > last) return;   // keys are positive: their bits order like the values
+    unsigned long long v = ((unsigned long long)bits << 32) | (unsigned)q1.w;
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        const unsigned long long old = atomicMin(&list[k], v);
+        if ((unsigned)(old >> 32) == (unsigned)(v >> 32)) return;   // one key: the smaller id stayed
+        v = old > v ? old : v;
+        if (v == RS_EMPTY) return;
+    }
+}
+
+// Orders the wavefront's LDS accesses: lanes read what other lanes wrote.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Tests the cnt staged triangles against the wavefront's pixels and evaluates
+// the pairs of walk WALK (2: of triangles within blim2 of the block).
 template <int K, int WALK>
-__device__ __forceinline__ void soft_block(const SoftStage &sg, int cnt, SoftBlock<K> &a, float dscale, float r,
-                                           float reach, int W) {
-    const int lane = lane_id(), slice = lane >> 4;
+__device__ __forceinline__ void soft_block(const SoftStage &sg, int cnt, SoftBlock &a, float blim2, float dscale,
+                                           float r, float reach) {
+    const int lane = lane_id();
     for (int c = 0; c < cnt; c += 64) {
-        // 64 triangles tested at once, one per lane
         const int e = c + lane;
-        bool want = false;
-        if (e < cnt) {
-            const int2 hb = sg.hb[e];
-            const int g = box_gap(hb.x, hb.y, a.x0, a.x0 + 3, a.y0, a.y0 + 3);
-            if (WALK == 0) want = g == 0 && __float_as_int(sg.el[e].w) <= a.wmax_bits;
-            else if (WALK == 1) want = g > 0 && g <= RL_NEAR && g <= a.gap_max;
-            else want = g > RL_NEAR && g <= a.gap_max;
+        int x0 = 0, x1 = 0, y0 = 0, y1 = 0, zl = 0;
+        const bool have = e < cnt;
+        if (have) {
+            const int4 q0 = sg.xy0[e], q1 = sg.xy1[e];
+            x0 = min3i(q0.x, q0.y, q0.z);
+            x1 = max3i(q0.x, q0.y, q0.z);
+            y0 = min3i(q0.w, q1.x, q1.y);
+            y1 = max3i(q0.w, q1.x, q1.y);
+            if (WALK == 0) zl = __float_as_int(sg.el[e].w);
         }
-        unsigned long long todo = __ballot(want);
-        if (!todo) continue;
-        while (todo) {
-            // the next four, one for each slice
-            const int j0 = __ffsll((long long)todo) - 1;
-            todo &= todo - 1ull;
-            const int j1 = todo ? __ffsll((long long)todo) - 1 : -1;
-            todo &= todo - 1ull;   // 0 stays 0
-            const int j2 = todo ? __ffsll((long long)todo) - 1 : -1;
-            todo &= todo - 1ull;
-            const int j3 = todo ? __ffsll((long long)todo) - 1 : -1;
-            todo &= todo - 1ull;
-            int j = slice < 2 ? (slice == 0 ? j0 : j1) : (slice == 2 ? j2 : j3);
-            if (j < 0 || !a.on) continue;
-            j += c;
-            const int4 q0 = sg.xy0[j], q1 = sg.xy1[j];
-            const float4 e4 = sg.el[j];
-            TriSetup s;
-            s.X[0] = q0.x; s.X[1] = q0.y; s.X[2] = q0.z;
-            s.Y[0] = q0.w; s.Y[1] = q1.x; s.Y[2] = q1.y;
-            s.meta = q1.z & 0xffff;
-            if (WALK == 0) {
-                const float4 z4 = sg.z[j];
-                s.zn[0] = z4.x; s.zn[1] = z4.y; s.zn[2] = z4.z;
-                s.Af = z4.w;
-            }
-            const float el[3] = {e4.x, e4.y, e4.z};
-            if (q1.z >> 16) {
-                // exact in 32-bit integers (see the staging test)
-                int ex[3], ey[3], len2[3], qx[3], qy[3], E[3];
-                rl_edges(s, ex, ey);
+        // none near the block at all: the next 64
+        const float bd2 = axis_dist2(x0, x1, a.px0, a.px0 + 3 * DRESSI_SUBPIX) +
+                          axis_dist2(y0, y1, a.py0, a.py0 + 3 * DRESSI_SUBPIX);
+        const float near2 = WALK == 0 ? 0.0f : WALK == 1 ? RS_NEAR2 : blim2;
+        if (!__ballot(have && bd2 <= near2)) continue;
+        // squared distances to the block's four columns
+        float dx2[4];
 #pragma unroll
-                for (int i = 0; i < 3; i++) {
-                    len2[i] = __mul24(ex[i], ex[i]) + __mul24(ey[i], ey[i]);
-                    qx[i] = a.px - s.X[i];
-                    qy[i] = a.py - s.Y[i];
+        for (int i = 0; i < 4; i++) {
+            const int px = a.px0 + i * DRESSI_SUBPIX;
+            dx2[i] = have ? axis_dist2(x0, x1, px, px) : 3.0e38f;
+        }
+        for (int row = 0; row < 4; row++) {
+            const int py = a.py0 + row * DRESSI_SUBPIX;
+            const float dy2 = axis_dist2(y0, y1, py, py);
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const float d2 = dx2[i] + dy2;
+                const float lim2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a.lim2), row * 4 + i));
+                bool want;
+                if (WALK == 0) want = d2 == 0.0f && zl <= __builtin_amdgcn_readlane(a.khi, row * 4 + i);
+                else if (WALK == 1) want = d2 > 0.0f && d2 <= fminf(lim2, RS_NEAR2);
+                else want = d2 > RS_NEAR2 && d2 <= lim2;
+                const unsigned long long bal = __ballot(want);
+                if (bal) {
+                    const int at = a.queued + (int)__builtin_amdgcn_mbcnt_hi(
+                                                  (unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+                    if (want) a.queue[at] = (uint16_t)(e | (row * 4 + i) << 9);
+                    a.queued += __popcll(bal);
                 }
-#pragma unroll
-                for (int i = 0; i < 3; i++) {
-                    const int v = (i + 1) % 3;
-                    E[i] = __mul24(ex[i], qy[v]) - __mul24(ey[i], qx[v]);
-                }
-                rl_merge<K, WALK == 0, int>(s, E, el, q1.w, a.px, a.py, dscale, r, reach, a.key, a.id, qx, qy, ex, ey,
-                                            len2);
-            } else {
-                double E[3];
-#pragma unroll
-                for (int i = 0; i < 3; i++) E[i] = dr_edge(s.X, s.Y, i, a.px, a.py);
-                rl_merge<K, WALK == 0, double>(s, E, el, q1.w, a.px, a.py, dscale, r, reach, a.key, a.id);
+            }
+            if (a.queued >= 64) {
+                wave_sync();
+                do {
+                    a.queued -= 64;
+                    soft_pair<K>(sg, a, a.queue[a.queued + lane], dscale, r, reach);
+                } while (a.queued >= 64);
+                wave_sync();
+                soft_refresh<K>(a, dscale, reach);
             }
         }
-        // the slices' lists become one
-#pragma unroll
-        for (int o = 16; o < 64; o <<= 1) {
-            float kk[K];
-            int ii[K];
-#pragma unroll
-            for (int k = 0; k < K; k++) {
-                kk[k] = __shfl_xor(a.key[k], o, 64);
-                ii[k] = __shfl_xor(a.id[k], o, 64);
-            }
-#pragma unroll
-            for (int k = 0; k < K; k++)
-                if (kk[k] < 2.0f) rl_insert<K>(kk[k], ii[k], a.key, a.id);
-        }
-        // keys only decrease: refresh the block's bounds
-        float wm = a.on ? a.key[K - 1] : 0.0f;
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) wm = fmaxf(wm, __shfl_xor(wm, o, 64));
-        wm = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(wm)));
-        a.wmax_bits = __float_as_int(wm);
-        // a soft candidate needs dn <= 2 (wmax - 0.5) + one key rounding;
-        // a pixel gap g (L-infinity, whole pixels) gives dn > (g - 1) / W
-        const float dp = (2.0f * (wm - 0.5f) + 1e-7f) * (float)W * 1.001f;
-        a.gap_max = min(a.gap_max, (int)floorf(fminf(dp, 1.0e9f)) + 1);
+    }
+    // the stage may be refilled after this
+    if (a.queued) {
+        wave_sync();
+        if (lane < a.queued) soft_pair<K>(sg, a, a.queue[lane], dscale, r, reach);
+        a.queued = 0;
+        wave_sync();
+        soft_refresh<K>(a, dscale, reach);
     }
 }
 
 template <int K, bool BANDED>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
-    k_raster_soft(const TriSetup *__restrict__ setup, const int4 *__restrict__ cullq, int32_t *__restrict__ counts,
+__global__ void __launch_bounds__(256)
+    k_raster_soft(const TriSetup *__restrict__ setup, const int4 *__restrict__ boxes, int32_t *__restrict__ counts,
                   const int32_t *__restrict__ bins, int cap, int T, int H, int W, int ntx, int nt, int64_t n_tiles,
-                  float r, int margin, int32_t *__restrict__ tri_id, float2 *__restrict__ bary,
-                  float *__restrict__ dist, const uint8_t *__restrict__ band,
-                  unsigned long long *__restrict__ status) {
+                  float r, int32_t *__restrict__ tri_id, float2 *__restrict__ bary, float *__restrict__ dist,
+                  const uint8_t *__restrict__ band, unsigned long long *__restrict__ status) {
     __shared__ SoftStage sg;
-    __shared__ int wcnt[2][4], sgap[4], hist[64];
+    __shared__ uint16_t queue[4][RS_QUEUE];
+    __shared__ unsigned long long lists[64 * K];
+    __shared__ uint8_t rings[RS_RINGS];   // 255: not kept
+    __shared__ int ids[RS_LIST], listed, hist[64];
+    __shared__ float blim2[4];
     const int64_t blk = xcd_block();
     const int bt = (int)(blk >> 2), q = (int)(blk & 3);
     const int b = bt / nt, tile = bt - b * nt;
     const int tx = tile % ntx, ty = tile / ntx;
-    const int p = threadIdx.x, lane = p & 63, w = p >> 6;
+    const int p = threadIdx.x, lane = p & 63, w = __builtin_amdgcn_readfirstlane(p >> 6);
     const int qx0 = tx * DRESSI_TILE + (q & 1) * 8, qy0 = ty * DRESSI_TILE + (q >> 1) * 8;
-    SoftBlock<K> a;
-    a.x0 = __builtin_amdgcn_readfirstlane(qx0 + (w & 1) * 4);
-    a.y0 = __builtin_amdgcn_readfirstlane(qy0 + (w >> 1) * 4);
-    const int x = a.x0 + (lane & 3), y = a.y0 + ((lane >> 2) & 3);
-    a.px = DRESSI_SUBPIX * x + DRESSI_SUBPIX / 2;
-    a.py = DRESSI_SUBPIX * y + DRESSI_SUBPIX / 2;
+    // pixel centres of the quadrant's corners (fixed point)
+    const int cx0 = DRESSI_SUBPIX * qx0 + DRESSI_SUBPIX / 2, cx1 = cx0 + 7 * DRESSI_SUBPIX;
+    const int cy0 = DRESSI_SUBPIX * qy0 + DRESSI_SUBPIX / 2, cy1 = cy0 + 7 * DRESSI_SUBPIX;
+    SoftBlock a;
+    a.px0 = cx0 + (w & 1) * 4 * DRESSI_SUBPIX;
+    a.py0 = cy0 + (w >> 1) * 4 * DRESSI_SUBPIX;
+    const int x = qx0 + (w & 1) * 4 + (lane & 3), y = qy0 + (w >> 1) * 4 + ((lane >> 2) & 3);
     const float dscale = (float)W * 256.0f;
     const float reach = r * dscale * 1.001f;   // conservative, in fixed-point units
     const TriSetup *__restrict__ sv = setup + (int64_t)b * T;
-    const int4 *__restrict__ cq = cullq + (int64_t)b * T;
+    const int4 *__restrict__ bv = boxes + (int64_t)b * T;
     const int32_t *__restrict__ bin = bins + (int64_t)bt * cap;
     int n = counts[bt], nf = counts[n_tiles + bt];
     if (!BANDED && q == 0 && p == 0 && n + nf > cap) {   // the front pass reports it in the banded form
@@ -956,6 +1033,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
     nf = min(nf, cap);
     a.on = x < W && y < H;
     if (BANDED) a.on = a.on && band[((int64_t)b * H + y) * W + x] != 0;
+    for (int i = p; i < 64 * K; i += 256) lists[i] = RS_EMPTY;
     // (the counts are an operand: every lane has them before the barrier)
     const int any = __syncthreads_or(a.on || n < 0 || nf < 0);
     // the tile's four workgroups have read its counts once each has passed
@@ -966,106 +1044,148 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
         counts[2 * n_tiles + bt] = 0;
     }
     if (!any) return;
-#pragma unroll
-    for (int k = 0; k < K; k++) {
-        a.key[k] = 2.0f;   // empty: above every fragment key
-        a.id[k] = -1;
-    }
-    // a block with no pixel to search wants nothing
-    const bool block_on = __ballot(a.on) != 0ull;
-    a.gap_max = block_on ? margin : -1;
-    a.wmax_bits = block_on ? __float_as_int(2.0f) : -1;
+    a.queue = queue[w];
+    a.queued = 0;
+    a.list = lists + w * 16 * K;
+    a.khi = a.on ? 0x7fffffff : -1;
+    a.lim2 = a.on ? reach * reach * 1.0001f : -1.0f;
 
     const unsigned long long below = (1ull << lane) - 1ull;
-    int cnt = 0, par = 0;
-    bool several = false;   // the staged triangles went through in more than one batch
-    // Compacts the entries [0, m) of the bin (near end, then far end) whose
-    // gap to the quadrant is in [lo, hi] into the stage, running walk WALK on
-    // it whenever the next ones do not fit; the rest stays staged.
-    auto gather = [&](auto walk, int m, int lo, int hi) {
+    const auto entry = [&](int e) { return bin[e < n ? e : cap - 1 - (e - n)]; };
+    // the whole pixels of a box's distance from the quadrant
+    const auto ring_of = [&](const int4 &c) {
+        return (int)(sqrtf(axis_dist2(c.x, c.y, cx0, cx1) + axis_dist2(c.z, c.w, cy0, cy1)) * (1.0f / DRESSI_SUBPIX));
+    };
+    // whether a block of the quadrant still looks as far as the box
+    const auto in_reach = [&](const int4 &c) {
+        const int s4 = 3 * DRESSI_SUBPIX, half = 4 * DRESSI_SUBPIX;
+        const float xa = axis_dist2(c.x, c.y, cx0, cx0 + s4), xb = axis_dist2(c.x, c.y, cx0 + half, cx1);
+        const float ya = axis_dist2(c.z, c.w, cy0, cy0 + s4), yb = axis_dist2(c.z, c.w, cy0 + half, cy1);
+        return xa + ya <= blim2[0] || xb + ya <= blim2[1] || xa + yb <= blim2[2] || xb + yb <= blim2[3];
+    };
+    // Lists the triangles of the bin's entries [e0, e1) (near end, then far
+    // end) in rings lo..hi, four entries a lane in flight; walk 2 leaves out
+    // what no block wants.  At most RS_LIST can be wanted (the caller's bound).
+    const auto scan = [&](auto walk, int e0, int e1, int lo, int hi) {
         constexpr int WALK = decltype(walk)::value;
-        cnt = 0;
-        several = false;
-        for (int c0 = 0; c0 < m; c0 += 256) {
-            const int e = c0 + p;
-            bool want = false;
-            int t = 0;
-            int4 c = make_int4(0, 0, 0, 0);
-            if (e < m) {
-                t = bin[e < n ? e : cap - 1 - (e - n)];
-                c = cq[t];
-                const int g = box_gap(c.x, c.y, qx0, qx0 + 7, qy0, qy0 + 7);
-                want = g >= lo && g <= hi;
-            }
-            const unsigned long long bal = __ballot(want);
-            if (lane == 0) wcnt[par][w] = __popcll(bal);
-            __syncthreads();
-            const int n0 = wcnt[par][0], n1 = wcnt[par][1], n2 = wcnt[par][2], n3 = wcnt[par][3];
-            par ^= 1;
-            const int tot = n0 + n1 + n2 + n3;
-            if (cnt + tot > RS_CAP) {
-                soft_block<K, WALK>(sg, cnt, a, dscale, r, reach, W);
-                several = true;
-                cnt = 0;
-                __syncthreads();
-            }
-            if (want) {
-                const int at = cnt + (w > 0 ? n0 : 0) + (w > 1 ? n1 : 0) + (w > 2 ? n2 : 0) + __popcll(bal & below);
-                const TriSetup s = sv[t];
-                // 32-bit integer path: every pixel-to-vertex difference over the
-                // quadrant and every edge vector below 2^15 in magnitude
-                const int lim15 = 1 << 15, span = DRESSI_SUBPIX * 7;
-                const int px0 = DRESSI_SUBPIX * qx0 + DRESSI_SUBPIX / 2, py0 = DRESSI_SUBPIX * qy0 + DRESSI_SUBPIX / 2;
-                bool small = true;
+        if (p == 0) listed = 0;
+        __syncthreads();
+        for (int c0 = e0 + p; c0 - p < e1; c0 += RS_SEGMENT) {
+            int t[4];
+            bool want[4];
+            int4 c[4];
 #pragma unroll
-                for (int i = 0; i < 3; i++) {
-                    small = small && abs(px0 - s.X[i]) < lim15 && abs(px0 + span - s.X[i]) < lim15 &&
-                            abs(py0 - s.Y[i]) < lim15 && abs(py0 + span - s.Y[i]) < lim15;
-                    const int v = (i + 1) % 3, u = (i + 2) % 3;
-                    small = small && abs(s.X[u] - s.X[v]) < lim15 && abs(s.Y[u] - s.Y[v]) < lim15;
+            for (int i = 0; i < 4; i++) {
+                const int e = c0 + 256 * i;
+                want[i] = e < e1;
+                if (WALK == 2 && want[i] && e < RS_RINGS) {
+                    const int g = rings[e];
+                    want[i] = g == 255 || (g >= lo && g <= hi);
                 }
-                sg.xy0[at] = make_int4(s.X[0], s.X[1], s.X[2], s.Y[0]);
-                sg.xy1[at] = make_int4(s.Y[1], s.Y[2], (s.meta & 0xffff) | (small ? 0x10000 : 0), t);
-                sg.z[at] = make_float4(s.zn[0], s.zn[1], s.zn[2], s.Af);
-                sg.el[at] = make_float4(s.elen[0], s.elen[1], s.elen[2], __int_as_float(c.z));
-                sg.hb[at] = make_int2(c.x, c.y);
+                t[i] = want[i] ? entry(e) : 0;
             }
-            cnt += tot;
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+                if (want[i]) c[i] = bv[t[i]];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                if (want[i]) {
+                    const int g = ring_of(c[i]);
+                    want[i] = g >= lo && g <= hi && (WALK < 2 || in_reach(c[i]));
+                }
+                const unsigned long long bal = __ballot(want[i]);
+                if (!bal) continue;
+                int at = lane == 0 ? atomicAdd(&listed, __popcll(bal)) : 0;
+                at = __builtin_amdgcn_readfirstlane(at) + __popcll(bal & below);
+                if (want[i]) ids[at] = t[i];
+            }
         }
         __syncthreads();
+        return listed;
     };
-    auto run = [&](auto walk) {
-        soft_block<K, decltype(walk)::value>(sg, cnt, a, dscale, r, reach, W);
+    // Stages the list and runs the walk on it; `staged`: it is staged already.
+    const auto run = [&](auto walk, int len, bool staged) {
+        for (int s0 = 0; s0 < len; s0 += RS_CAP) {
+            const int cnt = min(RS_CAP, len - s0);
+            if (!staged) {
+                if (p < cnt) {
+                    const int t = ids[s0 + p];
+                    const TriSetup s = sv[t];
+                    // 32-bit integer path: every pixel-to-vertex difference over the
+                    // quadrant and every edge vector below 2^15 in magnitude
+                    const int lim15 = 1 << 15;
+                    bool small = true;
+#pragma unroll
+                    for (int i = 0; i < 3; i++) {
+                        small = small && abs(cx0 - s.X[i]) < lim15 && abs(cx1 - s.X[i]) < lim15 &&
+                                abs(cy0 - s.Y[i]) < lim15 && abs(cy1 - s.Y[i]) < lim15;
+                        const int v = (i + 1) % 3, u = (i + 2) % 3;
+                        small = small && abs(s.X[u] - s.X[v]) < lim15 && abs(s.Y[u] - s.Y[v]) < lim15;
+                    }
+                    sg.xy0[p] = make_int4(s.X[0], s.X[1], s.X[2], s.Y[0]);
+                    sg.xy1[p] = make_int4(s.Y[1], s.Y[2], (s.meta & 0xffff) | (small ? 0x10000 : 0), t);
+                    sg.z[p] = make_float4(s.zn[0], s.zn[1], s.zn[2], s.Af);
+                    // a soft key is at least 0.5
+                    sg.el[p] = make_float4(s.elen[0], s.elen[1], s.elen[2], fminf(__int_as_float(s.zlb), 0.5f));
+                }
+                __syncthreads();
+            }
+            soft_block<K, decltype(walk)::value>(sg, cnt, a, blim2[w], dscale, r, reach);
+            if (!staged) __syncthreads();
+        }
     };
-    // the largest gap that a block of the quadrant still looks at
-    auto widest = [&]() {
-        if (lane == 0) sgap[w] = a.gap_max;
+    // scan and run over all of [0, m), in segments where more than a list's
+    // worth may be wanted; returns the length of the last list
+    const auto visit = [&](auto walk, int m, int lo, int hi, int most) {
+        const int step = most <= RS_LIST ? m : RS_SEGMENT;
+        int len = 0;
+        for (int e0 = 0; e0 < m; e0 += step) {
+            len = scan(walk, e0, min(e0 + step, m), lo, hi);
+            run(walk, len, false);
+        }
+        return len;
+    };
+    // the farthest ring that a pixel of the quadrant still looks at (-1: none)
+    const auto widest = [&]() {
+        float m = a.lim2;
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+        if (lane == 0) blim2[w] = m;
         __syncthreads();
-        return max(max(sgap[0], sgap[1]), max(sgap[2], sgap[3]));
+        m = fmaxf(fmaxf(blim2[0], blim2[1]), fmaxf(blim2[2], blim2[3]));
+        return m < 0.0f ? -1 : (int)(sqrtf(m) * (1.0001f / DRESSI_SUBPIX));
     };
     using W0 = std::integral_constant<int, 0>;
     using W1 = std::integral_constant<int, 1>;
     using W2 = std::integral_constant<int, 2>;
-    // covering triangles; the near ones are staged with them and stay if all fit
-    gather(W0{}, n, 0, RL_NEAR);
-    run(W0{});
-    int G = widest();
-    if (G > 0) {
-        if (several) gather(W1{}, n, 0, min(RL_NEAR, G));
-        run(W1{});
-        __syncthreads();
-        G = widest();
-        if (G > RL_NEAR) {
+    if (n + nf > 0) {
+        // boxes around a pixel, then the near ones, from the same list if one holds them
+        const int len = visit(W0{}, n, 0, RL_NEAR, n);
+        int far = widest();
+        if (far >= 0) {
+            if (n <= RS_LIST) run(W1{}, len, len <= RS_CAP);
+            else visit(W1{}, n, 0, RL_NEAR, n);
+            __syncthreads();
+            far = widest();
+        }
+        if (far >= RL_NEAR) {
             if (p < 64) hist[p] = 0;
             __syncthreads();
             const int m = n + nf;
-            for (int e = p; e < m; e += 256) {
-                const int4 c = cq[bin[e < n ? e : cap - 1 - (e - n)]];
-                const int g = box_gap(c.x, c.y, qx0, qx0 + 7, qy0, qy0 + 7);
-                if (g <= G) atomicAdd(&hist[min(g, 63)], 1);
+            for (int e0 = p; e0 < m; e0 += RS_SEGMENT) {   // four loads in flight
+                int4 c[4];
+#pragma unroll
+                for (int i = 0; i < 4; i++) c[i] = bv[entry(min(e0 + 256 * i, m - 1))];
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const int e = e0 + 256 * i, g = ring_of(c[i]);
+                    if (e >= m) break;
+                    if (e < RS_RINGS) rings[e] = (uint8_t)min(g, 255);
+                    if (g <= far) atomicAdd(&hist[min(g, 63)], 1);
+                }
             }
             __syncthreads();
-            // this lane: the number of triangles with a gap of at most `lane`
+            // this lane: the number of triangles of rings up to `lane`
             int cum = hist[lane];
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
@@ -1073,53 +1193,40 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
                 if (lane >= o) cum += v;
             }
             int done = -1, goal = RS_RING;
-            while (done < G) {
+            while (done < far) {
                 const unsigned long long reached = __ballot(cum >= goal);
-                int hi = reached ? __ffsll((long long)reached) - 1 : G;
-                if (hi >= 63 || hi > G) hi = G;   // the last bin holds every larger gap
-                hi = max(hi, min(RL_NEAR + 1, G));
-                if (hi <= done) {
-                    goal += RS_RING;
-                    continue;
-                }
-                gather(W2{}, m, done + 1, hi);
-                run(W2{});
-                __syncthreads();
+                int hi = reached ? __ffsll((long long)reached) - 1 : far;
+                hi = max(hi, done + 1);
+                if (hi >= 63 || hi > far) hi = far;   // the last bin holds every larger ring
+                const int upto = __shfl(cum, min(hi, 63), 64);
+                visit(W2{}, m, done + 1, hi, upto - (done < 0 ? 0 : __shfl(cum, min(done, 63), 64)));
                 done = hi;
-                goal = __shfl(cum, min(hi, 63), 64) + 4 * RS_RING;
-                G = widest();
+                goal = upto + 4 * RS_RING;
+                __syncthreads();
+                far = widest();
             }
         }
     }
-    // the quadrant's lists to LDS, then one lane per (pixel, layer) resolves
-    // them (a wavefront writes rows of eight pixels of one layer)
-    __syncthreads();
-    float *fkey = reinterpret_cast<float *>(sg.xy0);
-    int *fid = reinterpret_cast<int *>(sg.xy1);
-    if (lane < 16) {
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-            fkey[k * 64 + w * 16 + lane] = a.on ? a.key[k] : -1.0f;
-            fid[k * 64 + w * 16 + lane] = a.id[k];
-        }
-    }
+    // one lane per (pixel, layer) resolves the lists (a wavefront writes rows
+    // of eight pixels of one layer)
     __syncthreads();
     const int rx = lane & 7, ry = lane >> 3;
     const int ox = qx0 + rx, oy = qy0 + ry;
+    if (ox >= W || oy >= H) return;
+    if (BANDED && band[((int64_t)b * H + oy) * W + ox] == 0) return;
     const int from = ((ry >> 2) * 2 + (rx >> 2)) * 16 + (ry & 3) * 4 + (rx & 3);
     for (int k = w; k < K; k += 4) {
-        const float kf = fkey[k * 64 + from];
-        const int t = fid[k * 64 + from];
-        if (kf < 0.0f) continue;   // not this pass's pixel
+        const unsigned long long v = lists[from * K + k];
         const int64_t o = (((int64_t)b * K + k) * H + oy) * W + ox;
-        if (t < 0) {
+        if (v == RS_EMPTY) {
             tri_id[o] = -1;
             bary[o] = make_float2(0.0f, 0.0f);
             dist[o] = 0.0f;
             continue;
         }
+        const int t = (int)(v & 0xffffffffu);
         resolve_frag<true>(sv[t], t, DRESSI_SUBPIX * ox + DRESSI_SUBPIX / 2, DRESSI_SUBPIX * oy + DRESSI_SUBPIX / 2,
-                           kf, dscale, o, tri_id, bary, dist);
+                           __uint_as_float((unsigned)(v >> 32)), dscale, o, tri_id, bary, dist);
     }
 }
 
@@ -1200,18 +1307,17 @@ static void launch_raster_k(int hard_pix, int hyb_w, dim3 g, hipStream_t st, con
 
 // The soft layers of every pixel (edge == NULL) or of the edge mask's pixels.
 template <int K>
-static void launch_soft_k(const uint8_t *edge, int B, hipStream_t st, const TriSetup *setup, const int4 *cullq,
+static void launch_soft_k(const uint8_t *edge, int B, hipStream_t st, const TriSetup *setup, const int4 *boxes,
                           int32_t *counts, const int32_t *bins, int cap, int T, int H, int W, int ntx, int nt,
-                          float r, int margin, int32_t *tid, float2 *bary, float *dist,
-                          unsigned long long *status) {
+                          float r, int32_t *tid, float2 *bary, float *dist, unsigned long long *status) {
     const int64_t tiles = (int64_t)B * nt;
     const dim3 g((unsigned)(4 * tiles));
     if (edge)
-        DR_LAUNCH("k_raster_soft", (k_raster_soft<K, true>), g, 256, 0, st, setup, cullq, counts, bins, cap, T, H, W,
-                  ntx, nt, tiles, r, margin, tid, bary, dist, edge, status);
+        DR_LAUNCH("k_raster_soft", (k_raster_soft<K, true>), g, 256, 0, st, setup, boxes, counts, bins, cap, T, H, W,
+                  ntx, nt, tiles, r, tid, bary, dist, edge, status);
     else
-        DR_LAUNCH("k_raster_soft", (k_raster_soft<K, false>), g, 256, 0, st, setup, cullq, counts, bins, cap, T, H,
-                  W, ntx, nt, tiles, r, margin, tid, bary, dist, edge, status);
+        DR_LAUNCH("k_raster_soft", (k_raster_soft<K, false>), g, 256, 0, st, setup, boxes, counts, bins, cap, T, H,
+                  W, ntx, nt, tiles, r, tid, bary, dist, edge, status);
 }
 
 static int soft_margin(float r, int W) {
@@ -1237,7 +1343,7 @@ static int tile_capacity(const dressi_ctx *ctx, int B, int T, int nt, int margin
 static size_t raster_scratch(int B, int T, int nt, int cap, bool soft, Carver &c, size_t *o) {
     o[0] = c.take(sizeof(TriSetup) * (size_t)B * T);            // setup
     o[1] = c.take(sizeof(int32_t) * (size_t)B * nt * cap);      // bins
-    o[2] = soft ? c.take(sizeof(int4) * (size_t)B * T) : 0;     // culling entries
+    o[2] = soft ? c.take(sizeof(int4) * (size_t)B * T) : 0;     // vertex boxes
     return c.off;
 }
 
@@ -1298,17 +1404,17 @@ static int rasterize_impl(dressi_ctx *ctx, const float *pos_clip, const int32_t 
     int32_t *bins = at<int32_t>(S, o[1]);
     int32_t *counts = ctx->counters;
     int64_t ntri = (int64_t)B * T;
-    int4 *cullq = soft ? at<int4>(S, o[2]) : nullptr;
+    int4 *boxes = soft ? at<int4>(S, o[2]) : nullptr;
     unsigned long long *status = reinterpret_cast<unsigned long long *>(ctx->status);
     const float4 *pc4 = reinterpret_cast<const float4 *>(pos_clip);
     if (ntri > 0) {
         const int gb = (int)((ntri + 255) / 256);
         if (soft)
             DR_LAUNCH("k_setup_bin", (k_setup_bin<true>), gb, 256, 0, st, pc4, tris, vp, B, V, T, H, W, cull, margin,
-                      ntx, nt, cap, setup, cullq, counts, bins, status);
+                      ntx, nt, cap, setup, boxes, counts, bins, status);
         else
             DR_LAUNCH("k_setup_bin", (k_setup_bin<false>), gb, 256, 0, st, pc4, tris, vp, B, V, T, H, W, cull, margin,
-                      ntx, nt, cap, setup, cullq, counts, bins, status);
+                      ntx, nt, cap, setup, boxes, counts, bins, status);
     }
     dim3 g((unsigned)(B * nt));
     float2 *b2 = reinterpret_cast<float2 *>(bary);
@@ -1320,7 +1426,12 @@ static int rasterize_impl(dressi_ctx *ctx, const float *pos_clip, const int32_t 
         uint8_t *rows = bnd + (size_t)B * H * W, *edge = rows + (size_t)B * H * W;
         const int keep = band >= 0 ? 1 : 0;
         switch (K) {
-#define DR_FRONT(KK)                                                                                                 case KK:                                                                                                             DR_LAUNCH("k_raster_front", (k_raster_list<KK, true, true>), g, DRESSI_TILE_PIX, 0, st, setup, counts,                     bins, cap, T, H, W, ntx, nt, tri_id, b2, dist, ctx->hybrid_weight, keep, (int64_t)B * nt,                        status);                                                                                               break;
+#define DR_FRONT(KK)                                                                                             \
+    case KK:                                                                                                     \
+        DR_LAUNCH("k_raster_front", (k_raster_list<KK, true, true>), g, DRESSI_TILE_PIX, 0, st, setup, counts,   \
+                  bins, cap, T, H, W, ntx, nt, tri_id, b2, dist, ctx->hybrid_weight, keep, (int64_t)B * nt,      \
+                  status);                                                                                       \
+        break;
             DR_FRONT(1) DR_FRONT(2) DR_FRONT(3) DR_FRONT(4) DR_FRONT(5)
 #undef DR_FRONT
         }
@@ -1330,7 +1441,14 @@ static int rasterize_impl(dressi_ctx *ctx, const float *pos_clip, const int32_t 
     }
     const int hp = ctx->hard_raster, hw = ctx->hybrid_weight;
     switch (K) {
-#define DR_RASTER(KK)                                                                                                case KK:                                                                                                             if (soft)                                                                                                            launch_soft_k<KK>(mask, B, st, setup, cullq, counts, bins, cap, T, H, W, ntx, nt, r, margin, tri_id,                               b2, dist, status);                                                                         else                                                                                                                 launch_raster_k<KK>(hp, hw, g, st, setup, counts, bins, cap, T, H, W, ntx, nt, tri_id, b2);                  break;
+#define DR_RASTER(KK)                                                                                            \
+    case KK:                                                                                                     \
+        if (soft)                                                                                                \
+            launch_soft_k<KK>(mask, B, st, setup, boxes, counts, bins, cap, T, H, W, ntx, nt, r, tri_id, b2,     \
+                              dist, status);                                                                     \
+        else                                                                                                     \
+            launch_raster_k<KK>(hp, hw, g, st, setup, counts, bins, cap, T, H, W, ntx, nt, tri_id, b2);          \
+        break;
         DR_RASTER(1) DR_RASTER(2) DR_RASTER(3) DR_RASTER(4) DR_RASTER(5)
 #undef DR_RASTER
     }
