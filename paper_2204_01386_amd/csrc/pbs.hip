@@ -3,13 +3,14 @@
 // image, the BRDF integration table, and split-sum shading (the render
 // graph of appendix B; appendix C optimises an environment map with it).
 //
-// The filters are dense sums over every environment texel, one workgroup per
-// output texel, accumulated in double and reduced in a fixed tree.  Their
-// adjoint is the transposed sum, one workgroup per environment texel, so the
-// environment gradient is exact and needs no atomics.  Shading follows the
+// The filters are dense sums over every environment texel, contracted on the
+// matrix cores in double in a fixed order.  Their adjoint is the transposed
+// sum, so the environment gradient is exact and needs no atomics.  Shading follows the
 // split sum per fragment; its backward is analytic, with the material's
 // scalar gradients reduced in a fixed order.
 #include "dressi_internal.h"
+
+#include <algorithm>
 
 #define PBS_BS 256
 
@@ -43,133 +44,189 @@ __device__ __forceinline__ double cube_texel_omega(int S, int64_t idx) {
     return F(a1, b1) - F(a0, b1) - F(a1, b0) + F(a0, b0);
 }
 
-// (direction, solid angle) of every texel of an S x S cube
-__global__ void k_cube_table(int S, double4 *__restrict__ tab) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= 6ll * S * S) return;
-    const double3 d = cube_texel_dir(S, idx);
-    tab[idx] = make_double4(d.x, d.y, d.z, cube_texel_omega(S, idx));
-}
-
 __device__ __forceinline__ double level_alpha(int l, int L) {
     const double r = (double)l / (double)(L - 1);
     return fmax(r * r, 1e-3);
 }
 
-// Every output of the filters: o < 6 Si^2 is an irradiance texel, the rest
-// the prefiltered levels, level by level.  (direction, alpha^2), alpha^2 < 0
-// marking the irradiance.
-__global__ void k_ibl_out_table(dressi_ibl_desc g, double4 *__restrict__ tab) {
-    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// The filters' kernel between output q (direction) and environment texel e
+// (direction w, solid angle O): max(0, q.w) O for the irradiance; for a
+// prefiltered level max(0, R.w) D(h) O with (R.h)^2 = (1 + R.w) / 2 for unit
+// vectors, D(h) = alpha^2 / (pi T^2), T = (R.h)^2 (alpha^2 - 1) + 1 =
+// (1 - c) / 2 + (1 + c) alpha^2 / 2 (without cancellation: T is of order
+// alpha^2 near the lobe's axis).  With A = (1 + alpha^2) / 2, T = A (1 + c) - c;
+// A = 1 gives T = 1, the irradiance's kernel.  O and the output's factor
+// (alpha^2 / pi, or 1) leave the sums: the pair's part is max(0, c) / T^2.
+__device__ __forceinline__ double2 output_factor(const dressi_ibl_desc &g, int64_t o, double3 &d) {
     const int64_t ni = 6ll * g.Si * g.Si, np = 6ll * g.Sp * g.Sp;
-    if (o >= ni + (int64_t)g.L * np) return;
-    double3 d;
-    double a2 = -1.0;
     if (o < ni) {
         d = cube_texel_dir(g.Si, o);
-    } else {
-        const int l = (int)((o - ni) / np);
-        d = cube_texel_dir(g.Sp, (o - ni) - (int64_t)l * np);
-        const double a = level_alpha(l, g.L);
-        a2 = a * a;
+        return make_double2(1.0, 1.0);
     }
-    tab[o] = make_double4(d.x, d.y, d.z, a2);
+    const int l = (int)((o - ni) / np);
+    d = cube_texel_dir(g.Sp, (o - ni) - (int64_t)l * np);
+    const double al = level_alpha(l, g.L), a2 = al * al;
+    return make_double2(0.5 + 0.5 * a2, a2 / 3.14159265358979323846);
 }
 
-// The filters' kernel between output q (direction, alpha^2) and environment
-// texel e (direction, solid angle): max(0, q.w) O for the irradiance; for a
-// prefiltered level max(0, R.w) D(h) O with (R.h)^2 = (1 + R.w) / 2 for unit
-// vectors, D(h) = alpha^2 / (pi t^2), t = (R.h)^2 (alpha^2 - 1) + 1 =
-// (1 - c) / 2 + (1 + c) alpha^2 / 2 (the form without cancellation: t is of
-// order alpha^2 near the lobe's axis).  c and t in double; the quotient in
-// float, where t's relative precision is kept.
-__device__ __forceinline__ float filter_kernel(const double4 &q, const double4 &e) {
-    const double c = q.x * e.x + q.y * e.y + q.z * e.z;
-    if (!(c > 0.0)) return 0.0f;
-    if (q.w < 0.0) return (float)(c * e.w);
-    const float t = (float)(0.5 * (1.0 - c) + 0.5 * (1.0 + c) * q.w);
-    return (float)(c * q.w * e.w) / (3.14159265358979f * t * t);
+// Outputs o < 6 Si^2 are the irradiance's texels, the rest the prefiltered
+// levels, level by level.  The tables of both sides: environment texels
+// (direction, solid angle) and outputs (direction, A), and the rows of the
+// contraction's right factor: for the filter O (env, 1) per texel, for the
+// adjoint factor / norm (grad, 0) per output.
+__global__ void k_ibl_tables(dressi_ibl_desc g, int64_t ne, int64_t no, const float *__restrict__ env,
+                             const double *__restrict__ norm,
+                             const float *__restrict__ g_irr, const float *__restrict__ g_pref,
+                             double4 *__restrict__ tab, double4 *__restrict__ otab, double4 *__restrict__ rhs) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < ne) {
+        const double3 d = cube_texel_dir(g.S, i);
+        const double om = cube_texel_omega(g.S, i);
+        tab[i] = make_double4(d.x, d.y, d.z, om);
+        if (env) rhs[i] = make_double4(om * env[3 * i], om * env[3 * i + 1], om * env[3 * i + 2], om);
+    }
+    if (i < no) {
+        double3 d;
+        const double2 f = output_factor(g, i, d);
+        otab[i] = make_double4(d.x, d.y, d.z, f.x);
+        if (!env) {
+            const int64_t ni = 6ll * g.Si * g.Si;
+            const float *go = i < ni ? g_irr + 3 * i : g_pref + 3 * (i - ni);
+            const double s = f.y / norm[i];
+            rhs[i] = make_double4(go[0] * s, go[1] * s, go[2] * s, 0.0);
+        }
+    }
 }
 
-// one workgroup per output texel: out = sum_j env_j K_j / sum_j K_j
-__global__ void __launch_bounds__(PBS_BS)
-    k_ibl_filter(dressi_ibl_desc g, const double4 *__restrict__ tab, const double4 *__restrict__ otab,
-                 const float *__restrict__ env, float *__restrict__ irr, float *__restrict__ pref,
-                 double *__restrict__ norm) {
-    __shared__ double red[4][PBS_BS];
-    const int64_t o = blockIdx.x;
-    const double4 q = otab[o];
-    const int64_t ne = 6ll * g.S * g.S;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, sw = 0.0;
-    for (int64_t j = threadIdx.x; j < ne; j += PBS_BS) {
-        const float k = filter_kernel(q, tab[j]);
-        if (k == 0.0f) continue;
-        s0 += (double)(k * env[3 * j]);
-        s1 += (double)(k * env[3 * j + 1]);
-        s2 += (double)(k * env[3 * j + 2]);
-        sw += (double)k;
+// D[row][n] = sum over columns of max(0, c) / T^2 rhs[column][n]: the filters
+// (rows: outputs, columns: environment texels) and their adjoint (rows and
+// columns exchanged), exact sums with no atomics, in a fixed order.
+//
+// It is bound by the pair's arithmetic: c and T in double (their cancellation
+// is the lobe's shape), the quotient in float, the sums in double.  The
+// contraction runs on the matrix cores: v_mfma_f64_4x4x4_4b takes one pair of
+// each lane (lane = 16 (column mod 4) + row mod 16), so a lane feeds the
+// kernel value that it computed and the four sums of a row cost one
+// instruction, where the vector unit would convert, multiply and add each
+// channel.  (The dot products on v_mfma_f64_16x16x4 measured no faster: 416 us
+// against 380.)  A lane holds R rows' directions in
+// registers; the eight wavefronts of a workgroup take every eighth group of
+// 64 columns, each through its own LDS (the next group's loads in flight), and
+// add their sums in wavefront order.  One workgroup per output summing 256 lanes in a tree,
+// with every pair's tables loaded anew, took 1.45 ms (filter) and 1.50 ms
+// (adjoint) at 6 x 64^2 -> 16^2 + 5 x 6 x 32^2 (0.79 G pairs); see the launches
+// for this form's times.
+//
+// A column with a value that is not finite must not reach rows that it does
+// not light (0 x inf): such a step multiplies on the vector unit and skips
+// zero kernel values.
+#define IBL_WAVES 8
+#define IBL_COLS (64 * IBL_WAVES)   // columns of a workgroup's step
+template <int R, bool ADJOINT>
+__global__ void __launch_bounds__(64 * IBL_WAVES)
+    k_ibl_contract(const double4 *__restrict__ rows, int64_t n_rows, const double4 *__restrict__ cols,
+                   const double4 *__restrict__ rhs, int64_t n_cols, int64_t n_irr, dressi_ibl_desc g,
+                   float *__restrict__ out, float *__restrict__ pref, double *__restrict__ norm) {
+    __shared__ double4 scol[IBL_WAVES][64], srhs[IBL_WAVES][64];
+    __shared__ double part[IBL_WAVES][R][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int kk = lane >> 4, low = lane & 15;
+    const int64_t row0 = (int64_t)blockIdx.x * (16 * R);
+    double qx[R], qy[R], qz[R], qa[R], acc[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const double4 q = rows[min(row0 + 16 * r + low, n_rows - 1)];
+        qx[r] = q.x;
+        qy[r] = q.y;
+        qz[r] = q.z;
+        qa[r] = q.w;
+        acc[r] = 0.0;
     }
-    red[0][threadIdx.x] = s0;
-    red[1][threadIdx.x] = s1;
-    red[2][threadIdx.x] = s2;
-    red[3][threadIdx.x] = sw;
+    // the pairs' kernel values of one column (this lane's) and the R rows
+    const auto kernel = [&](const double4 &e, float *k) {
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const double c = fma(qz[r], e.z, fma(qy[r], e.y, qx[r] * e.x));
+            const double A = ADJOINT ? e.w : qa[r];
+            const float t = (float)(fma(A, c, A) - c);
+            k[r] = fminf(fmaxf((float)c, 0.0f), 1.0f) * __builtin_amdgcn_rcpf(t * t);
+        }
+    };
+    // 64 columns at a time, one a lane, through the wavefront's own LDS
+    // (past the end: a direction that lights nothing)
+    int64_t base = 64 * w;
+    double4 e, v;
+    const auto load = [&](int64_t i) {
+        const int64_t at = min(i, n_cols - 1);
+        const double in = i < n_cols ? 1.0 : 0.0;
+        e = cols[at];
+        v = rhs[at];
+        e.x *= in;
+        e.y *= in;
+        e.z *= in;
+        if (i >= n_cols) v.x = v.y = v.z = v.w = 0.0;
+    };
+    load(base + lane);
+    for (; base < n_cols; base += IBL_COLS) {
+        scol[w][lane] = e;
+        srhs[w][lane] = v;
+        const bool finite = !__ballot(!(isfinite(v.x) && isfinite(v.y) && isfinite(v.z) && isfinite(v.w)));
+        load(base + IBL_COLS + lane);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const int n = (int)min((int64_t)64, n_cols - base);
+        const double *sr = reinterpret_cast<const double *>(srhs[w]);
+        if (finite) {
+            for (int c = kk; c - kk < n; c += 8) {   // two steps side by side
+                float k0[R], k1[R];
+                const double v0 = sr[4 * c + (lane & 3)], v1 = sr[4 * c + 16 + (lane & 3)];
+                kernel(scol[w][c], k0);
+                kernel(scol[w][c + 4], k1);
+#pragma unroll
+                for (int r = 0; r < R; r++) {
+                    acc[r] = __builtin_amdgcn_mfma_f64_4x4x4f64((double)k0[r], v0, acc[r], 0, 0, 0);
+                    acc[r] = __builtin_amdgcn_mfma_f64_4x4x4f64((double)k1[r], v1, acc[r], 0, 0, 0);
+                }
+            }
+        } else {
+            for (int c = kk; c - kk < n; c += 4) {
+                float k[R];
+                kernel(scol[w][c], k);
+                // this lane's sums: row (lane >> 4) of its block, channel lane & 3
+                for (int q = 0; q < 4; q++) {
+                    const double vq = sr[4 * (c - kk + q) + (lane & 3)];
+#pragma unroll
+                    for (int r = 0; r < R; r++) {
+                        const float kq = __shfl(k[r], 16 * q + (lane & 12) + (lane >> 4), 64);
+                        if (kq != 0.0f) acc[r] += (double)kq * vq;
+                    }
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+#pragma unroll
+    for (int r = 0; r < R; r++) part[w][r][lane] = acc[r];
     __syncthreads();
-    for (int s = PBS_BS / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s)
-            for (int c = 0; c < 4; c++) red[c][threadIdx.x] += red[c][threadIdx.x + s];
-        __syncthreads();
+    // the sums of row 16 r + 4 (block) + (lane >> 4), channel lane & 3
+    for (int r = w; r < R; r += IBL_WAVES) {
+        double d = 0.0;
+#pragma unroll
+        for (int k = 0; k < IBL_WAVES; k++) d += part[k][r][lane];
+        const double sum = __shfl(d, lane | 3, 64);   // the row's fourth channel
+        const int64_t row = row0 + 16 * r + (lane & 12) + (lane >> 4);
+        const int n = lane & 3;
+        if (row >= n_rows) continue;
+        if (ADJOINT) {
+            if (n < 3) out[3 * row + n] = (float)(d * rows[row].w);
+        } else if (n < 3) {
+            (row < n_irr ? out + 3 * row : pref + 3 * (row - n_irr))[n] = (float)(d * (1.0 / sum));
+        } else {
+            double3 dir;
+            norm[row] = output_factor(g, row, dir).y * d;
+        }
     }
-    if (threadIdx.x != 0) return;
-    const double inv = 1.0 / red[3][0];
-    const int64_t ni = 6ll * g.Si * g.Si;
-    float *dst = o < ni ? irr + 3 * o : pref + 3 * (o - ni);
-    dst[0] = (float)(red[0][0] * inv);
-    dst[1] = (float)(red[1][0] * inv);
-    dst[2] = (float)(red[2][0] * inv);
-    norm[o] = red[3][0];
-}
-
-// every output's gradient over its denominator, g_o / norm_o
-__global__ void k_ibl_bwd_scale(dressi_ibl_desc g, const double *__restrict__ norm, const float *__restrict__ g_irr,
-                                const float *__restrict__ g_pref, float4 *__restrict__ gs) {
-    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t ni = 6ll * g.Si * g.Si, no = ni + (int64_t)g.L * 6 * g.Sp * g.Sp;
-    if (o >= no) return;
-    const float *go = o < ni ? g_irr + 3 * o : g_pref + 3 * (o - ni);
-    const double inv = 1.0 / norm[o];
-    gs[o] = make_float4((float)(go[0] * inv), (float)(go[1] * inv), (float)(go[2] * inv), 0.0f);
-}
-
-// one workgroup per environment texel j: g_env_j = sum_o K_oj g_o / norm_o
-__global__ void __launch_bounds__(PBS_BS)
-    k_ibl_filter_bwd(dressi_ibl_desc g, const double4 *__restrict__ tab, const double4 *__restrict__ otab,
-                     const float4 *__restrict__ gs, float *__restrict__ g_env) {
-    __shared__ double red[3][PBS_BS];
-    const int64_t j = blockIdx.x;
-    const double4 e = tab[j];
-    const int64_t no = 6ll * g.Si * g.Si + (int64_t)g.L * 6 * g.Sp * g.Sp;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-    for (int64_t o = threadIdx.x; o < no; o += PBS_BS) {
-        const float k = filter_kernel(otab[o], e);
-        if (k == 0.0f) continue;
-        const float4 q = gs[o];
-        s0 += (double)(k * q.x);
-        s1 += (double)(k * q.y);
-        s2 += (double)(k * q.z);
-    }
-    red[0][threadIdx.x] = s0;
-    red[1][threadIdx.x] = s1;
-    red[2][threadIdx.x] = s2;
-    __syncthreads();
-    for (int s = PBS_BS / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s)
-            for (int c = 0; c < 3; c++) red[c][threadIdx.x] += red[c][threadIdx.x + s];
-        __syncthreads();
-    }
-    if (threadIdx.x != 0) return;
-    g_env[3 * j] = (float)red[0][0];
-    g_env[3 * j + 1] = (float)red[1][0];
-    g_env[3 * j + 2] = (float)red[2][0];
 }
 
 static int check_ibl(dressi_ctx *ctx, const dressi_ibl_desc *d) {
@@ -180,23 +237,54 @@ static int check_ibl(dressi_ctx *ctx, const dressi_ibl_desc *d) {
     return DRESSI_OK;
 }
 
-// The environment texels' and the outputs' tables, in the context's scratch.
-// (with gs, room for the backward's per-output gradient scale as well)
-static int ibl_tables(dressi_ctx *ctx, const dressi_ibl_desc *d, hipStream_t st, double4 *&tab, double4 *&otab,
-                      float4 **gs = nullptr) {
-    const int64_t ne = 6ll * d->S * d->S;
-    const int64_t no = 6ll * d->Si * d->Si + (int64_t)d->L * 6 * d->Sp * d->Sp;
+// The tables of k_ibl_tables in the context's scratch; env (the filter) or
+// norm and the gradients (the adjoint).
+struct IblTables {
+    double4 *tab, *otab, *rhs;
+    int64_t ne, no;
+};
+static size_t ibl_layout(const dressi_ibl_desc &d, IblTables &t, Carver &c, size_t *o) {
+    t.ne = 6ll * d.S * d.S;
+    t.no = 6ll * d.Si * d.Si + (int64_t)d.L * 6 * d.Sp * d.Sp;
+    o[0] = c.take(sizeof(double4) * (size_t)t.ne);
+    o[1] = c.take(sizeof(double4) * (size_t)t.no);
+    o[2] = c.take(sizeof(double4) * (size_t)std::max(t.ne, t.no));
+    return c.off;
+}
+static int ibl_tables(dressi_ctx *ctx, const dressi_ibl_desc *d, hipStream_t st, const float *env, const double *norm,
+                      const float *g_irr, const float *g_pref, IblTables &t) {
     Carver c;
-    const size_t o_t = c.take(sizeof(double4) * (size_t)ne), o_o = c.take(sizeof(double4) * (size_t)no);
-    const size_t o_g = c.take(sizeof(float4) * (size_t)no);
-    int rc = dressi_scratch(ctx, c.off, st);
+    size_t o[3];
+    int rc = dressi_scratch(ctx, ibl_layout(*d, t, c, o), st);
     if (rc) return rc;
-    tab = at<double4>(ctx->scratch, o_t);
-    otab = at<double4>(ctx->scratch, o_o);
-    if (gs) *gs = at<float4>(ctx->scratch, o_g);
-    DR_LAUNCH("k_cube_table", (k_cube_table), (int)((ne + 255) / 256), 256, 0, st, d->S, tab);
-    DR_LAUNCH("k_ibl_out_table", (k_ibl_out_table), (int)((no + 255) / 256), 256, 0, st, *d, otab);
+    t.tab = at<double4>(ctx->scratch, o[0]);
+    t.otab = at<double4>(ctx->scratch, o[1]);
+    t.rhs = at<double4>(ctx->scratch, o[2]);
+    DR_LAUNCH("k_ibl_tables", (k_ibl_tables), (int)((std::max(t.ne, t.no) + 255) / 256), 256, 0, st, *d, t.ne,
+              t.no, env, norm, g_irr, g_pref, t.tab, t.otab, t.rhs);
     return DRESSI_OK;
+}
+
+// Rows a lane: the more, the fewer LDS reads a pair, but the fewer workgroups.
+// Below 4,096 rows (128 workgroups of two) one; else four where their last
+// round over the 256 CUs is full enough, a round of four costing 1.7 of two.
+// Measured with 1, 2 and 4 rows (us; rows x columns): 960 x 1,536 7.4, 10.4, 14.8;
+// 8,064 x 6,144 36, 35, 51; 32,256 x 24,576 (504 workgroups of four) 487, 450, 380;
+// 24,576 x 32,256 (384) 488, 431, 536; 57,888 x 38,400 1255, 1224, 1098.
+template <bool ADJOINT>
+static void ibl_contract(const char *name, const dressi_ibl_desc &d, const double4 *rows, int64_t n_rows,
+                         const double4 *cols, const double4 *rhs, int64_t n_cols, float *out, float *pref,
+                         double *norm, hipStream_t st) {
+    const int64_t n_irr = 6ll * d.Si * d.Si;
+    const auto grid = [&](int R) { return (int)((n_rows + 16 * R - 1) / (16 * R)); };
+    const auto rounds = [&](int R) { return (grid(R) + 255) / 256; };
+#define DR_IBL(RR)                                                                                               \
+    DR_LAUNCH(name, (k_ibl_contract<RR, ADJOINT>), grid(RR), 64 * IBL_WAVES, 0, st, rows, n_rows, cols, rhs, n_cols, \
+              n_irr, d, out, pref, norm)
+    if (n_rows < 4096) DR_IBL(1);
+    else if (17 * rounds(4) < 10 * rounds(2)) DR_IBL(4);
+    else DR_IBL(2);
+#undef DR_IBL
 }
 
 extern "C" size_t dressi_ibl_norm_bytes(const dressi_ibl_desc *d) {
@@ -210,10 +298,9 @@ extern "C" int dressi_ibl_filter(dressi_ctx *ctx, const float *env, const dressi
     if (rc) return rc;
     if (!env || !irr || !pref || !norm) return dressi_fail(ctx, DRESSI_EINVAL, "ibl_filter: null pointer");
     hipStream_t st = (hipStream_t)stream;
-    double4 *tab, *otab;
-    if ((rc = ibl_tables(ctx, d, st, tab, otab))) return rc;
-    const int64_t no = 6ll * d->Si * d->Si + (int64_t)d->L * 6 * d->Sp * d->Sp;
-    DR_LAUNCH("k_ibl_filter", (k_ibl_filter), (int)no, PBS_BS, 0, st, *d, tab, otab, env, irr, pref, norm);
+    IblTables t;
+    if ((rc = ibl_tables(ctx, d, st, env, nullptr, nullptr, nullptr, t))) return rc;
+    ibl_contract<false>("k_ibl_filter", *d, t.otab, t.no, t.tab, t.rhs, t.ne, irr, pref, norm, st);
     return dressi_launch_check(ctx, "ibl_filter");
 }
 
@@ -225,14 +312,9 @@ extern "C" int dressi_ibl_filter_bwd(dressi_ctx *ctx, const dressi_ibl_desc *d, 
     if (!norm || !grad_irr || !grad_pref || !grad_env)
         return dressi_fail(ctx, DRESSI_EINVAL, "ibl_filter_bwd: null pointer");
     hipStream_t st = (hipStream_t)stream;
-    double4 *tab, *otab;
-    float4 *gs;
-    if ((rc = ibl_tables(ctx, d, st, tab, otab, &gs))) return rc;
-    const int64_t ne = 6ll * d->S * d->S;
-    const int64_t no = 6ll * d->Si * d->Si + (int64_t)d->L * 6 * d->Sp * d->Sp;
-    DR_LAUNCH("k_ibl_bwd_scale", (k_ibl_bwd_scale), (int)((no + 255) / 256), 256, 0, st, *d, norm, grad_irr,
-              grad_pref, gs);
-    DR_LAUNCH("k_ibl_filter_bwd", (k_ibl_filter_bwd), (int)ne, PBS_BS, 0, st, *d, tab, otab, gs, grad_env);
+    IblTables t;
+    if ((rc = ibl_tables(ctx, d, st, nullptr, norm, grad_irr, grad_pref, t))) return rc;
+    ibl_contract<true>("k_ibl_filter_bwd", *d, t.tab, t.ne, t.otab, t.rhs, t.no, grad_env, nullptr, nullptr, st);
     return dressi_launch_check(ctx, "ibl_filter_bwd");
 }
 
@@ -615,12 +697,10 @@ extern "C" int dressi_shade_pbs_bwd(dressi_ctx *ctx, const dressi_pbs_in *in, co
 size_t dr_need_pbs(const dressi_limits &l) {
     size_t need = 0;
     if (l.ibl_S > 0) {
-        const int64_t ne = 6ll * l.ibl_S * l.ibl_S;
-        const int64_t no = 6ll * l.ibl_Si * l.ibl_Si + (int64_t)l.ibl_L * 6 * l.ibl_Sp * l.ibl_Sp;
+        IblTables t;
         Carver c;
-        c.take(sizeof(double4) * (size_t)ne);
-        c.take(sizeof(double4) * (size_t)no);
-        c.take(sizeof(float4) * (size_t)no);
+        size_t o[3];
+        ibl_layout(dressi_ibl_desc{l.ibl_S, l.ibl_Si, l.ibl_Sp, l.ibl_L}, t, c, o);
         need = c.off;
     }
     if (l.pbs_fragments > 0)
