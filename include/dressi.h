@@ -151,8 +151,7 @@ int dressi_check_status(dressi_ctx *ctx, int64_t *needed, void *stream);
  *   value at a non-empty slot.
  * DRESSI_TUNE_IV_ROWS: texel rows per lane of the inverse-UV gather of
  *   dressi_texture_bwd and dressi_texture_grad_invuv: 1, 2 or 4 (0 =
- *   automatic).  Each workgroup covers 16 x 16*rows texels; every choice
- *   adds the same terms in the same order. */
+ *   automatic).  Every choice adds the same terms in the same order. */
 #define DRESSI_TUNE_BIN_CAPACITY 1
 #define DRESSI_TUNE_HARD_RASTER 2
 #define DRESSI_TUNE_HYBRID_WEIGHT 3

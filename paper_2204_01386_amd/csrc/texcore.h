@@ -12,6 +12,15 @@ struct Taps {
     float fx, fy;
 };
 
+// c modulo n in [0, n): one addition or subtraction for the usual range, a
+// division only beyond it
+__device__ __forceinline__ int wrap_repeat(int c, int n) {
+    if (c >= 0 && c < n) return c;
+    if (c < 0 && c >= -n) return c + n;
+    if (c >= n && c < 2 * n) return c - n;
+    return ((c % n) + n) % n;
+}
+
 // s = u*n - 1/2 (float), taps floor(s) + {0,1}, wrapped or clamped
 __device__ __forceinline__ void taps1d(float u, int n, int wrap, int &a, int &b, float &f) {
     float s = u * (float)n;
@@ -21,10 +30,8 @@ __device__ __forceinline__ void taps1d(float u, int n, int wrap, int &a, int &b,
     a = (int)fl;
     b = a + 1;
     if (wrap == DRESSI_WRAP_REPEAT) {
-        a %= n;
-        if (a < 0) a += n;
-        b %= n;
-        if (b < 0) b += n;
+        a = wrap_repeat(a, n);
+        b = a + 1 < n ? a + 1 : 0;
     } else {
         a = min(max(a, 0), n - 1);
         b = min(max(b, 0), n - 1);
@@ -35,8 +42,7 @@ __device__ __forceinline__ int cell1d(float u, int n, int wrap) {
     float p = u * (float)n;
     int c = (int)floorf(p);
     if (wrap == DRESSI_WRAP_REPEAT) {
-        c %= n;
-        if (c < 0) c += n;
+        c = wrap_repeat(c, n);
     } else {
         c = min(max(c, 0), n - 1);
     }

@@ -213,12 +213,12 @@ static Jitter jitter_of_frame(uint32_t frame) {
     return j;
 }
 
-// Texture gradient through the inverse UV.  A workgroup of 256 lanes (16
-// columns x 16 rows) owns a block of 16 x 16R texels, R texels per lane (rows
-// ly, ly + 16, ...).  Per slice the cells around the block (a one-cell halo)
-// are staged in LDS (wrapped, or empty outside a clamped texture), each with
-// its winner's taps, bilinear fractions and gradient; blocks whose cells are
-// all empty skip the slice.  Each texel then visits its 3x3 cells in
+// Texture gradient through the inverse UV.  A workgroup of LANES (16 columns x
+// LANES / 16 rows) owns a block of texels, R per lane.  Per slice the cells
+// around the block (a one-cell halo) are staged in LDS (wrapped, or empty
+// outside a clamped texture), each with its winner's bilinear weights on the
+// three texel columns and rows around it and its gradient; blocks whose cells
+// are all empty skip the slice.  Each texel then visits its 3x3 cells in
 // row-major order and adds the kept pixel's gradient times that pixel's
 // bilinear weight on the texel.
 #define IV_T 16
@@ -232,41 +232,46 @@ static Jitter jitter_of_frame(uint32_t frame) {
 // f has its taps on f, so they are recomputed from its coordinate alone.
 // More rows per lane (R) means fewer, larger blocks: more loads in flight per
 // lane and fewer halo cells per texel, against more LDS per block.
-// c modulo n in [0, n): one addition or subtraction for the halo's usual
-// range, a division only for blocks that reach past a small texture
-__device__ __forceinline__ int wrap_repeat(int c, int n) {
-    if (c >= 0 && c < n) return c;
-    if (c < 0 && c >= -n) return c + n;
-    if (c >= n && c < 2 * n) return c - n;
-    return ((c % n) + n) % n;
-}
-
-template <int SG, int R>
+template <int SG, int R, int LANES>
 struct IvGeom {
-    static constexpr int NT = 256;                 // lanes: 16 columns x 16 rows
-    static constexpr int TY = 16 * R;              // texel rows per block
+    static constexpr int NT = LANES;               // lanes: 16 columns x LANES / 16 rows
+    static constexpr int LY = LANES / 16;
+    static constexpr int TY = LY * R;              // texel rows per block
     static constexpr int HW = IV_T + 2, HH = TY + 2, HN = HW * HH;   // halo
     static constexpr int PT = (HN + NT - 1) / NT;  // halo cells per lane
 };
 
+// The weights of a winner's two taps along one axis (t0 | t1 << 16, upper
+// fraction f) on the texels at offsets -1, 0, 1 from its cell c of n, wrapped;
+// both taps of a clamped coordinate can fall on one.  Written to o[0], o[s],
+// o[2 s].
+__device__ __forceinline__ void iv_weights(int t, float f, int c, int n, int s, float *o) {
+    int a = (t & 0xffff) - c, b = (t >> 16) - c;
+    a = a > 1 ? a - n : a < -1 ? a + n : a;
+    b = b > 1 ? b - n : b < -1 ? b + n : b;
+    const float g = 1.0f - f;
+#pragma unroll
+    for (int d = -1; d <= 1; d++) o[(d + 1) * s] = (a == d ? g : 0.0f) + (b == d ? f : 0.0f);
+}
+
 // With REC (RGBA, 2-D or array textures) each kept pixel's taps, fractions
 // and gradient come from its record (invrec_put) in one 32-byte read, in
 // place of its coordinate and gradient: the same values.
-template <int CT, int SG, int R, bool REC = false>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(((R == 1 && CT == 8) || (R == 2 && CT > 0 && CT <= 4)) ? 8 : 1)))
+template <int CT, int SG, int R, bool REC = false, int LANES = 256>
+__global__ void __launch_bounds__(LANES)
     k_invuv_gather(dressi_tex_desc td, const float *__restrict__ coord, const int32_t *__restrict__ tri_id,
                    int64_t npix, int S, int nsplit, const int32_t *__restrict__ inv,
                    const float *__restrict__ grad_out, float *__restrict__ out, int xcd,
                    const int4 *__restrict__ rec, LossJob lj, ListJob job, int jcols) {
     static_assert(!REC || CT == 4, "records hold an RGBA gradient");
-    // per halo cell of each slice of the group: the winner's four tap
-    // coordinates, bilinear fractions (fx < 0: no winner, or one on another
-    // cube face) and pixel gradient
-    using G = IvGeom<SG, R>;
+    // per halo cell of each slice of the group: the winner's bilinear weights
+    // on the texels at offsets -1, 0, 1 from the cell, by column (0: none, no
+    // winner, or one on another cube face) and by row, and its pixel gradient
+    using G = IvGeom<SG, R, LANES>;
     constexpr int NC = TEX_NC(CT);
-    __shared__ int2 ctap[SG][G::HN];   // x0 | x1 << 16, y0 | y1 << 16
-    __shared__ float2 cfr[SG][G::HN];  // fx, fy (also the loss job's 256 floats)
-    static_assert(2 * SG * G::HN >= 256, "the loss job reuses cfr");
+    __shared__ float cwx[SG][3][G::HN];   // also the loss job's 256 floats
+    __shared__ float cwy[SG][3][G::HN];
+    static_assert(LANES < 256 || 3 * SG * G::HN >= 256, "the loss job reuses cwx");
     __shared__ float cg[SG][G::HN * NC];
     const int Ht = td.Ht, Wt = td.Wt, Ct = CT > 0 ? CT : td.Ct;
     const bool cube = td.kind == DRESSI_TEX_CUBE;
@@ -281,11 +286,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(((R ==
     // first workgroup runs it, the others exit)
     // and with a list-building job of the step, the columns after it are the
     // job's workgroups
-    const int lc = lj.loss ? 1 : 0;
+    const int lc = LANES == 256 && lj.loss ? 1 : 0;
     const int gxb = (int)gridDim.x - lc - jcols;
-    if ((int)blockIdx.x >= gxb) {
+    if (LANES == 256 && (int)blockIdx.x >= gxb) {
         if (lj.loss && (int)blockIdx.x == gxb) {
-            if (blockIdx.y == 0 && blockIdx.z == 0) loss_sum_block(lj, reinterpret_cast<float *>(&cfr[0][0]));
+            if (blockIdx.y == 0 && blockIdx.z == 0) loss_sum_block(lj, &cwx[0][0][0]);
             return;
         }
         list_job_block(job, (((int)blockIdx.x - gxb - lc) * (int)gridDim.y + (int)blockIdx.y) * (int)gridDim.z +
@@ -318,10 +323,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(((R ==
     const int64_t cells_all = (int64_t)F * face_cells;
     // this lane's halo entries (row-major over the halo) and their cell offsets
     int hoff[G::PT];
+    int hcell[G::PT];   // x | y << 16
 #pragma unroll
     for (int k = 0; k < G::PT; k++) {
         const int h = threadIdx.x + k * G::NT;
         hoff[k] = -1;
+        hcell[k] = 0;
         if (h < G::HN) {
             int cy = by0 - 1 + h / G::HW, cx = bx0 - 1 + h % G::HW;
             bool ok = true;
@@ -330,6 +337,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(((R ==
             if (wu == DRESSI_WRAP_REPEAT) cx = wrap_repeat(cx, Wt);
             else ok = ok && cx >= 0 && cx < Wt;
             if (ok) hoff[k] = cy * Wt + cx;
+            hcell[k] = cx | (cy << 16);
         }
     }
     float acc[R][NC];
@@ -385,8 +393,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(((R ==
                 const int h = threadIdx.x + k * G::NT;
                 if (h >= G::HN) continue;
                 const int i = wpix[q][k];
-                int2 tp = make_int2(0, 0);
-                float2 fr = make_float2(-1.0f, 0.0f);
+                bool put = false;
+                int2 tp;
+                float2 fr;
                 if (REC && i >= 0) {
                     // a kept pixel's taps are on the face or layer of its cell
                     int4 a, b;
@@ -400,7 +409,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(((R ==
                     }
                     tp = make_int2(a.x, a.y);
                     fr = make_float2(__int_as_float(a.z), __int_as_float(a.w));
-                    found = 1;
+                    put = true;
                     cg[q][h * NC] = __int_as_float(b.x);
                     cg[q][h * NC + 1] = __int_as_float(b.y);
                     cg[q][h * NC + 2] = __int_as_float(b.z);
@@ -414,37 +423,35 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(((R ==
                     if (t.ok && t.face == f) {
                         tp = make_int2(t.x0 | (t.x1 << 16), t.y0 | (t.y1 << 16));
                         fr = make_float2(t.fx, t.fy);
-                        found = 1;
+                        put = true;
 #pragma unroll
                         for (int c = 0; c < NC; c++)
                             if (CT > 0 || c < Ct) cg[q][h * NC + c] = g[c];
                     }
                 }
-                ctap[q][h] = tp;
-                cfr[q][h] = fr;
+                if (put) {
+                    found = 1;
+                    iv_weights(tp.x, fr.x, hcell[k] & 0xffff, Wt, G::HN, &cwx[q][0][h]);
+                    iv_weights(tp.y, fr.y, hcell[k] >> 16, Ht, G::HN, &cwy[q][0][h]);
+                } else {
+                    cwx[q][0][h] = cwx[q][1][h] = cwx[q][2][h] = 0.0f;
+                }
             }
         }
         if (!__syncthreads_or(found)) continue;
 #pragma unroll
         for (int r = 0; r < R; r++) {
-            const int ry = ly + 16 * r, ty = by0 + ry;
+            const int ry = ly + G::LY * r, ty = by0 + ry;
             if (tx >= Wt || ty >= Ht) continue;
             for (int q = 0; q < ng; q++) {
 #pragma unroll
                 for (int dy = 0; dy < 3; dy++) {
 #pragma unroll
                     for (int dx = 0; dx < 3; dx++) {
+                        // the cell at (dx - 1, dy - 1) sees this texel at the opposite offset
                         const int h = (ry + dy) * G::HW + lx + dx;
-                        const float2 fr = cfr[q][h];
-                        if (fr.x < 0.0f) continue;
-                        const int2 tp = ctap[q][h];
-                        const int x0 = tp.x & 0xffff, x1 = tp.x >> 16, y0 = tp.y & 0xffff, y1 = tp.y >> 16;
-                        float w = 0.0f;
-                        if (y0 == ty && x0 == tx) w += (1.0f - fr.y) * (1.0f - fr.x);
-                        if (y0 == ty && x1 == tx) w += (1.0f - fr.y) * fr.x;
-                        if (y1 == ty && x0 == tx) w += fr.y * (1.0f - fr.x);
-                        if (y1 == ty && x1 == tx) w += fr.y * fr.x;
-                        if (w == 0.0f) continue;
+                        const float wx = cwx[q][2 - dx][h], w = wx * cwy[q][2 - dy][h];
+                        if (wx == 0.0f || w == 0.0f) continue;
                         float g[NC];
 #pragma unroll
                         for (int c = 0; c < NC; c++)
@@ -460,7 +467,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(((R ==
     }
 #pragma unroll
     for (int r = 0; r < R; r++) {
-        const int ty = by0 + ly + 16 * r;
+        const int ty = by0 + ly + G::LY * r;
         if (tx >= Wt || ty >= Ht) continue;
         float *gt = out + ((int64_t)part * cells_all + (int64_t)f * face_cells + (int64_t)ty * Wt + tx) * Ct;
         stv<CT>(gt, acc[r], Ct);
@@ -476,63 +483,59 @@ __global__ void k_invuv_reduce(const float *__restrict__ part, int nsplit, int64
     out[i] = a;
 }
 
-template <int SG, int R>
+template <int SG, int R, int LANES>
 static void launch_gather_r(int ct, dim3 g, hipStream_t st, const dressi_tex_desc &td, const float *coord,
                             const int32_t *tri_id, int64_t npix, int S, int nsplit, const int32_t *inv,
                             const float *grad_out, float *dst, int xcd, const int4 *rec, LossJob lj,
                             const ListJob &job, int jcols) {
-    constexpr int nt = IvGeom<SG, R>::NT;
-    if (rec)
-        DR_LAUNCH("k_invuv_gather", (k_invuv_gather<4, SG, R, true>), g, nt, 0, st, td, coord, tri_id, npix, S,
-                  nsplit, inv, grad_out, dst, xcd, rec, lj, job, jcols);
-    else if (ct == 4)
-        DR_LAUNCH("k_invuv_gather", (k_invuv_gather<4, SG, R>), g, nt, 0, st, td, coord, tri_id, npix, S,
-                  nsplit, inv, grad_out, dst, xcd, rec, lj, job, jcols);
-    else if (ct == 3)
-        DR_LAUNCH("k_invuv_gather", (k_invuv_gather<3, SG, R>), g, nt, 0, st, td, coord, tri_id, npix, S,
-                  nsplit, inv, grad_out, dst, xcd, rec, lj, job, jcols);
-    else if (ct == 8)
-        DR_LAUNCH("k_invuv_gather", (k_invuv_gather<8, SG, R>), g, nt, 0, st, td, coord, tri_id, npix, S,
-                  nsplit, inv, grad_out, dst, xcd, rec, lj, job, jcols);
-    else
-        DR_LAUNCH("k_invuv_gather", (k_invuv_gather<0, SG, 1>), g, nt, 0, st, td, coord, tri_id, npix, S,
-                  nsplit, inv, grad_out, dst, xcd, rec, lj, job, jcols);
+#define DR_GATHER(CT, REC)                                                                                       \
+    DR_LAUNCH("k_invuv_gather", (k_invuv_gather<CT, SG, R, REC, LANES>), g, LANES, 0, st, td, coord, tri_id, npix, S, \
+              nsplit, inv, grad_out, dst, xcd, rec, lj, job, jcols)
+    if constexpr (LANES == 256) DR_GATHER(4, true);
+    else if (ct == 4) DR_GATHER(4, false);
+    else if (ct == 3) DR_GATHER(3, false);
+    else if (ct == 8) DR_GATHER(8, false);
+    else if constexpr (R == 1) DR_GATHER(0, false);   // other channel counts
+#undef DR_GATHER
 }
 
-// Large textures take the XCD-contiguous block order and two texel rows per
-// lane in the gather as well.
-
-// Texel rows per lane of the gather: `rows` (1, 2 or 4) or, for 0, 2 rows
-// for a single slice or a large texture and 1 otherwise (measured: with one
-// slice the larger blocks are faster; with many slices of a 1024^2 texture
-// the loop over slices prefers more, smaller blocks in flight; a 4096^2
-// texture prefers the larger blocks again).  Any choice gives the same sums
-// in the same order.
-static int gather_rows(int rows, int ct, int S, const dressi_tex_desc &td, bool rec) {
+// Lanes of a workgroup: one wavefront (16 x 4R texels), which waits for no
+// other between the slices' loads and sums; 256 where the launch also carries
+// the loss or list jobs of a step (records), whose code takes 256.
+// Texel rows per lane: `rows` (1, 2 or 4) or, for 0, 1, but 2 with records of a
+// large texture.  Measured, 64 lanes with 1 and 2 rows and 256 lanes with 1 and 2
+// (us): 8 slices of 512^2 on 1024^2 RGB 57, 70, 60, 58; 8 of 500 x 333 on 768^2
+// RGBA 31, 34, 38, 38; 48 of 512^2 on 1024^2 x 8 channels and a cube map 320, 414,
+// 339, 406; 24 of 2048^2 on 4096^2 RGBA 2563, 2760, 2985, 2786; before weights
+// were staged in place of taps, 256 lanes: 70, 42, 355, 2650 (2 rows).  Any
+// choice gives the same sums in the same order.
+static int gather_rows(int rows, int ct, const dressi_tex_desc &td, bool rec) {
     if (ct != 3 && ct != 4 && ct != 8) return 1;
     if (rows == 1 || rows == 2 || rows == 4) return rows;
-    if ((int64_t)td.Ht * td.Wt >= IV_LARGE_CELLS) return 2;
-    return (S == 1 && !rec) ? 2 : 1;
+    return rec && (int64_t)td.Ht * td.Wt >= IV_LARGE_CELLS ? 2 : 1;
 }
 
 static void launch_gather(int rows, int ct, int64_t gx, int64_t ty_cells, int gz, hipStream_t st,
                           const dressi_tex_desc &td, const float *coord, const int32_t *tri_id, int64_t npix,
                           int S, int nsplit, const int32_t *inv, const float *grad_out, float *dst,
                           const int4 *rec, LossJob lj, const ListJob &job) {
-    const int R = gather_rows(rows, ct, S, td, rec != nullptr);
+    const int R = gather_rows(rows, ct, td, rec != nullptr);
     const int xcd = (int64_t)td.Ht * td.Wt >= IV_LARGE_CELLS;
-    const int64_t gy = (ty_cells + 16 * R - 1) / (16 * R);
+    const int lanes = rec ? 256 : 64;
+    const int64_t gy = (ty_cells + lanes / 16 * R - 1) / (lanes / 16 * R);
     const int jcols = job.nb > 0 ? (int)((job.nb + gy * gz - 1) / (gy * gz)) : 0;
     dim3 g((unsigned)(gx + (lj.loss ? 1 : 0) + jcols), (unsigned)gy, (unsigned)gz);
-    if (R == 4)
-        launch_gather_r<DRESSI_IV_SG, 4>(ct, g, st, td, coord, tri_id, npix, S, nsplit, inv, grad_out, dst, xcd,
-                                          rec, lj, job, jcols);
-    else if (R == 2)
-        launch_gather_r<DRESSI_IV_SG, 2>(ct, g, st, td, coord, tri_id, npix, S, nsplit, inv, grad_out, dst, xcd,
-                                          rec, lj, job, jcols);
-    else
-        launch_gather_r<DRESSI_IV_SG, 1>(ct, g, st, td, coord, tri_id, npix, S, nsplit, inv, grad_out, dst, xcd,
-                                          rec, lj, job, jcols);
+#define DR_ROWS(RR)                                                                                              \
+    if (rec)                                                                                                     \
+        launch_gather_r<DRESSI_IV_SG, RR, 256>(ct, g, st, td, coord, tri_id, npix, S, nsplit, inv, grad_out,     \
+                                               dst, xcd, rec, lj, job, jcols);                                   \
+    else                                                                                                         \
+        launch_gather_r<DRESSI_IV_SG, RR, 64>(ct, g, st, td, coord, tri_id, npix, S, nsplit, inv, grad_out, dst, \
+                                              xcd, rec, lj, job, jcols)
+    if (R == 4) { DR_ROWS(4); }
+    else if (R == 2) { DR_ROWS(2); }
+    else { DR_ROWS(1); }
+#undef DR_ROWS
 }
 
 // float4 rows need 16-byte aligned bases
