@@ -47,12 +47,24 @@ int dressi_hip_check(dressi_ctx *ctx, hipError_t e, const char *what);
 // fails with DRESSI_ENOMEM while `stream` is capturing.
 int dressi_scratch(dressi_ctx *ctx, size_t bytes, hipStream_t stream);
 int dressi_launch_check(dressi_ctx *ctx, const char *what);
-// The blend's edge mask (softras.hip): S^H from layer 0 of tri_id (hard where
-// the sign bit of dist is clear, all present fragments when dist is NULL),
-// its 4-neighbour boundary `bnd`, the row pass `rows` and the mask `edge`
-// (L-infinity dilation of radius rho >= 0), one byte per pixel [B,H,W].
-void dressi_edge_mask(const int32_t *tri_id, const float *dist, int B, int K, int H, int W, int rho,
-                      uint8_t *bnd, uint8_t *rows, uint8_t *edge, hipStream_t st);
+// The blend's edge mask as bits (softras.hip): a row of pixels is `words` words
+// of 64 bits (wide), or one of 8.
+struct EdgeBits {
+    const void *plane;
+    int words;
+    bool wide;
+    __device__ __forceinline__ uint8_t at(int64_t row, int x) const {
+        if (wide) return (uint8_t)((static_cast<const uint64_t *>(plane)[row * words + (x >> 6)] >> (x & 63)) & 1);
+        return (uint8_t)((static_cast<const uint8_t *>(plane)[row] >> x) & 1);
+    }
+};
+// S^H from layer 0 of tri_id (hard where the sign bit of dist is clear, all
+// present fragments when dist is NULL) into `sten`, its 4-neighbour boundary
+// dilated by rho >= 0 (L-infinity) into `edge`; planes of
+// dressi_edge_plane_bytes each, at most one byte a pixel.
+EdgeBits dressi_edge_mask(const int32_t *tri_id, const float *dist, int B, int K, int H, int W, int rho, void *sten,
+                          void *edge, hipStream_t st);
+size_t dressi_edge_plane_bytes(int B, int H, int W);
 // Scratch each file's entry points need at the given limits (the largest
 // call, with every optional index built internally); for dressi_limits.
 size_t dr_need_raster(const dressi_limits &l, int64_t cap);   // raster.hip

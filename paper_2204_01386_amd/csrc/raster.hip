@@ -999,7 +999,7 @@ __global__ void __launch_bounds__(256)
     k_raster_soft(const TriSetup *__restrict__ setup, const int4 *__restrict__ boxes, int32_t *__restrict__ counts,
                   const int32_t *__restrict__ bins, int cap, int T, int H, int W, int ntx, int nt, int64_t n_tiles,
                   float r, int32_t *__restrict__ tri_id, float2 *__restrict__ bary, float *__restrict__ dist,
-                  const uint8_t *__restrict__ band, unsigned long long *__restrict__ status) {
+                  EdgeBits band, unsigned long long *__restrict__ status) {
     __shared__ SoftStage sg;
     __shared__ uint16_t queue[4][RS_QUEUE];
     __shared__ unsigned long long lists[64 * K];
@@ -1032,7 +1032,7 @@ __global__ void __launch_bounds__(256)
     n = min(n, cap);
     nf = min(nf, cap);
     a.on = x < W && y < H;
-    if (BANDED) a.on = a.on && band[((int64_t)b * H + y) * W + x] != 0;
+    if (BANDED) a.on = a.on && band.at((int64_t)b * H + y, x);
     for (int i = p; i < 64 * K; i += 256) lists[i] = RS_EMPTY;
     // (the counts are an operand: every lane has them before the barrier)
     const int any = __syncthreads_or(a.on || n < 0 || nf < 0);
@@ -1213,7 +1213,7 @@ __global__ void __launch_bounds__(256)
     const int rx = lane & 7, ry = lane >> 3;
     const int ox = qx0 + rx, oy = qy0 + ry;
     if (ox >= W || oy >= H) return;
-    if (BANDED && band[((int64_t)b * H + oy) * W + ox] == 0) return;
+    if (BANDED && !band.at((int64_t)b * H + oy, ox)) return;
     const int from = ((ry >> 2) * 2 + (rx >> 2)) * 16 + (ry & 3) * 4 + (rx & 3);
     for (int k = w; k < K; k += 4) {
         const unsigned long long v = lists[from * K + k];
@@ -1305,14 +1305,14 @@ static void launch_raster_k(int hard_pix, int hyb_w, dim3 g, hipStream_t st, con
                   tid, bary);
 }
 
-// The soft layers of every pixel (edge == NULL) or of the edge mask's pixels.
+// The soft layers of every pixel (no edge plane) or of the edge mask's pixels.
 template <int K>
-static void launch_soft_k(const uint8_t *edge, int B, hipStream_t st, const TriSetup *setup, const int4 *boxes,
+static void launch_soft_k(EdgeBits edge, int B, hipStream_t st, const TriSetup *setup, const int4 *boxes,
                           int32_t *counts, const int32_t *bins, int cap, int T, int H, int W, int ntx, int nt,
                           float r, int32_t *tid, float2 *bary, float *dist, unsigned long long *status) {
     const int64_t tiles = (int64_t)B * nt;
     const dim3 g((unsigned)(4 * tiles));
-    if (edge)
+    if (edge.plane)
         DR_LAUNCH("k_raster_soft", (k_raster_soft<K, true>), g, 256, 0, st, setup, boxes, counts, bins, cap, T, H, W,
                   ntx, nt, tiles, r, tid, bary, dist, edge, status);
     else
@@ -1394,7 +1394,8 @@ static int rasterize_impl(dressi_ctx *ctx, const float *pos_clip, const int32_t 
     Carver c;
     size_t o[3];
     raster_scratch(B, T, nt, cap, soft, c, o);
-    const size_t o_band = banded ? c.take(3 * (size_t)B * H * W) : 0;   // boundary, rows, edge mask
+    const size_t o_sten = banded ? c.take(dressi_edge_plane_bytes(B, H, W)) : 0;   // S^H and the edge mask
+    const size_t o_edge = banded ? c.take(dressi_edge_plane_bytes(B, H, W)) : 0;
     rc = dressi_scratch(ctx, c.off, st);
     if (rc) return rc;
     rc = dressi_counters(ctx, (size_t)B * nt * (soft ? 3 : 1), st);   // soft: near, far, workgroups done
@@ -1418,12 +1419,10 @@ static int rasterize_impl(dressi_ctx *ctx, const float *pos_clip, const int32_t 
     }
     dim3 g((unsigned)(B * nt));
     float2 *b2 = reinterpret_cast<float2 *>(bary);
-    const uint8_t *mask = nullptr;
+    EdgeBits mask{nullptr, 0, false};
     if (banded) {
         // first pass: the front hard fragment of every pixel (the bins are
         // read again by the second pass, so their counts are kept)
-        uint8_t *bnd = at<uint8_t>(S, o_band);
-        uint8_t *rows = bnd + (size_t)B * H * W, *edge = rows + (size_t)B * H * W;
         const int keep = band >= 0 ? 1 : 0;
         switch (K) {
 #define DR_FRONT(KK)                                                                                             \
@@ -1436,8 +1435,7 @@ static int rasterize_impl(dressi_ctx *ctx, const float *pos_clip, const int32_t 
 #undef DR_FRONT
         }
         if (band < 0) return dressi_launch_check(ctx, "rasterize_banded");
-        dressi_edge_mask(tri_id, dist, B, K, H, W, band, bnd, rows, edge, st);
-        mask = edge;
+        mask = dressi_edge_mask(tri_id, dist, B, K, H, W, band, at<void>(S, o_sten), at<void>(S, o_edge), st);
     }
     const int hp = ctx->hard_raster, hw = ctx->hybrid_weight;
     switch (K) {
@@ -2500,7 +2498,8 @@ size_t dr_need_raster(const dressi_limits &l, int64_t cap) {
         Carver c;
         size_t o[3];
         raster_scratch(B, T, nt, (int)cap, l.r > 0.0f, c, o);
-        if (l.r > 0.0f) c.take(3 * (size_t)B * H * W);
+        if (l.r > 0.0f)
+            for (int k = 0; k < 2; k++) c.take(dressi_edge_plane_bytes(B, H, W));
         need = std::max(need, c.off);
     }
     {
@@ -2530,7 +2529,12 @@ extern "C" size_t dressi_limits_scratch_bytes(const dressi_limits *l) {
     need = std::max(need, dr_need_shade(*l));
     need = std::max(need, dr_need_optim(*l));
     need = std::max(need, dr_need_pbs(*l));
-    need = std::max(need, 2 * (size_t)std::max(l->B, 0) * std::max(l->H, 0) * std::max(l->W, 0));  // softras
+    {   // softras
+        Carver c;
+        for (int k = 0; k < 2; k++)
+            c.take(dressi_edge_plane_bytes(std::max(l->B, 0), std::max(l->H, 0), std::max(l->W, 0)));
+        need = std::max(need, c.off);
+    }
     // the whole packed step of one image: the packed backward's and the
     // geometry adjoints' scratch, then the fragment index's temporary
     if (l->K <= 1 && l->H > 0 && l->W > 0) {

@@ -1,11 +1,11 @@
 // HardSoftRas blend (§3.4.3, BuildBlend) and its backward for gfx950.
 //
-// Edge mask: the hard stencil S^H of the front layer, its 4-neighbour
-// boundary (both sides), and an L-infinity dilation of radius
-// rho = ceil(delta*W) - 1 done as a row pass then a column pass, integer
-// exact.  The column pass is fused with the per-pixel blend.
+// Edge mask: the hard stencil S^H of the front layer as one bit a pixel, then
+// its 4-neighbour boundary (both sides) and an L-infinity dilation of radius
+// rho = ceil(delta*W) - 1 on whole words of bits, integer exact.
 #include "dressi_internal.h"
 
+#include <algorithm>
 #include <mutex>
 
 __device__ __forceinline__ bool front_hard(const int32_t *tri_id, const float *dist, int64_t o) {
@@ -14,65 +14,170 @@ __device__ __forceinline__ bool front_hard(const int32_t *tri_id, const float *d
     return !signbit(dist[o]);
 }
 
-// S^H boundary: pixels whose S^H differs from an in-image 4-neighbour
-__global__ void k_boundary(const int32_t *__restrict__ tri_id, const float *__restrict__ dist,
-                           int B, int K, int H, int W, uint8_t *__restrict__ bnd) {
-    int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t N = (int64_t)H * W;
-    if (gid >= (int64_t)B * N) return;
-    int b = (int)(gid / N);
-    int p = (int)(gid - (int64_t)b * N);
-    int y = p / W, x = p - y * W;
-    int64_t o = (int64_t)b * K * N + p;
-    bool s = front_hard(tri_id, dist, o);
-    bool e = false;
-    if (x > 0) e |= front_hard(tri_id, dist, o - 1) != s;
-    if (x < W - 1) e |= front_hard(tri_id, dist, o + 1) != s;
-    if (y > 0) e |= front_hard(tri_id, dist, o - W) != s;
-    if (y < H - 1) e |= front_hard(tri_id, dist, o + W) != s;
-    bnd[gid] = e ? 1 : 0;
+// ---------------------------------------------------------------------------
+// Bit planes [B,H,Wd]: pixel x of a row is bit x mod N of its word x / N, N =
+// 64, or 8 for rows of at most 8 pixels (so that a plane never takes more than
+// a byte a pixel).
+//
+// One byte a pixel and a loop over the dilation's 2 rho + 1 neighbours for each
+// pixel took, for 8 views 2048^2 (rho = 20), 0.20 ms for the boundary (five
+// reads of the layer a pixel), 0.39 for the rows and most of the blend's 1.12
+// for the columns.  A word handles 64 pixels at a time: 0.054 for the stencil
+// (bound by reading the layer once), 0.038 for the whole mask (the column
+// loop's loads, from cache) and 0.45 for the blend, which reads one bit.
+// ---------------------------------------------------------------------------
+static int plane_words(int W) { return W > 8 ? (W + 63) / 64 : 1; }
+static size_t plane_bytes(int B, int H, int W) {
+    return (size_t)B * H * plane_words(W) * (W > 8 ? sizeof(uint64_t) : sizeof(uint8_t));
 }
 
-// row pass of the dilation: any boundary pixel within |dx| <= rho
-__global__ void k_dilate_rows(const uint8_t *__restrict__ bnd, int B, int H, int W, int rho,
-                              uint8_t *__restrict__ rows) {
-    int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t N = (int64_t)H * W;
-    if (gid >= (int64_t)B * N) return;
-    int64_t rowbase = gid - (gid % W);
-    int x = (int)(gid % W);
-    int a = max(x - rho, 0), e = min(x + rho, W - 1);
-    uint8_t v = 0;
-    for (int q = a; q <= e && !v; q++) v = bnd[rowbase + q];
-    rows[gid] = v;
+// S^H, one wavefront a row: 64 lanes of the row are one ballot
+__global__ void k_stencil(const int32_t *__restrict__ tri_id, const float *__restrict__ dist, int64_t rows, int K,
+                          int H, int W, int Wd, uint64_t *__restrict__ s) {
+    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (row >= rows) return;
+    const int b = (int)(row / H), y = (int)(row - (int64_t)b * H);
+    const int64_t o = ((int64_t)b * K * H + y) * W;
+    for (int d = 0; d < Wd; d++) {
+        const int x = 64 * d + lane;
+        const unsigned long long m = __ballot(x < W && front_hard(tri_id, dist, o + x));
+        if (lane == 0) s[row * Wd + d] = m;
+    }
+}
+__global__ void k_stencil8(const int32_t *__restrict__ tri_id, const float *__restrict__ dist, int64_t rows, int K,
+                           int H, int W, uint8_t *__restrict__ s) {
+    const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (row >= rows) return;
+    const int b = (int)(row / H), y = (int)(row - (int64_t)b * H);
+    const int64_t o = ((int64_t)b * K * H + y) * W;
+    unsigned m = 0;
+    for (int x = 0; x < W; x++) m |= (unsigned)front_hard(tri_id, dist, o + x) << x;
+    s[row] = (uint8_t)m;
 }
 
-// column pass of the dilation, written out as the edge mask itself (the blend
-// fuses this pass; the banded rasterizer needs the mask before any blend)
-__global__ void k_dilate_cols(const uint8_t *__restrict__ rows, int B, int H, int W, int rho,
-                              uint8_t *__restrict__ edge) {
-    int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t N = (int64_t)H * W;
-    if (gid >= (int64_t)B * N) return;
-    int b = (int)(gid / N);
-    int p = (int)(gid - (int64_t)b * N);
-    int y = p / W, x = p - y * W;
-    int a = max(y - rho, 0), e = min(y + rho, H - 1);
-    const uint8_t *col = rows + (int64_t)b * N + x;
-    uint8_t v = 0;
-    for (int q = a; q <= e && !v; q++) v = col[(int64_t)q * W];
-    edge[gid] = v;
+// One word of the S^H boundary: pixels whose S^H differs from an in-image
+// 4-neighbour.  s: its row's word, with the neighbouring words' adjacent bits
+// l and r; up, dn: the words above and below (s itself at the image's edge).
+template <typename WT>
+__device__ __forceinline__ WT boundary_word(WT s, WT up, WT dn, WT l, WT r, WT not_first, WT not_last) {
+    constexpr int N = 8 * sizeof(WT);
+    const WT left = (WT)(s ^ (WT)((WT)(s << 1) | l)) & not_first;
+    const WT right = (WT)(s ^ (WT)((WT)(s >> 1) | (WT)(r << (N - 1)))) & not_last;
+    return (WT)((s ^ up) | (s ^ dn) | left | right);
 }
 
-void dressi_edge_mask(const int32_t *tri_id, const float *dist, int B, int K, int H, int W, int rho,
-                      uint8_t *bnd, uint8_t *rows, uint8_t *edge, hipStream_t st) {
-    const int64_t n = (int64_t)B * H * W;
-    if (n == 0) return;
-    const int g = (int)((n + 255) / 256);
-    DR_LAUNCH("k_boundary", (k_boundary), g, 256, 0, st, tri_id, dist, B, K, H, W, bnd);
-    DR_LAUNCH("k_dilate_rows", (k_dilate_rows), g, 256, 0, st, bnd, B, H, W, rho, rows);
-    DR_LAUNCH("k_dilate_cols", (k_dilate_cols), g, 256, 0, st, rows, B, H, W, rho, edge);
+// The bits of x moved by 0..n places, to the left and to the right.
+template <typename WT> __device__ __forceinline__ WT spread(WT x, int n) {
+    constexpr int N = 8 * sizeof(WT);
+    n = min(n, N - 1);
+    WT a = x, b = x;
+    for (int c = 0; c < n;) {
+        const int step = min(c + 1, n - c);
+        a |= (WT)(a << step);
+        b |= (WT)(b >> step);
+        c += step;
+    }
+    return a | b;
 }
+
+// Word d of a row's boundary, ORed over the rows y - rho .. y + rho (sv: the
+// view's S^H plane).
+template <typename WT>
+__device__ __forceinline__ WT boundary_columns(const WT *__restrict__ sv, int H, int W, int Wd, int y, int d, int rho) {
+    constexpr int N = 8 * sizeof(WT);
+    sv += d;
+    const int last = W - 1 - N * d;   // the row's last pixel, if in this word
+    const WT in = last < N - 1 ? (WT)(((WT)1 << (last + 1)) - 1) : (WT)~(WT)0;
+    const WT not_first = d == 0 ? (WT)~(WT)1 : (WT)~(WT)0;
+    const WT not_last = last < N ? (WT)~((WT)1 << last) : (WT)~(WT)0;
+    const int64_t a = max((int64_t)y - rho, (int64_t)0), z = min((int64_t)y + rho, (int64_t)H - 1);
+    WT m = 0, cur = sv[a * Wd], up = a > 0 ? sv[(a - 1) * Wd] : cur;
+    for (int64_t q = a; q <= z; q++) {
+        const WT dn = q < H - 1 ? sv[(q + 1) * Wd] : cur;
+        const WT l = d > 0 ? (WT)(sv[q * Wd - 1] >> (N - 1)) : (WT)0;
+        const WT r = d < Wd - 1 ? (WT)(sv[q * Wd + 1] & 1) : (WT)0;
+        m |= boundary_word<WT>(cur, up, dn, l, r, not_first, not_last);
+        up = cur;
+        cur = dn;
+    }
+    return m & in;
+}
+
+// The edge mask: each row's boundary columns spread by rho along the row.  A
+// workgroup takes `per` whole rows of at most EDGE_WORDS words through LDS; a
+// longer row's neighbouring words are formed again by each lane that reads them.
+#define EDGE_WORDS 512
+template <typename WT, bool LONG>
+__global__ void __launch_bounds__(256)
+    k_edge_mask(const WT *__restrict__ s, int H, int W, int Wd, int64_t rows, int per, int rho, WT *__restrict__ e) {
+    constexpr int N = 8 * sizeof(WT);
+    __shared__ WT col[LONG ? 1 : EDGE_WORDS];
+    const int64_t row0 = (int64_t)blockIdx.x * per;
+    const int n = (int)min((int64_t)per, rows - row0) * Wd;
+    const int64_t b0 = row0 / H;
+    const int y0 = (int)(row0 - b0 * H);
+    if (!LONG) {
+        for (int i = threadIdx.x; i < n; i += 256) {
+            const unsigned y = (unsigned)y0 + (unsigned)i / Wd, b = y / (unsigned)H;
+            col[i] = boundary_columns<WT>(s + (b0 + b) * H * Wd, H, W, Wd, (int)(y - b * H), i % Wd, rho);
+        }
+        __syncthreads();
+    }
+    for (int i = threadIdx.x; i < n; i += 256) {
+        const unsigned y = (unsigned)y0 + (unsigned)i / Wd, b = y / (unsigned)H;
+        const int d = i % Wd;
+        const auto at = [&](int o) {   // the word o places along the row
+            if constexpr (LONG)
+                return boundary_columns<WT>(s + (b0 + b) * H * Wd, H, W, Wd, (int)(y - b * H), d + o, rho);
+            else
+                return col[i + o];
+        };
+        WT m = spread<WT>(at(0), rho);
+        // words o places away: their nearest set bit reaches in this far
+        for (int o = 1; (int64_t)N * (o - 1) < rho && (d - o >= 0 || d + o < Wd) && (WT)~m; o++) {
+            const WT r = d + o < Wd ? at(o) : (WT)0, l = d - o >= 0 ? at(-o) : (WT)0;
+            if (r) {
+                const int64_t k = (int64_t)__ffsll((unsigned long long)r) - 1 + (int64_t)N * o - rho;
+                if (k < N) m |= (WT)((WT)~(WT)0 << (k > 0 ? (int)k : 0));
+            }
+            if (l) {
+                const int64_t k = 63 - (int64_t)__clzll((long long)(unsigned long long)l) + rho - (int64_t)N * o;
+                if (k >= N - 1) m = (WT)~(WT)0;
+                else if (k >= 0) m |= (WT)(((WT)2 << k) - 1);
+            }
+        }
+        e[row0 * Wd + i] = m;
+    }
+}
+
+EdgeBits dressi_edge_mask(const int32_t *tri_id, const float *dist, int B, int K, int H, int W, int rho, void *sten,
+                          void *edge, hipStream_t st) {
+    EdgeBits eb{edge, plane_words(W), W > 8};
+    const int64_t rows = (int64_t)B * H;
+    if (rows == 0 || W == 0) return eb;
+    const int per = std::max(1, 256 / eb.words);
+    const unsigned g = (unsigned)((rows + per - 1) / per);
+    if (eb.wide) {
+        DR_LAUNCH("k_stencil", (k_stencil), (unsigned)((rows + 3) / 4), 256, 0, st, tri_id, dist, rows, K, H, W, eb.words,
+                  static_cast<uint64_t *>(sten));
+        const uint64_t *s = static_cast<const uint64_t *>(sten);
+        uint64_t *e = static_cast<uint64_t *>(edge);
+        if (eb.words <= EDGE_WORDS)
+            DR_LAUNCH("k_edge_mask", (k_edge_mask<uint64_t, false>), g, 256, 0, st, s, H, W, eb.words, rows, per, rho,
+                      e);
+        else
+            DR_LAUNCH("k_edge_mask", (k_edge_mask<uint64_t, true>), g, 256, 0, st, s, H, W, eb.words, rows, per, rho,
+                      e);
+    } else {
+        DR_LAUNCH("k_stencil", (k_stencil8), (unsigned)((rows + 255) / 256), 256, 0, st, tri_id, dist, rows, K, H, W,
+                  static_cast<uint8_t *>(sten));
+        DR_LAUNCH("k_edge_mask", (k_edge_mask<uint8_t, false>), g, 256, 0, st, static_cast<const uint8_t *>(sten), H, W,
+                  eb.words, rows, per, rho, static_cast<uint8_t *>(edge));
+    }
+    return eb;
+}
+size_t dressi_edge_plane_bytes(int B, int H, int W) { return plane_bytes(B, H, W); }
 
 // sigmoid(x) and 1 - sigmoid(x) = sigmoid(-x), each to full relative
 // precision: the complement is never formed by subtracting from 1, which
@@ -89,26 +194,31 @@ __device__ __forceinline__ float sigmoid_pair(float x, float &q) {
     return e * q;
 }
 
+// View and pixel of this lane, of B views of N pixels.  The 64-bit division is
+// the workgroup's, not the lane's: a lane divides (in 32 bits) only where its
+// workgroup goes past a view's end.
+__device__ __forceinline__ bool view_pixel(int B, int64_t N, int &b, int &p) {
+    const int64_t first = (int64_t)blockIdx.x * 256, b0 = first / N;
+    const uint32_t n = (uint32_t)N, q = (uint32_t)(first - b0 * N) + threadIdx.x;
+    const uint32_t k = q < n ? 0 : q / n;
+    b = (int)(b0 + k);
+    p = (int)(q - k * n);
+    return b < B;
+}
+
 template <int K>
-__global__ void k_blend(const float *__restrict__ color, const float *__restrict__ dist,
-                        const int32_t *__restrict__ tri_id, int B, int H, int W, int Cc,
-                        float inv_sigma, int mode, int rho, const uint8_t *__restrict__ rows,
-                        float *__restrict__ out_color, float *__restrict__ out_sil,
-                        uint8_t *__restrict__ edge) {
-    int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t N = (int64_t)H * W;
-    if (gid >= (int64_t)B * N) return;
-    int b = (int)(gid / N);
-    int p = (int)(gid - (int64_t)b * N);
-    int y = p / W, x = p - y * W;
-    uint8_t E;
-    if (mode == DRESSI_BLEND_SOFTRAS) E = 1;
-    else if (mode == DRESSI_BLEND_HARD || rho < 0) E = 0;
-    else {
-        E = 0;
-        int a = max(y - rho, 0), e = min(y + rho, H - 1);
-        const uint8_t *col = rows + (int64_t)b * N + x;
-        for (int q = a; q <= e && !E; q++) E = col[(int64_t)q * W];
+__global__ void __launch_bounds__(256)
+    k_blend(const float *__restrict__ color, const float *__restrict__ dist, const int32_t *__restrict__ tri_id,
+            int B, int H, int W, int Cc, float inv_sigma, int mode, EdgeBits eb, float *__restrict__ out_color,
+            float *__restrict__ out_sil, uint8_t *__restrict__ edge) {
+    const int64_t N = (int64_t)H * W;
+    int b, p;
+    if (!view_pixel(B, N, b, p)) return;
+    const int64_t gid = (int64_t)b * N + p;
+    uint8_t E = mode == DRESSI_BLEND_SOFTRAS;
+    if (eb.plane) {
+        const int y = p / W, x = p - y * W;
+        E = eb.at((int64_t)b * H + y, x);
     }
     edge[gid] = E;
     float *oc = out_color + gid * Cc;
@@ -147,16 +257,14 @@ __global__ void k_blend(const float *__restrict__ color, const float *__restrict
 }
 
 template <int K>
-__global__ void k_blend_bwd(const float *__restrict__ color, const float *__restrict__ dist,
-                            const int32_t *__restrict__ tri_id, int B, int H, int W, int Cc,
-                            float inv_sigma, const uint8_t *__restrict__ edge,
-                            const float *__restrict__ grad_color, const float *__restrict__ grad_sil,
-                            float *__restrict__ grad_layer, float *__restrict__ grad_dist, int skip_empty) {
-    int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t N = (int64_t)H * W;
-    if (gid >= (int64_t)B * N) return;
-    int b = (int)(gid / N);
-    int p = (int)(gid - (int64_t)b * N);
+__global__ void __launch_bounds__(256)
+    k_blend_bwd(const float *__restrict__ color, const float *__restrict__ dist, const int32_t *__restrict__ tri_id,
+                int B, int64_t N, int Cc, float inv_sigma, const uint8_t *__restrict__ edge,
+                const float *__restrict__ grad_color, const float *__restrict__ grad_sil,
+                float *__restrict__ grad_layer, float *__restrict__ grad_dist, int skip_empty) {
+    int b, p;
+    if (!view_pixel(B, N, b, p)) return;
+    const int64_t gid = (int64_t)b * N + p;
     const int64_t o1 = (int64_t)b * K * N + p;
     const float *gc = grad_color + gid * Cc;
     float gs = grad_sil ? grad_sil[gid] : 0.0f;
@@ -243,22 +351,18 @@ static int check_softras(dressi_ctx *ctx, const void *color, const void *tid, in
     default: { constexpr int KK = 5; __VA_ARGS__; } break; \
     }
 
-// The edge mask and blend, given the two one-byte-per-pixel planes the edge
-// mask needs (bnd: the boundary, rows: its row-dilated form; unused when the
-// mode needs no dilation).  Shared by dressi_softras and its allocation-free
-// variant.
+// The edge mask and blend, given the two bit planes the mask needs
+// (plane_bytes each; null when the mode needs none).  Shared by dressi_softras
+// and its allocation-free variant.
 static void softras_launch(const float *color, const float *dist, const int32_t *tri_id, int B, int K, int H,
-                           int W, int Cc, float sigma, int rho, int mode, uint8_t *bnd, uint8_t *rows,
+                           int W, int Cc, float sigma, int rho, int mode, void *sten, void *plane,
                            float *out_color, float *out_sil, uint8_t *edge_mask, hipStream_t st) {
-    const int64_t n = (int64_t)B * H * W;
-    const int g = (int)((n + 255) / 256);
-    if (rows) {
-        DR_LAUNCH("k_boundary", (k_boundary), g, 256, 0, st, tri_id, dist, B, K, H, W, bnd);
-        DR_LAUNCH("k_dilate_rows", (k_dilate_rows), g, 256, 0, st, bnd, B, H, W, rho, rows);
-    }
+    const unsigned g = (unsigned)(((int64_t)B * H * W + 255) / 256);
+    EdgeBits eb{nullptr, 0, false};
+    if (plane) eb = dressi_edge_mask(tri_id, dist, B, K, H, W, rho, sten, plane, st);
     const float inv_sigma = mode == DRESSI_BLEND_HARD ? 0.0f : 1.0f / sigma;
-    KDISPATCH(K, DR_LAUNCH("k_blend", (k_blend<KK>), g, 256, 0, st, color, dist, tri_id, B, H, W, Cc, inv_sigma, mode,
-                                                 rho, rows, out_color, out_sil, edge_mask));
+    KDISPATCH(K, DR_LAUNCH("k_blend", (k_blend<KK>), g, 256, 0, st, color, dist, tri_id, B, H, W, Cc,
+                           inv_sigma, mode, eb, out_color, out_sil, edge_mask));
 }
 
 static bool softras_needs_planes(int mode, float delta, int W, int *rho) {
@@ -278,23 +382,22 @@ extern "C" int dressi_softras(dressi_ctx *ctx, const float *color, const float *
         return dressi_fail(ctx, DRESSI_EINVAL, "softras: null output");
     hipStream_t st = (hipStream_t)stream;
     int rho = 0;
-    uint8_t *bnd = nullptr, *rows = nullptr;
+    void *sten = nullptr, *plane = nullptr;
     if (softras_needs_planes(mode, delta, W, &rho)) {
         Carver c;
-        size_t o_b = c.take((size_t)n);
-        size_t o_r = c.take((size_t)n);
+        const size_t o_s = c.take(plane_bytes(B, H, W)), o_e = c.take(plane_bytes(B, H, W));
         rc = dressi_scratch(ctx, c.off, st);
         if (rc) return rc;
-        bnd = at<uint8_t>(ctx->scratch, o_b);
-        rows = at<uint8_t>(ctx->scratch, o_r);
+        sten = at<void>(ctx->scratch, o_s);
+        plane = at<void>(ctx->scratch, o_e);
     }
-    softras_launch(color, dist, tri_id, B, K, H, W, Cc, sigma, rho, mode, bnd, rows, out_color, out_sil,
+    softras_launch(color, dist, tri_id, B, K, H, W, Cc, sigma, rho, mode, sten, plane, out_color, out_sil,
                    edge_mask, st);
     return dressi_launch_check(ctx, "softras");
 }
 
 // ---------------------------------------------------------------------------
-// Allocation-free variant of dressi_softras: the two edge-mask planes live in
+// Allocation-free variant of dressi_softras: the two edge-mask bit planes live in
 // a fixed device array of the library instead of the context's arena.  In
 // host code `scratch` names a host-side stand-in, never the device memory:
 // its device address is looked up once per device (with that device current)
@@ -341,12 +444,12 @@ extern "C" int dressi_softras_noalloc(dressi_ctx *ctx, const float *color, const
     if (!base)
         return dressi_fail(ctx, DRESSI_EHIP, "softras_noalloc: the fixed scratch of this device was not set up");
     int rho = 0;
-    uint8_t *bnd = nullptr, *rows = nullptr;
+    void *sten = nullptr, *plane = nullptr;
     if (softras_needs_planes(mode, delta, W, &rho)) {
-        bnd = base;
-        rows = base + DRESSI_SOFTRAS_NOALLOC_MAX_PIXELS;
+        sten = base;
+        plane = base + DRESSI_SOFTRAS_NOALLOC_MAX_PIXELS;
     }
-    softras_launch(color, dist, tri_id, B, K, H, W, Cc, sigma, rho, mode, bnd, rows, out_color, out_sil,
+    softras_launch(color, dist, tri_id, B, K, H, W, Cc, sigma, rho, mode, sten, plane, out_color, out_sil,
                    edge_mask, (hipStream_t)stream);
     return dressi_launch_check(ctx, "softras_noalloc");
 }
@@ -365,9 +468,9 @@ extern "C" int dressi_softras_bwd(dressi_ctx *ctx, const float *color, const flo
         return dressi_fail(ctx, DRESSI_EINVAL, "softras_bwd: null edge_mask, grad_color or grad_layer_color");
     hipStream_t st = (hipStream_t)stream;
     float inv_sigma = sigma > 0.0f ? 1.0f / sigma : 0.0f;
-    int g = (int)((n + 255) / 256);
-    KDISPATCH(K, DR_LAUNCH("k_blend_bwd", (k_blend_bwd<KK>), g, 256, 0, st, color, dist, tri_id, B, H, W, Cc, inv_sigma,
-                                                     edge_mask, grad_color, grad_sil,
-                                                     grad_layer_color, grad_dist, ctx->skip_empty));
+    const unsigned g = (unsigned)((n + 255) / 256);
+    KDISPATCH(K, DR_LAUNCH("k_blend_bwd", (k_blend_bwd<KK>), g, 256, 0, st, color, dist, tri_id, B, (int64_t)H * W,
+                           Cc, inv_sigma, edge_mask, grad_color, grad_sil, grad_layer_color, grad_dist,
+                           ctx->skip_empty));
     return dressi_launch_check(ctx, "softras_bwd");
 }
