@@ -15,10 +15,8 @@ struct Taps {
 // c modulo n in [0, n): one addition or subtraction for the usual range, a
 // division only beyond it
 __device__ __forceinline__ int wrap_repeat(int c, int n) {
-    if (c >= 0 && c < n) return c;
-    if (c < 0 && c >= -n) return c + n;
-    if (c >= n && c < 2 * n) return c - n;
-    return ((c % n) + n) % n;
+    const int r = c < 0 ? c + n : c >= n ? c - n : c;
+    return (unsigned)r < (unsigned)n ? r : ((c % n) + n) % n;
 }
 
 // s = u*n - 1/2 (float), taps floor(s) + {0,1}, wrapped or clamped

@@ -257,22 +257,24 @@ __device__ __forceinline__ void iv_weights(int t, float f, int c, int n, int s, 
 // With REC (RGBA, 2-D or array textures) each kept pixel's taps, fractions
 // and gradient come from its record (invrec_put) in one 32-byte read, in
 // place of its coordinate and gradient: the same values.
-template <int CT, int SG, int R, bool REC = false, int LANES = 256>
-__global__ void __launch_bounds__(LANES)
+template <int CT, int SG, int R, bool REC>
+__global__ void __launch_bounds__(REC ? 256 : 64)
     k_invuv_gather(dressi_tex_desc td, const float *__restrict__ coord, const int32_t *__restrict__ tri_id,
                    int64_t npix, int S, int nsplit, const int32_t *__restrict__ inv,
                    const float *__restrict__ grad_out, float *__restrict__ out, int xcd,
                    const int4 *__restrict__ rec, LossJob lj, ListJob job, int jcols) {
     static_assert(!REC || CT == 4, "records hold an RGBA gradient");
+    constexpr int LANES = REC ? 256 : 64;
     // per halo cell of each slice of the group: the winner's bilinear weights
     // on the texels at offsets -1, 0, 1 from the cell, by column (0: none, no
     // winner, or one on another cube face) and by row, and its pixel gradient
     using G = IvGeom<SG, R, LANES>;
     constexpr int NC = TEX_NC(CT);
-    __shared__ float cwx[SG][3][G::HN];   // also the loss job's 256 floats
-    __shared__ float cwy[SG][3][G::HN];
-    static_assert(LANES < 256 || 3 * SG * G::HN >= 256, "the loss job reuses cwx");
+    __shared__ __align__(16) float cwx[SG][3][G::HN];   // also the loss job's 256 floats
+    __shared__ __align__(16) float cwy[SG][3][G::HN];   // also a wavefront's queue of winners
+    static_assert(!REC || 3 * SG * G::HN >= 256, "the loss job reuses cwx");
     __shared__ float cg[SG][G::HN * NC];
+    __shared__ int cellxy[REC ? 1 : G::HN];   // x | y << 16 of the halo's cells
     const int Ht = td.Ht, Wt = td.Wt, Ct = CT > 0 ? CT : td.Ct;
     const bool cube = td.kind == DRESSI_TEX_CUBE;
     const int F = tex_faces(td);
@@ -286,9 +288,9 @@ __global__ void __launch_bounds__(LANES)
     // first workgroup runs it, the others exit)
     // and with a list-building job of the step, the columns after it are the
     // job's workgroups
-    const int lc = LANES == 256 && lj.loss ? 1 : 0;
+    const int lc = REC && lj.loss ? 1 : 0;
     const int gxb = (int)gridDim.x - lc - jcols;
-    if (LANES == 256 && (int)blockIdx.x >= gxb) {
+    if (REC && (int)blockIdx.x >= gxb) {
         if (lj.loss && (int)blockIdx.x == gxb) {
             if (blockIdx.y == 0 && blockIdx.z == 0) loss_sum_block(lj, &cwx[0][0][0]);
             return;
@@ -356,8 +358,38 @@ __global__ void __launch_bounds__(LANES)
             for (int k = 0; k < G::PT; k++) w[q][k] = (q < ng && hoff[k] >= 0) ? iv[hoff[k]] : -1;
         }
     };
+    // adds a staged slice's 3x3 cells to the lane's texels
+    auto gather = [&](int q) {
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const int ry = ly + G::LY * r, ty = by0 + ry;
+            if (tx >= Wt || ty >= Ht) continue;
+#pragma unroll
+            for (int dy = 0; dy < 3; dy++) {
+#pragma unroll
+                for (int dx = 0; dx < 3; dx++) {
+                    // the cell at (dx - 1, dy - 1) sees this texel at the opposite offset
+                    const int h = (ry + dy) * G::HW + lx + dx;
+                    const float wx = cwx[q][2 - dx][h], w = wx * cwy[q][2 - dy][h];
+                    if (wx == 0.0f || w == 0.0f) continue;
+                    float g[NC];
+#pragma unroll
+                    for (int c = 0; c < NC; c++)
+                        if (CT > 0 || c < Ct) g[c] = cg[q][h * NC + c];
+#pragma unroll
+                    for (int c = 0; c < NC; c++)
+                        if (CT > 0 || c < Ct) acc[r][c] += w * g[c];
+                }
+            }
+        }
+    };
     int wnext[SG][G::PT];
     if (s0 < s1) load_group(s0, wnext);
+    if constexpr (!REC) {
+#pragma unroll
+        for (int k = 0; k < G::PT; k++)
+            if (threadIdx.x + k * 64 < G::HN) cellxy[threadIdx.x + k * 64] = hcell[k];
+    }
     for (int g0 = s0; g0 < s1; g0 += SG) {
         const int ng = min(SG, s1 - g0);
         int wpix[SG][G::PT];
@@ -366,37 +398,86 @@ __global__ void __launch_bounds__(LANES)
 #pragma unroll
             for (int k = 0; k < G::PT; k++) wpix[q][k] = wnext[q][k];
         if (g0 + SG < s1) load_group(g0 + SG, wnext);
-        int found = 0;
-        // records: the first HK halo entries' loads are all in flight before
-        // the first is stored (all of them with one row per lane, two with
-        // more rows, where holding a third would spill registers)
-        constexpr int HK = REC ? (R == 1 ? G::PT : (G::PT < 2 ? G::PT : 2)) : 0;
-        int4 ra[SG][HK > 0 ? HK : 1], rb[SG][HK > 0 ? HK : 1];
+        if constexpr (!REC) {
+            static_assert(SG == 1, "one slice at a time");
+            // The slice's winners, packed onto the first lanes: most slices
+            // have none or few, and staging one (its coordinate's taps and six
+            // weights) costs far more than the rest.
+            unsigned long long m[G::PT], any = 0;
 #pragma unroll
-        for (int q = 0; q < SG; q++)
-#pragma unroll
-            for (int k = 0; k < HK; k++) {
-                const int i = wpix[q][k];
-                ra[q][k] = make_int4(0, 0, -1, 0);
-                rb[q][k] = make_int4(0, 0, 0, 0);
-                if (i >= 0) {
-                    const int4 *rp = rec + 2 * ((int64_t)(g0 + q) * npix + i);
-                    ra[q][k] = rp[0];
-                    rb[q][k] = rp[1];
-                }
-            }
-        // each winner's taps, computed once for the up to 9 texels that visit it
-#pragma unroll
-        for (int q = 0; q < SG; q++) {
+            for (int k = 0; k < G::PT; k++) any |= m[k] = __ballot(wpix[0][k] >= 0);
+            if (!any) continue;
+            int2 *queue = reinterpret_cast<int2 *>(&cwy[0][0][0]);   // read before the weights are written
+            int n = 0;
 #pragma unroll
             for (int k = 0; k < G::PT; k++) {
-                const int h = threadIdx.x + k * G::NT;
-                if (h >= G::HN) continue;
-                const int i = wpix[q][k];
-                bool put = false;
-                int2 tp;
-                float2 fr;
-                if (REC && i >= 0) {
+                const int h = threadIdx.x + k * 64;
+                if (wpix[0][k] >= 0)
+                    queue[n + __builtin_amdgcn_mbcnt_hi((unsigned)(m[k] >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((unsigned)m[k], 0u))] =
+                        make_int2(wpix[0][k], h);
+                n += __popcll(m[k]);
+                if (h < G::HN) cwx[0][0][h] = cwx[0][1][h] = cwx[0][2][h] = 0.0f;
+            }
+            __syncthreads();
+            int2 e[G::PT];
+#pragma unroll
+            for (int k = 0; k < G::PT; k++)
+                e[k] = (int)threadIdx.x + k * 64 < n ? queue[threadIdx.x + k * 64] : make_int2(-1, 0);
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < G::PT; k++) {
+                if (k * 64 >= n) break;
+                if (e[k].x < 0) continue;
+                const int h = e[k].y, xy = cellxy[h];
+                const int64_t o = (int64_t)g0 * npix + e[k].x;
+                // the winner's gradient is read alongside its coordinate
+                float g[NC];
+                ldv<CT>(grad_out + o * Ct, g, Ct);
+                const Taps t = make_taps(td, coord + o * cd, f);
+                if (!t.ok || t.face != f) continue;
+#pragma unroll
+                for (int c = 0; c < NC; c++)
+                    if (CT > 0 || c < Ct) cg[0][h * NC + c] = g[c];
+                iv_weights(t.x0 | (t.x1 << 16), t.fx, xy & 0xffff, Wt, G::HN, &cwx[0][0][h]);
+                iv_weights(t.y0 | (t.y1 << 16), t.fy, xy >> 16, Ht, G::HN, &cwy[0][0][h]);
+            }
+            __syncthreads();
+            gather(0);
+            __syncthreads();
+            continue;
+        } else {
+            int found = 0;
+            // the first HK halo entries' records are all in flight before the
+            // first is stored (all of them with one row per lane, two with
+            // more rows, where holding a third would spill registers)
+            constexpr int HK = R == 1 ? G::PT : (G::PT < 2 ? G::PT : 2);
+            int4 ra[SG][HK], rb[SG][HK];
+#pragma unroll
+            for (int q = 0; q < SG; q++)
+#pragma unroll
+                for (int k = 0; k < HK; k++) {
+                    const int i = wpix[q][k];
+                    ra[q][k] = make_int4(0, 0, -1, 0);
+                    rb[q][k] = make_int4(0, 0, 0, 0);
+                    if (i >= 0) {
+                        const int4 *rp = rec + 2 * ((int64_t)(g0 + q) * npix + i);
+                        ra[q][k] = rp[0];
+                        rb[q][k] = rp[1];
+                    }
+                }
+            // each winner's taps, computed once for the up to 9 texels that visit it
+#pragma unroll
+            for (int q = 0; q < SG; q++) {
+#pragma unroll
+                for (int k = 0; k < G::PT; k++) {
+                    const int h = threadIdx.x + k * G::NT;
+                    if (h >= G::HN) continue;
+                    const int i = wpix[q][k];
+                    if (i < 0) {
+                        cwx[q][0][h] = cwx[q][1][h] = cwx[q][2][h] = 0.0f;
+                        continue;
+                    }
                     // a kept pixel's taps are on the face or layer of its cell
                     int4 a, b;
                     if (k < HK) {
@@ -407,62 +488,18 @@ __global__ void __launch_bounds__(LANES)
                         a = rp[0];
                         b = rp[1];
                     }
-                    tp = make_int2(a.x, a.y);
-                    fr = make_float2(__int_as_float(a.z), __int_as_float(a.w));
-                    put = true;
+                    found = 1;
                     cg[q][h * NC] = __int_as_float(b.x);
                     cg[q][h * NC + 1] = __int_as_float(b.y);
                     cg[q][h * NC + 2] = __int_as_float(b.z);
                     cg[q][h * NC + 3] = __int_as_float(b.w);
-                } else if (!REC && i >= 0) {
-                    const int64_t o = (int64_t)(g0 + q) * npix + i;
-                    // the winner's gradient is read alongside its coordinate
-                    float g[NC];
-                    ldv<CT>(grad_out + o * Ct, g, Ct);
-                    const Taps t = make_taps(td, coord + o * cd, f);
-                    if (t.ok && t.face == f) {
-                        tp = make_int2(t.x0 | (t.x1 << 16), t.y0 | (t.y1 << 16));
-                        fr = make_float2(t.fx, t.fy);
-                        put = true;
-#pragma unroll
-                        for (int c = 0; c < NC; c++)
-                            if (CT > 0 || c < Ct) cg[q][h * NC + c] = g[c];
-                    }
-                }
-                if (put) {
-                    found = 1;
-                    iv_weights(tp.x, fr.x, hcell[k] & 0xffff, Wt, G::HN, &cwx[q][0][h]);
-                    iv_weights(tp.y, fr.y, hcell[k] >> 16, Ht, G::HN, &cwy[q][0][h]);
-                } else {
-                    cwx[q][0][h] = cwx[q][1][h] = cwx[q][2][h] = 0.0f;
+                    iv_weights(a.x, __int_as_float(a.z), hcell[k] & 0xffff, Wt, G::HN, &cwx[q][0][h]);
+                    iv_weights(a.y, __int_as_float(a.w), hcell[k] >> 16, Ht, G::HN, &cwy[q][0][h]);
                 }
             }
+            if (!__syncthreads_or(found)) continue;
         }
-        if (!__syncthreads_or(found)) continue;
-#pragma unroll
-        for (int r = 0; r < R; r++) {
-            const int ry = ly + G::LY * r, ty = by0 + ry;
-            if (tx >= Wt || ty >= Ht) continue;
-            for (int q = 0; q < ng; q++) {
-#pragma unroll
-                for (int dy = 0; dy < 3; dy++) {
-#pragma unroll
-                    for (int dx = 0; dx < 3; dx++) {
-                        // the cell at (dx - 1, dy - 1) sees this texel at the opposite offset
-                        const int h = (ry + dy) * G::HW + lx + dx;
-                        const float wx = cwx[q][2 - dx][h], w = wx * cwy[q][2 - dy][h];
-                        if (wx == 0.0f || w == 0.0f) continue;
-                        float g[NC];
-#pragma unroll
-                        for (int c = 0; c < NC; c++)
-                            if (CT > 0 || c < Ct) g[c] = cg[q][h * NC + c];
-#pragma unroll
-                        for (int c = 0; c < NC; c++)
-                            if (CT > 0 || c < Ct) acc[r][c] += w * g[c];
-                    }
-                }
-            }
-        }
+        for (int q = 0; q < ng; q++) gather(q);
         __syncthreads();
     }
 #pragma unroll
@@ -483,19 +520,19 @@ __global__ void k_invuv_reduce(const float *__restrict__ part, int nsplit, int64
     out[i] = a;
 }
 
-template <int SG, int R, int LANES>
+template <int SG, int R, bool REC>
 static void launch_gather_r(int ct, dim3 g, hipStream_t st, const dressi_tex_desc &td, const float *coord,
                             const int32_t *tri_id, int64_t npix, int S, int nsplit, const int32_t *inv,
                             const float *grad_out, float *dst, int xcd, const int4 *rec, LossJob lj,
                             const ListJob &job, int jcols) {
-#define DR_GATHER(CT, REC)                                                                                       \
-    DR_LAUNCH("k_invuv_gather", (k_invuv_gather<CT, SG, R, REC, LANES>), g, LANES, 0, st, td, coord, tri_id, npix, S, \
-              nsplit, inv, grad_out, dst, xcd, rec, lj, job, jcols)
-    if constexpr (LANES == 256) DR_GATHER(4, true);
-    else if (ct == 4) DR_GATHER(4, false);
-    else if (ct == 3) DR_GATHER(3, false);
-    else if (ct == 8) DR_GATHER(8, false);
-    else if constexpr (R == 1) DR_GATHER(0, false);   // other channel counts
+#define DR_GATHER(CT)                                                                                            \
+    DR_LAUNCH("k_invuv_gather", (k_invuv_gather<CT, SG, R, REC>), g, REC ? 256 : 64, 0, st, td, coord, tri_id, npix, \
+              S, nsplit, inv, grad_out, dst, xcd, rec, lj, job, jcols)
+    if constexpr (REC) DR_GATHER(4);
+    else if (ct == 4) DR_GATHER(4);
+    else if (ct == 3) DR_GATHER(3);
+    else if (ct == 8) DR_GATHER(8);
+    else if constexpr (R == 1) DR_GATHER(0);   // other channel counts
 #undef DR_GATHER
 }
 
@@ -503,12 +540,16 @@ static void launch_gather_r(int ct, dim3 g, hipStream_t st, const dressi_tex_des
 // other between the slices' loads and sums; 256 where the launch also carries
 // the loss or list jobs of a step (records), whose code takes 256.
 // Texel rows per lane: `rows` (1, 2 or 4) or, for 0, 1, but 2 with records of a
-// large texture.  Measured, 64 lanes with 1 and 2 rows and 256 lanes with 1 and 2
-// (us): 8 slices of 512^2 on 1024^2 RGB 57, 70, 60, 58; 8 of 500 x 333 on 768^2
-// RGBA 31, 34, 38, 38; 48 of 512^2 on 1024^2 x 8 channels and a cube map 320, 414,
-// 339, 406; 24 of 2048^2 on 4096^2 RGBA 2563, 2760, 2985, 2786; before weights
-// were staged in place of taps, 256 lanes: 70, 42, 355, 2650 (2 rows).  Any
-// choice gives the same sums in the same order.
+// large texture.  Measured, 64 lanes with 1, 2 and 4 rows (us): 8 slices of
+// 512^2 on 1024^2 RGB 44, 51, 82; 8 of 500 x 333 on 768^2 RGBA 26.5, 26.8, 40; 48
+// of 512^2 on 1024^2 x 8 channels and a cube map 305, 338, 457; 24 of 2048^2 on
+// 4096^2 RGBA 1981, 2120, 2883.  With a winner staged by the lane of its cell
+// (64 lanes, 1 row: 57, 31, 320, 2563; 256 lanes: 60, 38, 339, 2985) two thirds of
+// the instructions were a few lanes' staging, and with taps in place of weights
+// 256 lanes took 70, 42, 355, 2650 (2 rows).  Maps loaded 2, 4 or 6 slices ahead
+// in place of 1 gain nothing (24 slices of 2048^2: 1989, 2160, 2394): the waves in
+// flight already cover that latency.  Any choice gives the same sums in the
+// same order.
 static int gather_rows(int rows, int ct, const dressi_tex_desc &td, bool rec) {
     if (ct != 3 && ct != 4 && ct != 8) return 1;
     if (rows == 1 || rows == 2 || rows == 4) return rows;
@@ -527,10 +568,10 @@ static void launch_gather(int rows, int ct, int64_t gx, int64_t ty_cells, int gz
     dim3 g((unsigned)(gx + (lj.loss ? 1 : 0) + jcols), (unsigned)gy, (unsigned)gz);
 #define DR_ROWS(RR)                                                                                              \
     if (rec)                                                                                                     \
-        launch_gather_r<DRESSI_IV_SG, RR, 256>(ct, g, st, td, coord, tri_id, npix, S, nsplit, inv, grad_out,     \
+        launch_gather_r<DRESSI_IV_SG, RR, true>(ct, g, st, td, coord, tri_id, npix, S, nsplit, inv, grad_out,     \
                                                dst, xcd, rec, lj, job, jcols);                                   \
     else                                                                                                         \
-        launch_gather_r<DRESSI_IV_SG, RR, 64>(ct, g, st, td, coord, tri_id, npix, S, nsplit, inv, grad_out, dst, \
+        launch_gather_r<DRESSI_IV_SG, RR, false>(ct, g, st, td, coord, tri_id, npix, S, nsplit, inv, grad_out, dst, \
                                               xcd, rec, lj, job, jcols)
     if (R == 4) { DR_ROWS(4); }
     else if (R == 2) { DR_ROWS(2); }
