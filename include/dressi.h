@@ -588,6 +588,40 @@ int dressi_packed_backward(dressi_ctx *ctx, const dressi_packed_scene *scene, co
                            float *grad_samp, float *grad_bary_uv, int32_t *inv, void *inv_rec, float *grad_tex,
                            void *stream);
 
+/* Inputs of the packed pass over the K layers of a soft image: s as in the
+ * packed single-layer pass, with mode Lambert (Cv 9), Phong (Cv 6, td of 4
+ * channels) or Phong with environment (Cv 9: normal, position, tangent; td
+ * of 8 channels: RGBA, normal map, padding), td a 2-D texture and tri_eye
+ * NULL; env, env_td: the environment cube map (3 channels). */
+typedef struct {
+    dressi_packed_scene s;
+    const float *env;
+    dressi_tex_desc env_td;
+} dressi_layer_scene;
+
+/* The per-fragment stages before the blend, over tri_id [B,K,H,W] and bary
+ * [B,K,H,W,2], as one pass.  Writes the same values as dressi_interpolate
+ * (gbuf [B,K,H,W,Cv]; textured: uvbuf [B,K,H,W,2]), dressi_texture (samp
+ * [B,K,H,W,Ct], 16-byte aligned), with an environment dressi_shade's dir and
+ * dressi_texture of it (dir, env_s [B,K,H,W,3]), and dressi_shade (color
+ * [B,K,H,W,3]); empty slots as DRESSI_TUNE_EMPTY_SLOTS says. */
+int dressi_layers_forward(dressi_ctx *ctx, const dressi_layer_scene *scene, const int32_t *tri_id,
+                          const float *bary, int B, int K, int H, int W, float *gbuf, float *uvbuf, float *samp,
+                          float *dir, float *env_s, float *color, void *stream);
+/* Their adjoints (textured modes), from grad_color [B,K,H,W,3] (dressi_softras_bwd's
+ * grad_layer_color): grad_gbuf, grad_samp and grad_env_s as dressi_shade_bwd
+ * writes them (16-byte aligned grad_samp, whose 8th channel is not written
+ * and must be zero), grad_bary_uv [B,K,H,W,2] as dressi_interpolate_bwd of uv does from
+ * dressi_texture_bwd's coordinate gradient, and the texel gradients grad_tex
+ * [Ht,Wt,Ct] and grad_env [6,S,S,3] of dressi_texture_bwd (frame 0).
+ * inv_env: dressi_invuv_bytes(env_td, B*K) bytes of workspace.  The scratch
+ * of dressi_texture_bwd on the albedo covers the call. */
+int dressi_layers_backward(dressi_ctx *ctx, const dressi_layer_scene *scene, const int32_t *tri_id, int B, int K,
+                           int H, int W, const float *gbuf, const float *uvbuf, const float *samp,
+                           const float *dir, const float *env_s, const float *grad_color, float *grad_gbuf,
+                           float *grad_samp, float *grad_env_s, float *grad_bary_uv, int32_t *inv_env,
+                           float *grad_tex, float *grad_env, void *stream);
+
 /* Geometry stages of the forward pass for one hard layer (§3.4.1's vertex
  * stage, then rasterization by Algorithm 2 with K = 1, r = 0, and the
  * fragment index of its result): the outputs of dressi_vertex_stage (vattr

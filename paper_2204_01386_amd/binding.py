@@ -59,6 +59,11 @@ class PackedScene(C.Structure):
                 ("tri_eye", _vp)]
 
 
+class LayerScene(C.Structure):
+    """dressi_layer_scene: the inputs of the packed pass over a soft image's layers."""
+    _fields_ = [("s", PackedScene), ("env", _vp), ("env_td", TexDesc)]
+
+
 class PackedStepBufs(C.Structure):
     """dressi_packed_step_bufs: the inputs, forward values and gradients of
     one packed step (dressi_packed_step)."""
@@ -138,6 +143,9 @@ _SIG = {
     "dressi_packed_forward": [_vp, _vp, _vp, _vp, _i, _i, _i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp],
     "dressi_packed_backward": [_vp, _vp, _vp, _i, _i, _i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp,
                                _vp, _vp, _vp, _vp, _vp, _vp, _vp],
+    "dressi_layers_forward": [_vp, _vp, _vp, _vp, _i, _i, _i, _i, _vp, _vp, _vp, _vp, _vp, _vp, _vp],
+    "dressi_layers_backward": [_vp, _vp, _vp, _i, _i, _i, _i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp,
+                               _vp, _vp, _vp, _vp],
     "dressi_texture_grad_invrec": [_vp, _vp, _i, _i, _i, _vp, _vp, _vp, _vp],
     "dressi_transform_batched": [_vp, _vp, _vp, _vp, _i, _vp, _vp],
     "dressi_tune": [_vp, _i, _i64],

@@ -148,6 +148,16 @@ __device__ __forceinline__ void loss_sum_block(const LossJob &j, float *red) {
 // job in an extra workgroup of its launch; part: scratch of
 // dressi_invuv_part_bytes(cells, 4, S).
 struct ListJob;
+// checks of a texture's descriptor, coordinates and slices, and of what its
+// texel gradient needs (texture.hip)
+int dr_check_tex(dressi_ctx *ctx, const void *tex, const dressi_tex_desc *td, const void *coord, const void *tid,
+                 int S, int H, int W);
+int dr_check_grad_tex(dressi_ctx *ctx, const dressi_tex_desc *td, const int32_t *tri_id, const char *what);
+// The texel gradient from a registered inverse-UV map; part: the bytes of
+// dressi_invuv_part_bytes(cells, Ct, S).
+void dr_gather_invuv(const dressi_tex_desc &td, const float *coord, const int32_t *tri_id, int S, int64_t npix,
+                     const int32_t *inv, const float *grad_out, float *part, float *grad_tex, hipStream_t st,
+                     int rows);
 void dr_gather_invrec(const dressi_tex_desc &td, int S, int64_t npix, const int32_t *inv, const int4 *rec,
                       float *part, float *grad_tex, hipStream_t st, int rows, LossJob lj, const ListJob &job);
 

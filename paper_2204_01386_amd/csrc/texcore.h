@@ -207,3 +207,46 @@ __device__ __forceinline__ void tex_dcoord(const float *__restrict__ tex, const 
     tex_taps_load<CT>(tex, td, t, Ct, p00, p01, p10, p11);
     tex_dcoord_texels<CT>(td, t, p00, p01, p10, p11, g, Ct, du, dv);
 }
+
+// The inverse-UV cell that a coordinate q with valid taps falls in, on the
+// taps' face or layer.
+__device__ __forceinline__ int64_t tex_cell(const dressi_tex_desc &td, const Taps &t, const float *q) {
+    int cx, cy;
+    if (td.kind == DRESSI_TEX_CUBE) {
+        float u, v, sc, tc, ma;
+        cube_face(q[0], q[1], q[2], u, v, sc, tc, ma);
+        cx = cell1d(u, td.Wt, DRESSI_WRAP_CLAMP);
+        cy = cell1d(v, td.Ht, DRESSI_WRAP_CLAMP);
+    } else {
+        cx = cell1d(q[0], td.Wt, td.wrap_u);
+        cy = cell1d(q[1], td.Ht, td.wrap_v);
+    }
+    return ((int64_t)t.face * td.Ht + cy) * td.Wt + cx;
+}
+
+// The gradient of a cube direction q from that of its face coordinates.
+__device__ __forceinline__ void cube_dcoord(const float *q, float du, float dv, float *g3) {
+    // u = (sc/ma + 1)/2 with ma = |major component|
+    float u, v, sc, tc, ma;
+    int f = cube_face(q[0], q[1], q[2], u, v, sc, tc, ma);
+    float gs = 0.5f * du / ma, gt = 0.5f * dv / ma;
+    float gm = -0.5f * (du * sc + dv * tc) / (ma * ma);
+    g3[0] = g3[1] = g3[2] = 0.0f;
+    // component index and sign of sc, tc and the major axis per face
+    switch (f) {
+    case 0: g3[2] -= gs; g3[1] -= gt; g3[0] += gm; break;
+    case 1: g3[2] += gs; g3[1] -= gt; g3[0] -= gm; break;
+    case 2: g3[0] += gs; g3[2] += gt; g3[1] += gm; break;
+    case 3: g3[0] += gs; g3[2] -= gt; g3[1] -= gm; break;
+    case 4: g3[0] += gs; g3[1] -= gt; g3[2] += gm; break;
+    default: g3[0] -= gs; g3[1] -= gt; g3[2] -= gm; break;
+    }
+}
+
+// Large textures (4 Mi cells a face and more): the per-pixel kernels give
+// each XCD one contiguous range of pixels, whose texels are then fetched
+// into one L2; smaller textures keep the default interleave.
+#define IV_LARGE_CELLS (1 << 22)
+__device__ __forceinline__ int64_t tex_block(const dressi_tex_desc &td) {
+    return (int64_t)td.Ht * td.Wt >= IV_LARGE_CELLS ? xcd_block() : (int64_t)blockIdx.x;
+}

@@ -10,15 +10,6 @@
 // slice, in a fixed order.  No float atomics.
 #include "texcore.h"
 
-
-// Large textures (4 Mi cells a face and more): the per-pixel kernels give
-// each XCD one contiguous range of pixels, whose texels are then fetched
-// into one L2; smaller textures keep the default interleave.
-#define IV_LARGE_CELLS (1 << 22)
-__device__ __forceinline__ int64_t tex_block(const dressi_tex_desc &td) {
-    return (int64_t)td.Ht * td.Wt >= IV_LARGE_CELLS ? xcd_block() : (int64_t)blockIdx.x;
-}
-
 template <int CT>
 __global__ void __launch_bounds__(256)
     k_tex_fwd(const float *__restrict__ tex, dressi_tex_desc td, const float *__restrict__ coord,
@@ -64,18 +55,8 @@ __global__ void __launch_bounds__(256)
     if (inv && covered && t.ok) {
         int s = (int)(i / npix);
         int pix = (int)(i - (int64_t)s * npix);
-        int cx, cy;
-        if (cube) {
-            float u, v, sc, tc, ma;
-            cube_face(q[0], q[1], q[2], u, v, sc, tc, ma);
-            cx = cell1d(u, td.Wt, DRESSI_WRAP_CLAMP);
-            cy = cell1d(v, td.Ht, DRESSI_WRAP_CLAMP);
-        } else {
-            cx = cell1d(q[0], td.Wt, td.wrap_u);
-            cy = cell1d(q[1], td.Ht, td.wrap_v);
-        }
-        int64_t cells = (int64_t)tex_faces(td) * td.Ht * td.Wt;
-        atomicMax(&inv[(int64_t)s * cells + ((int64_t)t.face * td.Ht + cy) * td.Wt + cx], pix);
+        const int64_t cells = (int64_t)tex_faces(td) * td.Ht * td.Wt;
+        atomicMax(&inv[(int64_t)s * cells + tex_cell(td, t, q)], pix);
     }
     if (!grad_coord || (skip_empty && !covered)) return;
     float *gc = grad_coord + i * cd;
@@ -92,21 +73,8 @@ __global__ void __launch_bounds__(256)
         gc[1] = dv;
         return;
     }
-    // u = (sc/ma + 1)/2 with ma = |major component|
-    float u, v, sc, tc, ma;
-    int f = cube_face(q[0], q[1], q[2], u, v, sc, tc, ma);
-    float gs = 0.5f * du / ma, gt = 0.5f * dv / ma;
-    float gm = -0.5f * (du * sc + dv * tc) / (ma * ma);
-    float g3[3] = {0.0f, 0.0f, 0.0f};
-    // component index and sign of sc, tc and the major axis per face
-    switch (f) {
-    case 0: g3[2] -= gs; g3[1] -= gt; g3[0] += gm; break;
-    case 1: g3[2] += gs; g3[1] -= gt; g3[0] -= gm; break;
-    case 2: g3[0] += gs; g3[2] += gt; g3[1] += gm; break;
-    case 3: g3[0] += gs; g3[2] -= gt; g3[1] -= gm; break;
-    case 4: g3[0] += gs; g3[1] -= gt; g3[2] += gm; break;
-    default: g3[0] -= gs; g3[1] -= gt; g3[2] -= gm; break;
-    }
+    float g3[3];
+    cube_dcoord(q, du, dv, g3);
     gc[0] = g3[0];
     gc[1] = g3[1];
     gc[2] = g3[2];
@@ -584,7 +552,7 @@ static bool aligned16(const void *a, const void *b) {
     return (((uintptr_t)a | (uintptr_t)b) & 15u) == 0;
 }
 
-static int check_tex(dressi_ctx *ctx, const void *tex, const dressi_tex_desc *td, const void *coord,
+int dr_check_tex(dressi_ctx *ctx, const void *tex, const dressi_tex_desc *td, const void *coord,
                      const void *tid, int S, int H, int W) {
     if (!ctx) return DRESSI_EINVAL;
     if (!td) return dressi_fail(ctx, DRESSI_EINVAL, "texture: null descriptor");
@@ -611,7 +579,7 @@ static int check_tex(dressi_ctx *ctx, const void *tex, const dressi_tex_desc *td
 extern "C" int dressi_texture(dressi_ctx *ctx, const float *tex, const dressi_tex_desc *td,
                               const float *coord, const int32_t *tri_id, int S, int H, int W,
                               float *out, void *stream) {
-    int rc = check_tex(ctx, tex, td, coord, tri_id, S, H, W);
+    int rc = dr_check_tex(ctx, tex, td, coord, tri_id, S, H, W);
     if (rc) return rc;
     int64_t n = (int64_t)S * H * W;
     if (n == 0) return DRESSI_OK;
@@ -669,7 +637,7 @@ static void tex_gather(const dressi_tex_desc &td, const float *coord, const int3
     }
 }
 
-static int check_grad_tex(dressi_ctx *ctx, const dressi_tex_desc *td, const int32_t *tri_id, const char *what) {
+int dr_check_grad_tex(dressi_ctx *ctx, const dressi_tex_desc *td, const int32_t *tri_id, const char *what) {
     if (!tri_id) return dressi_fail(ctx, DRESSI_EINVAL, what);
     if (td->kind != DRESSI_TEX_CUBE &&
         ((td->wrap_u == DRESSI_WRAP_REPEAT && td->Wt < 3) || (td->wrap_v == DRESSI_WRAP_REPEAT && td->Ht < 3)))
@@ -681,11 +649,11 @@ extern "C" int dressi_texture_bwd(dressi_ctx *ctx, const float *tex, const dress
                                   const float *coord, const int32_t *tri_id, int S, int H, int W,
                                   const float *grad_out, uint32_t frame, float *grad_tex, float *grad_coord,
                                   void *stream) {
-    int rc = check_tex(ctx, tex, td, coord, tri_id, S, H, W);
+    int rc = dr_check_tex(ctx, tex, td, coord, tri_id, S, H, W);
     if (rc) return rc;
     int64_t npix = (int64_t)H * W, n = (int64_t)S * npix;
     if (n > 0 && !grad_out) return dressi_fail(ctx, DRESSI_EINVAL, "texture_bwd: null grad_out");
-    if (grad_tex && (rc = check_grad_tex(ctx, td, tri_id, "texture_bwd: the texture gradient needs tri_id")))
+    if (grad_tex && (rc = dr_check_grad_tex(ctx, td, tri_id, "texture_bwd: the texture gradient needs tri_id")))
         return rc;
     const bool jit = grad_tex && frame > 0;
     if (jit && td->kind == DRESSI_TEX_2D_ARRAY)
@@ -745,9 +713,9 @@ extern "C" size_t dressi_invuv_bytes(const dressi_tex_desc *td, int S) {
 extern "C" int dressi_invuv_build(dressi_ctx *ctx, const dressi_tex_desc *td, const float *coord,
                                   const int32_t *tri_id, int S, int H, int W, int32_t *inv, void *stream) {
     // the texels themselves are not read: any non-null pointer passes the shared check
-    int rc = check_tex(ctx, coord, td, coord, tri_id, S, H, W);
+    int rc = dr_check_tex(ctx, coord, td, coord, tri_id, S, H, W);
     if (rc) return rc;
-    if ((rc = check_grad_tex(ctx, td, tri_id, "invuv_build: needs tri_id"))) return rc;
+    if ((rc = dr_check_grad_tex(ctx, td, tri_id, "invuv_build: needs tri_id"))) return rc;
     if (S > 0 && !inv) return dressi_fail(ctx, DRESSI_EINVAL, "invuv_build: null inv");
     tex_bwd_pixels(nullptr, *td, coord, tri_id, (int64_t)H * W, S, nullptr, nullptr, inv, (hipStream_t)stream);
     return dressi_launch_check(ctx, "invuv_build");
@@ -756,9 +724,9 @@ extern "C" int dressi_invuv_build(dressi_ctx *ctx, const dressi_tex_desc *td, co
 extern "C" int dressi_texture_grad_invuv(dressi_ctx *ctx, const dressi_tex_desc *td, const float *coord,
                                          const int32_t *tri_id, int S, int H, int W, const int32_t *inv,
                                          const float *grad_out, float *grad_tex, void *stream) {
-    int rc = check_tex(ctx, coord, td, coord, tri_id, S, H, W);
+    int rc = dr_check_tex(ctx, coord, td, coord, tri_id, S, H, W);
     if (rc) return rc;
-    if ((rc = check_grad_tex(ctx, td, tri_id, "texture_grad_invuv: needs tri_id"))) return rc;
+    if ((rc = dr_check_grad_tex(ctx, td, tri_id, "texture_grad_invuv: needs tri_id"))) return rc;
     if (!grad_tex) return dressi_fail(ctx, DRESSI_EINVAL, "texture_grad_invuv: null grad_tex");
     if (S > 0 && (!inv || (H * W > 0 && !grad_out)))
         return dressi_fail(ctx, DRESSI_EINVAL, "texture_grad_invuv: null inv or grad_out");
@@ -774,6 +742,12 @@ extern "C" int dressi_texture_grad_invuv(dressi_ctx *ctx, const dressi_tex_desc 
     return dressi_launch_check(ctx, "texture_grad_invuv");
 }
 
+void dr_gather_invuv(const dressi_tex_desc &td, const float *coord, const int32_t *tri_id, int S, int64_t npix,
+                     const int32_t *inv, const float *grad_out, float *part, float *grad_tex, hipStream_t st,
+                     int rows) {
+    tex_gather(td, coord, tri_id, npix, S, inv, grad_out, part, grad_tex, st, rows);
+}
+
 void dr_gather_invrec(const dressi_tex_desc &td, int S, int64_t npix, const int32_t *inv, const int4 *rec,
                       float *part, float *grad_tex, hipStream_t st, int rows, LossJob lj, const ListJob &job) {
     tex_gather(td, nullptr, nullptr, npix, S, inv, nullptr, part, grad_tex, st, rows, rec, lj, job);
@@ -782,9 +756,9 @@ void dr_gather_invrec(const dressi_tex_desc &td, int S, int64_t npix, const int3
 extern "C" int dressi_texture_grad_invrec(dressi_ctx *ctx, const dressi_tex_desc *td, int S, int H, int W,
                                           const int32_t *inv, const void *rec, float *grad_tex, void *stream) {
     // the records stand in for the texels, coordinates and triangle ids in the shared checks
-    int rc = check_tex(ctx, rec, td, rec, rec, S, H, W);
+    int rc = dr_check_tex(ctx, rec, td, rec, rec, S, H, W);
     if (rc) return rc;
-    if ((rc = check_grad_tex(ctx, td, inv, "texture_grad_invrec: null inv"))) return rc;
+    if ((rc = dr_check_grad_tex(ctx, td, inv, "texture_grad_invrec: null inv"))) return rc;
     if (td->kind == DRESSI_TEX_CUBE || td->Ct != 4)
         return dressi_fail(ctx, DRESSI_EINVAL, "texture_grad_invrec: records are for 2-D RGBA textures and arrays");
     if (!grad_tex || !aligned16(rec, grad_tex))

@@ -300,6 +300,15 @@ class Step(_TwoStreams):
                 # each covered pixel's gather record (taps, fractions, gradient)
                 self.inv_rec = torch.empty((B, H * W, 8), dtype=torch.float32, device=dev)
             self._pscene = ps
+        # other forms: the stages between the rasterization and the blend as one
+        # forward and one backward pass over the layers (same values; the
+        # coordinate gradients g_uvbuf and g_dir stay in registers); False keeps
+        # the separate stages
+        self.fuse_layers = not self.packed
+        self.inv_env = None
+        if self.fuse_layers and self.env is not None:
+            nb = int(_lib.dressi_invuv_bytes(C.byref(self.env_desc), B * K))
+            self.inv_env = torch.empty(nb // 4, dtype=torch.int32, device=dev)
         # one view: the geometry adjoints as one call (dressi_geometry_bwd)
         self.packed_geo = self.packed and B == 1
         self.hard_raster = None     # rasterization strategy chosen by autotune() (None: triangle-parallel)
@@ -380,6 +389,30 @@ class Step(_TwoStreams):
                 fi.env, fi.env_stride = _cp(self.env_s, 0), 3
         return fi
 
+    def _layer_scene(self):
+        """The step's tensors as the packed layer pass takes them, or None
+        where the stages run separately: other channel counts, or texels and
+        samples that float4 accesses are not aligned for."""
+        if not self.fuse_layers:
+            return None
+        if self.mode != Bd.SHADE_LAMBERT:
+            if self.Ct != (8 if self.mode == Bd.SHADE_PHONG_ENV else 4) or self.desc.kind != Bd.TEX_2D:
+                return None
+            if any(t.data_ptr() % 16 for t in (self.tex, self.samp, self.g_samp)):
+                return None
+        ls = Bd.LayerScene()
+        ps = ls.s
+        ps.mode, ps.vattr, ps.V, ps.Cv = self.mode, _p(self.vattr), self.V, self.Cv
+        ps.tris, ps.T, ps.eye = _p(self.tris), self.T, _p(self.eye)
+        if self.mode != Bd.SHADE_LAMBERT:
+            ps.uv, ps.uv_tris, ps.Vuv = _p(self.uv), _p(self.uv_tris), self.uv.shape[0]
+            ps.tex, ps.td = _p(self.tex), self.desc
+        if self.env is not None:
+            if self.env_desc.Ct != 3:
+                return None
+            ls.env, ls.env_td = _p(self.env), self.env_desc
+        return ls
+
     def _chk(self, rc, what):
         if rc != 0:
             self.ctx.check(rc, what)
@@ -428,21 +461,27 @@ class Step(_TwoStreams):
                                           _p(self.sil), _p(self.E), _p(self.inv), s), "packed_forward")
             self._join()
             return
-        ck(_lib.dressi_interpolate(h, _p(self.vattr), 1, V, self.Cv, _p(self.tris), T, _p(self.tri_id),
-                                   _p(self.bary), B, K, H, W, _p(self.gbuf), s), "interpolate")
-        if self.uv is not None:
-            ck(_lib.dressi_interpolate(h, _p(self.uv), 1, self.uv.shape[0], 2, _p(self.uv_tris), T,
-                                       _p(self.tri_id), _p(self.bary), B, K, H, W, _p(self.uvbuf), s),
-               "interpolate uv")
-            ck(_lib.dressi_texture(h, _p(self.tex), C.byref(self.desc), _p(self.uvbuf), _p(self.tri_id),
-                                   B * K, H, W, _p(self.samp), s), "texture")
-        if self.env is not None:
-            ck(_lib.dressi_shade(h, self.mode, C.byref(self._fin_dir), _p(self.eye), _p(self.tri_id), B,
-                                 K * H * W, None, _p(self.dir), s), "shade dir")
-            ck(_lib.dressi_texture(h, _p(self.env), C.byref(self.env_desc), _p(self.dir),
-                                   _p(self.tri_id), B * K, H, W, _p(self.env_s), s), "texture env")
-        ck(_lib.dressi_shade(h, self.mode, C.byref(self._fin), _p(self.eye), _p(self.tri_id), B,
-                             K * H * W, _p(self.layer_color), None, s), "shade")
+        ls = self._layer_scene()
+        if ls is not None:
+            ck(_lib.dressi_layers_forward(h, C.byref(ls), _p(self.tri_id), _p(self.bary), B, K, H, W,
+                                          _p(self.gbuf), _p(self.uvbuf), _p(self.samp), _p(self.dir),
+                                          _p(self.env_s), _p(self.layer_color), s), "layers_forward")
+        else:
+            ck(_lib.dressi_interpolate(h, _p(self.vattr), 1, V, self.Cv, _p(self.tris), T, _p(self.tri_id),
+                                       _p(self.bary), B, K, H, W, _p(self.gbuf), s), "interpolate")
+            if self.uv is not None:
+                ck(_lib.dressi_interpolate(h, _p(self.uv), 1, self.uv.shape[0], 2, _p(self.uv_tris), T,
+                                           _p(self.tri_id), _p(self.bary), B, K, H, W, _p(self.uvbuf), s),
+                   "interpolate uv")
+                ck(_lib.dressi_texture(h, _p(self.tex), C.byref(self.desc), _p(self.uvbuf), _p(self.tri_id),
+                                       B * K, H, W, _p(self.samp), s), "texture")
+            if self.env is not None:
+                ck(_lib.dressi_shade(h, self.mode, C.byref(self._fin_dir), _p(self.eye), _p(self.tri_id), B,
+                                     K * H * W, None, _p(self.dir), s), "shade dir")
+                ck(_lib.dressi_texture(h, _p(self.env), C.byref(self.env_desc), _p(self.dir),
+                                       _p(self.tri_id), B * K, H, W, _p(self.env_s), s), "texture env")
+            ck(_lib.dressi_shade(h, self.mode, C.byref(self._fin), _p(self.eye), _p(self.tri_id), B,
+                                 K * H * W, _p(self.layer_color), None, s), "shade")
         ck(_lib.dressi_softras(h, _p(self.layer_color), _p(self.dist), _p(self.tri_id), B, K, H, W, 3,
                                self.sigma, self.delta, self.blend, _p(self.color), _p(self.sil),
                                _p(self.E), s), "softras")
@@ -466,6 +505,16 @@ class Step(_TwoStreams):
         ck(_lib.dressi_softras_bwd(h, _p(self.layer_color), _p(self.dist), _p(self.tri_id), B, K, H, W, 3,
                                    self.sigma, _p(self.E), _p(self.g_color), _p(self.g_sil),
                                    _p(self.g_layer), _p(self.g_dist), s), "softras_bwd")
+        ls = self._layer_scene() if self.uv is not None and self.frame == 0 and not self._on("texel") else None
+        if ls is not None:
+            ck(_lib.dressi_layers_backward(h, C.byref(ls), _p(self.tri_id), B, K, H, W, _p(self.gbuf),
+                                           _p(self.uvbuf), _p(self.samp), _p(self.dir), _p(self.env_s),
+                                           _p(self.g_layer), _p(self.g_gbuf), _p(self.g_samp), _p(self.g_env_s),
+                                           _p(self.g_bary_uv), _p(self.inv_env), _p(self.g_tex),
+                                           _p(self.g_envtex), s), "layers_backward")
+            self._backward_geometry(self.g_bary_uv)
+            self._join()
+            return
         Npv = K * H * W
         if self.env is not None:
             ge = Bd.FragGrad()
