@@ -1065,11 +1065,21 @@ __device__ __forceinline__ bool tri_corners(const int32_t *__restrict__ tris, in
     return !(v0 < 0 || v0 >= Va || v1 < 0 || v1 >= Va || v2 < 0 || v2 >= Va);
 }
 
+// Slice (view, or layer of one) and pixel of this lane of a 256-lane block, of n
+// pixels a slice: a lane divides, in 32 bits, only past a slice's end.
+__device__ __forceinline__ void slice_pixel(int64_t block, uint32_t n, int &sl, int &pix) {
+    const int64_t first = block * 256, s0 = first / n;
+    const uint32_t q = (uint32_t)(first - s0 * n) + threadIdx.x;
+    const uint32_t k = q < n ? 0 : q / n;
+    sl = (int)(s0 + k);
+    pix = (int)(q - k * n);
+}
+
 // CV attribute channels (6: normal, position; 9: + colour); TEX: Phong with a
 // 2-D RGBA albedo texture, else Lambert with the vertex colour.
 template <int CV, bool TEX>
 __global__ void __launch_bounds__(256)
-    k_packed_fwd(int mode, dressi_packed_scene sc, const int32_t *__restrict__ tri_id,
+    k_packed_fwd(dressi_packed_scene sc, const int32_t *__restrict__ tri_id,
                  const float2 *__restrict__ bary, int64_t npix, int64_t n, float *__restrict__ gbuf,
                  float *__restrict__ uvbuf, float *__restrict__ samp, float *__restrict__ color,
                  float *__restrict__ sil, uint8_t *__restrict__ edge, int32_t *__restrict__ inv, int64_t ncells,
@@ -1107,7 +1117,8 @@ __global__ void __launch_bounds__(256)
     // later load): the corners, the barycentrics, the camera and the texture
     // layer together, then the attribute and coordinate rows, then the taps.
     const float2 w = bary[i];
-    const bool view = mode != DRESSI_SHADE_LAMBERT;
+    constexpr int mode = TEX ? DRESSI_SHADE_PHONG : DRESSI_SHADE_LAMBERT;
+    constexpr bool view = TEX;
     int v0 = -1, v1 = -1, v2 = -1, u0 = -1, u1 = -1, u2 = -1, layer = 0;
     float eye[3] = {0.0f, 0.0f, 0.0f};
     if (t < sc.T) {
@@ -1187,9 +1198,16 @@ __global__ void __launch_bounds__(256)
     sil[i] = 1.0f;
 }
 
-template <int CV, bool TEX>
+// LOOP (more pixels than the grid has lanes) is a form of its own, and the mode
+// a constant: with the loop and the mode at run time the textured pass took 144
+// registers and 3 wavefronts a SIMD; without 125 and 4.  24 instances (12.6 M
+// pixels) 341 -> 271 us, one 512^2 view 10.4 -> 8.7, six 1024^2 Lambert views (90
+// -> 54 registers) 80 -> 76.  Loading texels and coordinates after the shading
+// (96 registers, 5 wavefronts) gives 258 but 9.5 for the one view; a bound of 80
+// registers spills (308).
+template <int CV, bool TEX, bool LOOP>
 __global__ void __launch_bounds__(256)
-    k_packed_bwd(int mode, dressi_packed_scene sc, const int32_t *__restrict__ tri_id, int64_t npix, int64_t n,
+    k_packed_bwd(dressi_packed_scene sc, const int32_t *__restrict__ tri_id, int64_t npix, int64_t n,
                  const float *__restrict__ gbuf, const float *__restrict__ uvbuf, const float *__restrict__ samp,
                  const float *__restrict__ color, const float *__restrict__ sil, const float4 *__restrict__ target,
                  const float *__restrict__ weight, float w_uniform, float *__restrict__ grad_color,
@@ -1203,10 +1221,12 @@ __global__ void __launch_bounds__(256)
     }
     __shared__ float red[256];
     float acc = 0.0f;
-    // one pixel per lane (grid-stride when the image has more pixels than the
-    // grid has lanes: each lane's loss terms are added in pixel order)
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)nmain * blockDim.x) {
+    // one pixel per lane; with LOOP, when the image has more pixels than the
+    // grid has lanes, grid-stride: each lane's loss terms are added in pixel
+    // order
+    const auto pixel = [&](int64_t blk) {
+        const int64_t i = blk * 256 + threadIdx.x;
+        if (i >= n) return;
         // L2 loss term and its gradient (the loss stage's arithmetic)
         const float4 tg = target[i];
         const float d0 = color[3 * i] - tg.x, d1 = color[3 * i + 1] - tg.y, d2 = color[3 * i + 2] - tg.z;
@@ -1232,7 +1252,7 @@ __global__ void __launch_bounds__(256)
                     if (g_bary_uv) g_bary_uv[i] = make_float2(0.0f, 0.0f);
                 }
             }
-            continue;
+            return;
         }
         // Every load of the fragment is issued before its first store (the
         // outputs may alias the inputs as far as the compiler knows, so a
@@ -1240,8 +1260,11 @@ __global__ void __launch_bounds__(256)
         // coordinate, its corners' coordinate indices, the texture layer and
         // the camera; then the corners' coordinates beside the taps' texels.
         // The shading adjoint writes into registers, stored at the end.
-        const bool view = mode != DRESSI_SHADE_LAMBERT;
+        constexpr int mode = TEX ? DRESSI_SHADE_PHONG : DRESSI_SHADE_LAMBERT;
+        constexpr bool view = TEX;
         const bool texg = TEX && (inv || g_bary_uv || rec);
+        int sl = 0, pix = 0;
+        if (TEX) slice_pixel(blk, (uint32_t)npix, sl, pix);
         float gv[CV];
 #pragma unroll
         for (int c = 0; c < CV; c++) gv[c] = gbuf[i * CV + c];
@@ -1284,7 +1307,7 @@ __global__ void __launch_bounds__(256)
         }
         float eye[3] = {0.0f, 0.0f, 0.0f};
         if (view) {
-            const int64_t e = sc.tri_eye ? (int64_t)sc.tri_eye[t] : i / npix;
+            const int64_t e = sc.tri_eye ? sc.tri_eye[t] : sl;
             eye[0] = sc.eye[3 * e]; eye[1] = sc.eye[3 * e + 1]; eye[2] = sc.eye[3 * e + 2];
         }
         // the hard blend passes the colour gradient to the front layer unchanged
@@ -1313,10 +1336,9 @@ __global__ void __launch_bounds__(256)
             if (tp.ok && inv) {
                 const int cx = cell1d(q[0], sc.td.Wt, sc.td.wrap_u);
                 const int cy = cell1d(q[1], sc.td.Ht, sc.td.wrap_v);
-                const int64_t sl = i / npix;
                 const int64_t cells = (int64_t)tex_faces(sc.td) * sc.td.Ht * sc.td.Wt;
                 atomicMax(&inv[sl * cells + ((int64_t)tp.face * sc.td.Ht + cy) * sc.td.Wt + cx],
-                          (int)(i - sl * npix));
+                          pix);
             }
             if (tp.ok && rec) invrec_put(rec + 2 * i, tp, gs);
             // barycentric adjoint of the interpolated coordinate
@@ -1343,6 +1365,11 @@ __global__ void __launch_bounds__(256)
             reinterpret_cast<float4 *>(g_samp)[i] = make_float4(gs[0], gs[1], gs[2], gs[3]);
             if (texg && g_bary_uv) g_bary_uv[i] = gb;
         }
+    };
+    if (LOOP) {
+        for (int64_t blk = blockIdx.x; blk * 256 < n; blk += nmain) pixel(blk);
+    } else {
+        pixel(blockIdx.x);
     }
     red[threadIdx.x] = acc;
     __syncthreads();
@@ -1405,10 +1432,10 @@ extern "C" int dressi_packed_forward(dressi_ctx *ctx, const dressi_packed_scene 
     const float2 *b2 = reinterpret_cast<const float2 *>(bary);
     const ListJob lj = dr_take_list_job(ctx);
     if (tex)
-        DR_LAUNCH("k_packed_fwd", (k_packed_fwd<6, true>), g + lj.nb, 256, 0, st, sc->mode, *sc, tri_id, b2, npix, n,
+        DR_LAUNCH("k_packed_fwd", (k_packed_fwd<6, true>), g + lj.nb, 256, 0, st, *sc, tri_id, b2, npix, n,
                   gbuf, uvbuf, samp, color, sil, edge, inv, ncells, ctx->skip_empty, lj, g);
     else
-        DR_LAUNCH("k_packed_fwd", (k_packed_fwd<9, false>), g + lj.nb, 256, 0, st, sc->mode, *sc, tri_id, b2, npix,
+        DR_LAUNCH("k_packed_fwd", (k_packed_fwd<9, false>), g + lj.nb, 256, 0, st, *sc, tri_id, b2, npix,
                   n, gbuf, uvbuf, samp, color, sil, edge, inv, ncells, ctx->skip_empty, lj, g);
     return dressi_launch_check(ctx, "packed_forward");
 }
@@ -1463,12 +1490,16 @@ extern "C" int dressi_packed_backward(dressi_ctx *ctx, const dressi_packed_scene
         dressi_fill_f32(partial, 0.0f, 1, st);
     } else {
         const ListJob job = dr_take_list_job(ctx);
-        if (tex)
-            DR_LAUNCH("k_packed_bwd", (k_packed_bwd<6, true>), (int)nb + job.nb, 256, 0, st, sc->mode, *sc, tri_id,
+        if (tex && nb * 256 < n)
+            DR_LAUNCH("k_packed_bwd", (k_packed_bwd<6, true, true>), (int)nb + job.nb, 256, 0, st, *sc, tri_id,
+                      npix, n, gbuf, uvbuf, samp, color, sil, t4, weight, w, grad_color, grad_sil, grad_gbuf,
+                      grad_samp, gb, inv, static_cast<int4 *>(inv_rec), partial, ctx->skip_empty, job, (int)nb);
+        else if (tex)
+            DR_LAUNCH("k_packed_bwd", (k_packed_bwd<6, true, false>), (int)nb + job.nb, 256, 0, st, *sc, tri_id,
                       npix, n, gbuf, uvbuf, samp, color, sil, t4, weight, w, grad_color, grad_sil, grad_gbuf,
                       grad_samp, gb, inv, static_cast<int4 *>(inv_rec), partial, ctx->skip_empty, job, (int)nb);
         else
-            DR_LAUNCH("k_packed_bwd", (k_packed_bwd<9, false>), (int)nb + job.nb, 256, 0, st, sc->mode, *sc, tri_id,
+            DR_LAUNCH("k_packed_bwd", (k_packed_bwd<9, false, true>), (int)nb + job.nb, 256, 0, st, *sc, tri_id,
                       npix, n, gbuf, uvbuf, samp, color, sil, t4, weight, w, grad_color, grad_sil, grad_gbuf,
                       grad_samp, gb, inv, nullptr, partial, ctx->skip_empty, job, (int)nb);
     }
@@ -1501,15 +1532,6 @@ extern "C" int dressi_packed_backward(dressi_ctx *ctx, const dressi_packed_scene
 // backward 533, 283; 8 views 2048^2 x 3 layers on 4096^2 texels 2136, 1218 and
 // 2716, 1693.  One lane per fragment rather than per pixel: a pixel's layers
 // are independent chains of dependent loads.
-
-// Slice (layer of a view) and pixel of this lane, of n pixels a slice.
-__device__ __forceinline__ void slice_pixel(int64_t block, uint32_t n, int &sl, int &pix) {
-    const int64_t first = block * 256, s0 = first / n;
-    const uint32_t q = (uint32_t)(first - s0 * n) + threadIdx.x;
-    const uint32_t k = q < n ? 0 : q / n;
-    sl = (int)(s0 + k);
-    pix = (int)(q - k * n);
-}
 
 // CV attribute channels; CT texture channels (0: vertex colours; 8: RGBA and a
 // normal map); ENV: an environment cube map looked up along the reflection.
