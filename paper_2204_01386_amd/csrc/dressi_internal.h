@@ -36,6 +36,10 @@ struct dressi_ctx {
     // whole step only)
     const struct ListJob *list_job = nullptr;
     int n_list_jobs = 0;
+    // a whole step without a texel gather: where the packed backward leaves
+    // its loss partials, and their last sum for the geometry adjoint's launch
+    float *step_partial = nullptr;
+    struct LossJob *step_loss = nullptr;
 };
 
 // ---------------------------------------------------------------------------
@@ -280,6 +284,7 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int &total, int *wsum
 #define SCAN_BS 256
 #define SCAN_PER 4
 #define SCAN_CHUNK (SCAN_BS * SCAN_PER)
+#define SCAN_SMALL 16384        // counts scanned without a pass for the chunks' sums
 #define SCAN_DIRECT_MAX 2048   // chunks the one-pass apply adds up before its own
 #define TT_SHORT 32
 
@@ -296,13 +301,10 @@ __device__ __forceinline__ void scan_reduce_block(const int32_t *in, int64_t n, 
     if (threadIdx.x == 0) block_sums[bid] = total;
 }
 
-// the exclusive scan of one chunk, after adding up the sums of the chunks
-// before it (nb chunks; the last writes the total to out[n])
-__device__ __forceinline__ void scan_apply_direct_block(const int32_t *in, int32_t *out, int64_t n,
-                                                        const int32_t *block_sums, int bid, int nb) {
+// the exclusive scan of chunk bid of nb, given this lane's part of the sum of
+// the counts before it (the last chunk writes the total to out[n])
+__device__ __forceinline__ void scan_chunk(const int32_t *in, int32_t *out, int64_t n, int pre, int bid, int nb) {
     __shared__ int wsum[SCAN_BS / 64];
-    int pre = 0;
-    for (int j = threadIdx.x; j < bid; j += SCAN_BS) pre += block_sums[j];
     int offset;
     block_exclusive_scan<SCAN_BS>(pre, offset, wsum);
     int64_t base = (int64_t)bid * SCAN_CHUNK + (int64_t)threadIdx.x * SCAN_PER;
@@ -321,6 +323,21 @@ __device__ __forceinline__ void scan_apply_direct_block(const int32_t *in, int32
         ex += v[j];
     }
     if (bid == nb - 1 && threadIdx.x == SCAN_BS - 1) out[n] = ex;
+}
+
+// one chunk, from the sums of the chunks before it
+__device__ __forceinline__ void scan_apply_direct_block(const int32_t *in, int32_t *out, int64_t n,
+                                                        const int32_t *block_sums, int bid, int nb) {
+    int pre = 0;
+    for (int j = threadIdx.x; j < bid; j += SCAN_BS) pre += block_sums[j];
+    scan_chunk(in, out, n, pre, bid, nb);
+}
+
+// one chunk, from the counts before it (few chunks: no pass for their sums)
+__device__ __forceinline__ void scan_small_block(const int32_t *in, int32_t *out, int64_t n, int bid, int nb) {
+    int pre = 0;
+    for (int j = threadIdx.x; j < bid * SCAN_CHUNK; j += SCAN_BS) pre += in[j];
+    scan_chunk(in, out, n, pre, bid, nb);
 }
 
 // One tile's records into their (view, triangle) lists, unsorted: each takes
@@ -408,7 +425,7 @@ __device__ __forceinline__ void tt_rank_block(const FragLists &fl, int K, int T,
     }
 }
 
-enum { LJ_NONE = 0, LJ_SCAN_REDUCE, LJ_SCAN_APPLY, LJ_TT_FILL, LJ_TT_RANK };
+enum { LJ_NONE = 0, LJ_SCAN, LJ_SCAN_REDUCE, LJ_SCAN_APPLY, LJ_TT_FILL, LJ_TT_RANK };
 // One job's arguments.  in: the record counts [n] (the scan's input); out:
 // the lists' offsets [n + 1] (the scan's output, which the fill and the
 // ranking read); n: the number of (view, triangle) keys; sums: the chunk
@@ -429,6 +446,7 @@ struct ListJob {
 __device__ __forceinline__ void list_job_block(const ListJob &j, int bid) {
     if (bid >= j.nb) return;
     switch (j.kind) {
+    case LJ_SCAN: scan_small_block(j.in, j.out, j.n, bid, j.nb); break;
     case LJ_SCAN_REDUCE: scan_reduce_block(j.in, j.n, j.sums, bid); break;
     case LJ_SCAN_APPLY: scan_apply_direct_block(j.in, j.out, j.n, j.sums, bid, j.nb); break;
     case LJ_TT_FILL:
@@ -450,6 +468,15 @@ static inline ListJob dr_take_list_job(dressi_ctx *ctx) {
     }
     return j;
 }
+// the loss's last sum that the packed backward left to the step (once)
+static inline LossJob dr_take_step_loss(dressi_ctx *ctx) {
+    LossJob j{};
+    if (ctx->step_loss) j = *ctx->step_loss;
+    ctx->step_loss = nullptr;
+    return j;
+}
+// the last sum as a launch of its own (shade.hip)
+void dr_loss_sum(const LossJob &j, hipStream_t st);
 // runs the jobs not taken yet as launches of their own (raster.hip)
 void dr_flush_list_jobs(dressi_ctx *ctx, hipStream_t st);
 

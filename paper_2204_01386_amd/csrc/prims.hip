@@ -128,7 +128,7 @@ void dressi_exclusive_scan(const int32_t *in, int32_t *out, int64_t n, void *tmp
         dressi_fill_i32(out, 0, 1, s);
         return;
     }
-    if (n <= 16384) {
+    if (n <= SCAN_SMALL) {
         DR_LAUNCH("k_scan_single", (k_scan_single), 1, 1024, 0, s, in, out, n);
         return;
     }

@@ -2305,11 +2305,14 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
                const float4 *__restrict__ pos_clip, Viewports vp, int H, int W, int cull,
                const int32_t *__restrict__ tri_id, const float2 *__restrict__ bary, int ntx, FragLists fl,
                const float *__restrict__ grad_out, const float2 *__restrict__ gb_in, float2 *__restrict__ grad_bary,
-               float *__restrict__ ipart, float *__restrict__ rpart, int skip_empty, ListJob lj, int nmain) {
+               float *__restrict__ ipart, float *__restrict__ rpart, int skip_empty, ListJob lj, LossJob loss,
+               int nmain) {
     extern __shared__ float vals[];   // [256][ib_stride(CC)] interpolation rows, then [256][9]
-    // workgroups past the tiles run a list-building job of the step
+    // workgroups past the tiles run a list-building job of the step, and the
+    // last one its loss's sum
     if ((int)blockIdx.x >= nmain) {
-        list_job_block(lj, (int)blockIdx.x - nmain);
+        if ((int)blockIdx.x - nmain >= lj.nb) loss_sum_block(loss, vals);
+        else list_job_block(lj, (int)blockIdx.x - nmain);
         return;
     }
     constexpr int S = (CC + 2) | 1;
@@ -2469,12 +2472,14 @@ extern "C" int dressi_geometry_bwd(dressi_ctx *ctx, const float *pos, const floa
     if (nt > 0 && (Cv == 9 || al8)) {
         const size_t lds = sizeof(float) * DRESSI_TILE_PIX * (((Cv + 2) | 1) + 9);
         const ListJob lj = dr_take_list_job(ctx);
+        const LossJob loss = dr_take_step_loss(ctx);
+        const int ng = nt + lj.nb + (loss.loss ? 1 : 0);
         if (Cv == 6)
-            DR_LAUNCH("k_geo_tile", (k_geo_tile<6>), nt + lj.nb, DRESSI_TILE_PIX, lds, st, vattr, V, tris, T, pc4, vp,
-                      H, W, cull, tri_id, b2, ntx, fl, grad_gbuf, gbi, gbo, ipart, rpart, ctx->skip_empty, lj, nt);
+            DR_LAUNCH("k_geo_tile", (k_geo_tile<6>), ng, DRESSI_TILE_PIX, lds, st, vattr, V, tris, T, pc4, vp, H, W,
+                      cull, tri_id, b2, ntx, fl, grad_gbuf, gbi, gbo, ipart, rpart, ctx->skip_empty, lj, loss, nt);
         else
-            DR_LAUNCH("k_geo_tile", (k_geo_tile<9>), nt + lj.nb, DRESSI_TILE_PIX, lds, st, vattr, V, tris, T, pc4, vp,
-                      H, W, cull, tri_id, b2, ntx, fl, grad_gbuf, gbi, gbo, ipart, rpart, ctx->skip_empty, lj, nt);
+            DR_LAUNCH("k_geo_tile", (k_geo_tile<9>), ng, DRESSI_TILE_PIX, lds, st, vattr, V, tris, T, pc4, vp, H, W,
+                      cull, tri_id, b2, ntx, fl, grad_gbuf, gbi, gbo, ipart, rpart, ctx->skip_empty, lj, loss, nt);
     } else {
         dr_interp_bwd_tiles(vattr, 1, V, Cv, tris, T, tri_id, bary, 1, 1, H, W, fl, grad_gbuf, grad_bary_in,
                             grad_bary, ipart, ctx->skip_empty, st);
@@ -2542,7 +2547,9 @@ extern "C" size_t dressi_limits_scratch_bytes(const dressi_limits *l) {
         size_t og[4];
         geometry_scratch(l->H, l->W, l->V, 9, cg, og);
         const size_t off = (std::max(cg.off, dr_need_shade(*l)) + 255) / 256 * 256;
-        need = std::max(need, off + dressi_fragindex_tmp_bytes(1, 1, l->H, l->W, l->T));
+        // (the loss partials of dr_need_shade once more, behind it)
+        need = std::max(need, off + (dressi_fragindex_tmp_bytes(1, 1, l->H, l->W, l->T) + 255) / 256 * 256 +
+                                  sizeof(float) * (((size_t)l->H * l->W + 255) / 256 + 64));
     }
     return need;
 }
@@ -2612,30 +2619,56 @@ extern "C" int dressi_packed_step(dressi_ctx *ctx, const dressi_packed_scene *sc
         return dressi_fail(ctx, DRESSI_EINVAL, "packed_step: the textured step needs inv, inv_rec and grad_tex");
     const int V = sc->V, T = sc->T, H = b->H, W = b->W, Cv = sc->Cv;
     hipStream_t st = (hipStream_t)stream;
-    // With the binless rasterizer and a two-pass scan of the record counts,
-    // the triangle -> tile lists are built by four jobs run in the launches
-    // of the packed forward (the counts' chunk sums), the packed backward
-    // (the scan), the texel gather (the fill) and the per-tile geometry
-    // adjoint (the ranking); jobs without such a launch run on their own
-    // before the per-vertex adjoint.  Otherwise the calls in sequence.
+    // With the binless rasterizer the triangle -> tile lists are built by jobs
+    // run in the launches of the packed forward, the packed backward, the
+    // texel gather (textured) and the per-tile geometry adjoint, one each:
+    // the scan of the record counts (beyond SCAN_SMALL the chunks' sums, then
+    // the scan), the fill, the ranking; jobs without such a launch run on
+    // their own before the per-vertex adjoint.  The loss's last sum, which
+    // rides in the gather, runs beside the geometry adjoint without one.  A
+    // Lambert scene of 1,280 triangles at 128^2 took 11 launches and 69.3 us
+    // when the small scan had a launch of its own, 7 and 58.1 with the jobs.
+    // Otherwise the calls in sequence.
     const int64_t nchunk = ((int64_t)T + SCAN_CHUNK - 1) / SCAN_CHUNK;
-    const bool jobs = ctx->hard_raster == 3 && b->adj && V > 0 && T > 16384 && nchunk <= SCAN_DIRECT_MAX &&
-                      b->pos_clip && b->tri_id && b->bary && b->index && b->pos && b->mvp && b->vattr &&
-                      H > 0 && W > 0 && H <= 32767 && W <= 32767 && T < 0x7fffffff;
+    const bool small = T <= SCAN_SMALL;
+    bool jobs = ctx->hard_raster == 3 && b->adj && V > 0 && T > 0 && nchunk <= SCAN_DIRECT_MAX && b->pos_clip &&
+                b->tri_id && b->bary && b->index && b->pos && b->mvp && b->vattr && H > 0 && W > 0 && H <= 32767 &&
+                W <= 32767 && T < 0x7fffffff;
+    // scratch: what the packed backward and the geometry adjoints take (from
+    // the arena's start), then the fragment index's temporary, which lives
+    // until the last job, and the loss partials
+    size_t off = 0, need = 0, o_loss = 0;
+    if (jobs) {
+        Carver cg;
+        size_t og[4];
+        geometry_scratch(H, W, V, Cv, cg, og);
+        off = (std::max(cg.off, dr_packed_bwd_scratch(sc, 1, H, W, tex)) + 255) / 256 * 256;
+        need = off + dressi_fragindex_tmp_bytes(1, 1, H, W, T);
+        o_loss = (need + 255) / 256 * 256;
+    }
+    bool later = jobs && !tex;
+    if (jobs) {
+        // a capture keeps to the arena it has: the calls in sequence need less
+        const size_t all = o_loss + dr_packed_bwd_scratch(sc, 1, H, W, false);
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if ((later ? all : need) > ctx->scratch_bytes) {
+            const hipError_t e = hipStreamIsCapturing(st, &cs);
+            if (e != hipSuccess) return dressi_hip_check(ctx, e, "hipStreamIsCapturing");
+        }
+        if (cs != hipStreamCaptureStatusNone) {
+            later = false;
+            if (small && need > ctx->scratch_bytes) jobs = false;
+        }
+        if (later) need = all;
+    }
     int rc;
     ListJob j[4];   // taken by the calls below (so it lives until the function's end)
+    LossJob step_loss{};
     if (!jobs) {
         rc = dressi_geometry_fwd(ctx, b->pos, sc->tris, V, T, b->extra, b->adj, b->mvp, 1, b->vattr, b->pos_clip, H,
                                  W, 0, b->tri_id, b->bary, b->index, stream);
     } else {
-        // scratch: what the packed backward and the geometry adjoints take
-        // (from the arena's start), then the fragment index's temporary, which
-        // lives until the last job
-        Carver cg;
-        size_t og[4];
-        geometry_scratch(H, W, V, Cv, cg, og);
-        const size_t off = (std::max(cg.off, dr_packed_bwd_scratch(sc, 1, H, W, tex)) + 255) / 256 * 256;
-        if ((rc = dressi_scratch(ctx, off + dressi_fragindex_tmp_bytes(1, 1, H, W, T), st))) return rc;
+        if ((rc = dressi_scratch(ctx, need, st))) return rc;
         void *tmp = static_cast<char *>(ctx->scratch) + off;
         const VertexStageArgs vs{b->pos, b->extra, b->mvp, b->adj, b->extra ? 9 : 6, b->vattr};
         rc = direct_indexed(ctx, b->pos_clip, sc->tris, 1, V, T, H, W, 0, b->tri_id, b->bary, b->index, st, &vs, tmp,
@@ -2668,12 +2701,21 @@ extern "C" int dressi_packed_step(dressi_ctx *ctx, const dressi_packed_scene *sc
             j[k].sbuf = sbuf;
             j[k].longk = longk;
         }
-        j[0].kind = LJ_SCAN_REDUCE, j[0].nb = (int)nchunk;
-        j[1].kind = LJ_SCAN_APPLY, j[1].nb = (int)nchunk;
-        j[2].kind = LJ_TT_FILL, j[2].nb = nt;
-        j[3].kind = LJ_TT_RANK, j[3].nb = (int)std::min<int64_t>((ne + 255) / 256, 4096);
+        int nj = 0;
+        if (small) {
+            j[nj].kind = LJ_SCAN, j[nj++].nb = (int)nchunk;
+        } else {
+            j[nj].kind = LJ_SCAN_REDUCE, j[nj++].nb = (int)nchunk;
+            j[nj].kind = LJ_SCAN_APPLY, j[nj++].nb = (int)nchunk;
+        }
+        j[nj].kind = LJ_TT_FILL, j[nj++].nb = nt;
+        j[nj].kind = LJ_TT_RANK, j[nj++].nb = (int)std::min<int64_t>((ne + 255) / 256, 4096);
         ctx->list_job = j;
-        ctx->n_list_jobs = 4;
+        ctx->n_list_jobs = nj;
+        if (later) {
+            ctx->step_partial = at<float>(ctx->scratch, o_loss);
+            ctx->step_loss = &step_loss;
+        }
     }
     if (!rc)
         rc = dressi_packed_forward(ctx, sc, b->tri_id, b->bary, 1, H, W, b->gbuf, b->uvbuf, b->samp, b->color,
@@ -2692,5 +2734,8 @@ extern "C" int dressi_packed_step(dressi_ctx *ctx, const dressi_packed_scene *sc
     if (ctx->n_list_jobs > 0) dr_flush_list_jobs(ctx, st);
     ctx->list_job = nullptr;
     ctx->n_list_jobs = 0;
+    const LossJob left = dr_take_step_loss(ctx);
+    if (left.loss) dr_loss_sum(left, st);
+    ctx->step_partial = nullptr;
     return rc;
 }

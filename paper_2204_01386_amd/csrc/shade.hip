@@ -1382,6 +1382,10 @@ __global__ void __launch_bounds__(256)
     if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
+void dr_loss_sum(const LossJob &j, hipStream_t st) {
+    DR_LAUNCH("k_loss_sum", (k_loss_sum), 1, LOSS_BS, 0, st, j.partial, j.nb, j.scale, j.loss);
+}
+
 static bool al16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 #define PACKED_MAX_BLOCKS 65536   // loss partials of the packed backward, at most
 
@@ -1482,7 +1486,10 @@ extern "C" int dressi_packed_backward(dressi_ctx *ctx, const dressi_packed_scene
     const int64_t cells = tex ? (int64_t)tex_faces(sc->td) * sc->td.Ht * sc->td.Wt : 0;
     const size_t o_g = grad_tex ? c.take(dressi_invuv_part_bytes(cells, 4, B)) : 0;
     if ((rc = dressi_scratch(ctx, c.off, st))) return rc;
-    float *partial = at<float>(ctx->scratch, o_p);
+    // in a whole step without a texel gather the sum of the partials runs
+    // beside the geometry adjoint, whose scratch they are kept clear of
+    const bool later = ctx->step_partial && !grad_tex;
+    float *partial = later ? ctx->step_partial : at<float>(ctx->scratch, o_p);
     const float w = 1.0f / (4.0f * (float)(n > 0 ? n : 1));
     const float4 *t4 = reinterpret_cast<const float4 *>(target);
     float2 *gb = reinterpret_cast<float2 *>(grad_bary_uv);
@@ -1508,8 +1515,10 @@ extern "C" int dressi_packed_backward(dressi_ctx *ctx, const dressi_packed_scene
         // the texel gather, with the loss's last sum in an extra workgroup of its launch
         dr_gather_invrec(sc->td, B, npix, inv, static_cast<const int4 *>(inv_rec), at<float>(ctx->scratch, o_g),
                          grad_tex, st, ctx->iv_rows, lj, dr_take_list_job(ctx));
+    } else if (later) {
+        *ctx->step_loss = lj;
     } else {
-        DR_LAUNCH("k_loss_sum", (k_loss_sum), 1, LOSS_BS, 0, st, lj.partial, lj.nb, lj.scale, lj.loss);
+        dr_loss_sum(lj, st);
     }
     return dressi_launch_check(ctx, "packed_backward");
 }
