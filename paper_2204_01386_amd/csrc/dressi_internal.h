@@ -735,13 +735,18 @@ __device__ __forceinline__ float dr_depth(const TriSetup &s, const TE *E) {
 // The binless hard rasterizer's merge of one set-up triangle t (K = 1): each
 // covered pixel centre of its box with depth in (0, 1) takes the 64-bit
 // maximum of ~(depth bits << 32 | t) in zb (one view, H x W), so that the
-// nearest fragment, then the lowest id, wins.
-__device__ __forceinline__ void dr_direct_merge(const TriSetup &s, int t, int W, unsigned long long *zb) {
+// nearest fragment, then the lowest id, wins.  A triangle's 2^lg lanes take its
+// box's pixels in turn (lane: this one of them).
+__device__ __forceinline__ void dr_direct_merge(const TriSetup &s, int t, int W, unsigned long long *zb, int lane,
+                                                int lg) {
     const int x0 = s.box0 & 0xffff, x1 = s.box0 >> 16, y0 = s.box1 & 0xffff, y1 = s.box1 >> 16;
-    for (int y = y0; y <= y1; y++) {
-        const int py = DRESSI_SUBPIX * y + DRESSI_SUBPIX / 2;
-        for (int x = x0; x <= x1; x++) {
-            const int px = DRESSI_SUBPIX * x + DRESSI_SUBPIX / 2;
+    const int wd = x1 - x0 + 1;
+    if (wd <= 0) return;
+    int x = x0 + lane, y = y0;
+    while (x > x1) x -= wd, y++;
+    for (; y <= y1;) {
+        do {
+            const int px = DRESSI_SUBPIX * x + DRESSI_SUBPIX / 2, py = DRESSI_SUBPIX * y + DRESSI_SUBPIX / 2;
             double E[3];
             bool in = true;
 #pragma unroll
@@ -750,11 +755,37 @@ __device__ __forceinline__ void dr_direct_merge(const TriSetup &s, int t, int W,
                 bool own = (s.meta >> (1 + i)) & 1;
                 in = in && (E[i] > 0 || (E[i] == 0 && own));
             }
-            if (!in) continue;
+            if (!in) break;
             const float z = dr_depth(s, E);
-            if (!(z > 0.0f && z < 1.0f)) continue;
+            if (!(z > 0.0f && z < 1.0f)) break;
             const unsigned long long v = ((unsigned long long)__float_as_uint(0.5f * z) << 32) | (unsigned)t;
             atomicMax(&zb[(int64_t)y * W + x], ~v);
-        }
+        } while (false);
+        x += 1 << lg;
+        while (x > x1) x -= wd, y++;
     }
+}
+
+// log2 of the lanes that merge a triangle, for ntri triangles over npx pixels:
+// one for each pixel of the mean triangle's share (its box is larger, its
+// projection half of that again for a closed mesh), at most 64, and twice as
+// many while that leaves less than 131,072 lanes in all.  With one lane a
+// triangle a wavefront waits for its largest box and a small mesh fills a
+// fraction of the card; with too many the lanes repeat the setup for nothing.
+// The merge, vertex stage included (us), by 1, 2, 4, 8, 16, 32, 64 lanes:
+//     1,280 triangles at  128^2      23   13    8.2  5.5  4.5  5.3  6.8
+//     5,120               512^2      77   40   21   12    7.8  6.3  9.0
+//    20,480               256^2      8.3  5.6  4.7  4.9  6.6  12   23
+//    20,480              1024^2      81   42   24   15   12   13   21
+//    81,920               512^2      11   8.4  9.0  12   19   35   72
+//    81,920              1024^2      36   24   18   17   20   33   63
+//    51,076 in six views 1024^2     190  125   93   76   73
+//    24 instances, 768,000 in all  1198  632  339  204  168
+// With the resolve and its fragment index the six views take 131 us, the binned
+// rasterizers with theirs 232.
+static inline int dr_direct_lanes(int64_t ntri, int64_t npx) {
+    int lg = 0;
+    while (lg < 6 && (ntri << (lg + 1)) <= npx) lg++;
+    if (lg > 0 && lg < 6 && (ntri << (lg + 1)) < 131072) lg++;
+    return lg;
 }

@@ -1230,16 +1230,16 @@ __global__ void __launch_bounds__(256)
     }
 }
 
-// Hard single-layer rasterization without bins (strategy 3, K = 1): one lane
-// per (view, triangle) sets the triangle up as k_setup_bin does and merges
+// Hard single-layer rasterization without bins (strategy 3, K = 1): the lanes
+// of a (view, triangle) (dr_direct_lanes) set it up as k_setup_bin does and merge
 // its key (depth bits << 32 | id, as k_raster) into every covered pixel of its
 // box with a 64-bit global atomicMax of the key's complement, on a per-pixel
 // array kept at zero between calls (zero: no fragment); a second kernel
 // resolves each pixel from the surviving key, recomputing the winner's setup,
 // and sets the entry back to zero.  The smallest key and the smallest id at
 // it, whatever the order of the atomics: the layer the other strategies
-// select.  A lane's work is its triangle's box, so this suits small
-// triangles; the autotuner times it against the others.
+// select.  The work is the triangles' boxes, whatever hides them; the autotuner
+// times it against the others.
 __device__ __forceinline__ bool direct_setup(const float4 *__restrict__ pos_clip, const int32_t *__restrict__ tris,
                                              const Viewports &vp, int b, int V, int t, int H, int W, int cull,
                                              TriSetup &s) {
@@ -1252,13 +1252,14 @@ __device__ __forceinline__ bool direct_setup(const float4 *__restrict__ pos_clip
 }
 
 __global__ void k_raster_direct(const float4 *__restrict__ pos_clip, const int32_t *__restrict__ tris, Viewports vp,
-                                int B, int V, int T, int H, int W, int cull, unsigned long long *__restrict__ zbuf) {
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                                int B, int V, int T, int H, int W, int cull, unsigned long long *__restrict__ zbuf,
+                                int lg) {
+    const int64_t lid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, gid = lid >> lg;
     if (gid >= (int64_t)B * T) return;
     const int b = (int)(gid / T), t = (int)(gid - (int64_t)b * T);
     TriSetup s;
     if (!direct_setup(pos_clip, tris, vp, b, V, t, H, W, cull, s)) return;
-    dr_direct_merge(s, t, W, zbuf + (int64_t)b * H * W);
+    dr_direct_merge(s, t, W, zbuf + (int64_t)b * H * W, (int)(lid & ((1 << lg) - 1)), lg);
 }
 
 __global__ void k_raster_direct_resolve(const float4 *__restrict__ pos_clip, const int32_t *__restrict__ tris,
@@ -1380,9 +1381,10 @@ static int rasterize_impl(dressi_ctx *ctx, const float *pos_clip, const int32_t 
         unsigned long long *zbuf = reinterpret_cast<unsigned long long *>(ctx->counters);
         const float4 *pc4 = reinterpret_cast<const float4 *>(pos_clip);
         const int64_t ntri = (int64_t)B * T;
+        const int lg = dr_direct_lanes(ntri, (int64_t)B * H * W);
         if (ntri > 0)
-            DR_LAUNCH("k_raster_direct", (k_raster_direct), (int)((ntri + 255) / 256), 256, 0, st, pc4, tris, vp, B,
-                      V, T, H, W, cull, zbuf);
+            DR_LAUNCH("k_raster_direct", (k_raster_direct), (int)(((ntri << lg) + 255) / 256), 256, 0, st, pc4, tris,
+                      vp, B, V, T, H, W, cull, zbuf, lg);
         DR_LAUNCH("k_raster_direct_resolve", (k_raster_direct_resolve), (int)((npx + 255) / 256), 256, 0, st, pc4,
                   tris, vp, B, V, T, H, W, cull, zbuf, tri_id, reinterpret_cast<float2 *>(bary));
         return dressi_launch_check(ctx, "rasterize");
@@ -1912,9 +1914,11 @@ static int direct_indexed(dressi_ctx *ctx, const float *pos_clip, const int32_t 
     if (vs)
         dr_vertex_raster_direct(vs->pos, tris, vs->extra, vs->adj, V, vs->C, vs->vattr, vs->mvp, B,
                                 const_cast<float *>(pos_clip), T, H, W, cull, zbuf, st);
-    else if (ntri > 0)
-        DR_LAUNCH("k_raster_direct", (k_raster_direct), (int)((ntri + 255) / 256), 256, 0, st, pc4, tris, vp, B, V,
-                  T, H, W, cull, zbuf);
+    else if (ntri > 0) {
+        const int lg = dr_direct_lanes(ntri, (int64_t)B * H * W);
+        DR_LAUNCH("k_raster_direct", (k_raster_direct), (int)(((ntri << lg) + 255) / 256), 256, 0, st, pc4, tris, vp,
+                  B, V, T, H, W, cull, zbuf, lg);
+    }
     FragLists fl;
     TriTiles tt;
     dressi_fragindex_view(index, B, 1, H, W, T, fl, tt);

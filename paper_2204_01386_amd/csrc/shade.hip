@@ -231,13 +231,13 @@ __global__ void __launch_bounds__(256)
     k_vertex_raster_direct(const float *__restrict__ pos, const int32_t *__restrict__ tris,
                            const float *__restrict__ extra, Adjacency adj, int V, int C, float *__restrict__ out,
                            const float *__restrict__ mvp, int B, float4 *__restrict__ pos_clip, int T, int H, int W,
-                           int cull, unsigned long long *__restrict__ zbuf, int nrb) {
+                           int cull, unsigned long long *__restrict__ zbuf, int nrb, int lg) {
     if ((int)blockIdx.x >= nrb) {
         vertex_stage((int64_t)(blockIdx.x - nrb) * blockDim.x + threadIdx.x, pos, tris, extra, adj, V, C, out, mvp,
                      nullptr, B, pos_clip);
         return;
     }
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t lid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, gid = lid >> lg;
     if (gid >= (int64_t)B * T) return;
     const int b = (int)(gid / T), t = (int)(gid - (int64_t)b * T);
     const int32_t *tv = tris + 3 * (int64_t)t;
@@ -257,18 +257,19 @@ __global__ void __launch_bounds__(256)
     for (int i = 0; i < 3; i++) p[i] = clip_of(M, q[3 * i], q[3 * i + 1], q[3 * i + 2]);
     const TriSetup s = dr_setup_pts(p, H, W, 0, 0, cull, 0);
     if (!(s.meta & 1)) return;
-    dr_direct_merge(s, t, W, zbuf + (int64_t)b * H * W);
+    dr_direct_merge(s, t, W, zbuf + (int64_t)b * H * W, (int)(lid & ((1 << lg) - 1)), lg);
 }
 
 void dr_vertex_raster_direct(const float *pos, const int32_t *tris, const float *extra, const int32_t *adj, int V,
                              int C, float *vattr, const float *mvp, int B, float *pos_clip, int T, int H, int W,
                              int cull, unsigned long long *zbuf, hipStream_t st) {
-    const int nrb = (int)(((int64_t)B * T + 255) / 256);
+    const int lg = dr_direct_lanes((int64_t)B * T, (int64_t)B * H * W);
+    const int nrb = (int)((((int64_t)B * T << lg) + 255) / 256);
     const int nvb = (int)(((int64_t)V * VA_LANES + 255) / 256);
     if (nrb + nvb == 0) return;
     DR_LAUNCH("k_vertex_raster_direct", (k_vertex_raster_direct), nrb + nvb, 256, 0, st, pos, tris, extra,
               adjacency_view(adj, V), V, C, vattr, mvp, B, reinterpret_cast<float4 *>(pos_clip), T, H, W, cull, zbuf,
-              nrb);
+              nrb, lg);
 }
 
 // gradient w.r.t. the un-normalised vertex normal sum
