@@ -824,6 +824,37 @@ int dressi_shade_pbs_bwd(dressi_ctx *ctx, const dressi_pbs_in *in, const float *
                          const float *grad_dir_n, const float *grad_dir_r,
                          const dressi_pbs_grad *grad, void *stream);
 
+/* The packed PBS pass: the same values as dressi_texture of the albedo (tex,
+ * td: 2-D RGBA, sampled at uv [B,K,H,W,2]), dressi_shade_pbs's directions and
+ * level masks, dressi_texture of the irradiance and the prefiltered maps
+ * (irr_map [6,Si,Si,3], pref_map [L,6,Sp,Sp,3]) and dressi_shade_pbs's colour,
+ * over tri_id [B,K,H,W].  in: normal, pos, material, lut and levels. */
+typedef struct {
+    dressi_pbs_in in;
+    const float *tex;
+    dressi_tex_desc td;
+    const float *uv;
+    const float *irr_map, *pref_map;
+    int Si, Sp;
+} dressi_pbs_layers;
+
+/* Workspace (16-byte aligned) of a pass over S = B K slices, kept from the
+ * forward to its backward. */
+size_t dressi_pbs_layers_bytes(int Si, int Sp, int S, int H, int W);
+/* samp [N,4] (16-byte aligned), irr_s [N,3], pref_s [2,N,3] (the two levels in
+ * use), color [N,3], N = B K H W; empty slots as DRESSI_TUNE_EMPTY_SLOTS says. */
+int dressi_pbs_layers_forward(dressi_ctx *ctx, const dressi_pbs_layers *L, const float *eye,
+                              const int32_t *tri_id, int B, int K, int H, int W, float *samp, float *irr_s,
+                              float *pref_s, float *color, void *ws, void *stream);
+/* From grad_color [N,3]: grad_samp [N,4] (the fourth channel is not written),
+ * grad_irr and grad_pref (the maps' gradients, as dressi_texture_bwd of
+ * dressi_shade_pbs_bwd's sample gradients gives them) and grad_material [2]. */
+int dressi_pbs_layers_backward(dressi_ctx *ctx, const dressi_pbs_layers *L, const float *eye,
+                               const int32_t *tri_id, int B, int K, int H, int W, const float *samp,
+                               const float *irr_s, const float *pref_s, const float *grad_color,
+                               float *grad_samp, void *ws, float *grad_irr, float *grad_pref,
+                               float *grad_material, void *stream);
+
 #ifdef __cplusplus
 }
 #endif

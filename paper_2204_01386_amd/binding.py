@@ -94,6 +94,12 @@ class PbsIn(C.Structure):
                 ("material", _vp), ("lut", _vp), ("lut_n", _i), ("levels", _i)]
 
 
+class PbsLayers(C.Structure):
+    """dressi_pbs_layers: the inputs of the packed PBS pass."""
+    _fields_ = [("inp", PbsIn), ("tex", _vp), ("td", TexDesc), ("uv", _vp), ("irr_map", _vp), ("pref_map", _vp),
+                ("Si", _i), ("Sp", _i)]
+
+
 class PbsGrad(C.Structure):
     _fields_ = [("normal", _vp), ("normal_stride", _i), ("pos", _vp), ("pos_stride", _i),
                 ("albedo", _vp), ("albedo_stride", _i), ("irr", _vp), ("pref", _vp), ("material", _vp)]
@@ -118,6 +124,9 @@ _SIG = {
     "dressi_brdf_lut": [_vp, _i, _i, _vp, _vp],
     "dressi_shade_pbs": [_vp, C.POINTER(PbsIn), _vp, _vp, _i, _i64, _vp, _vp, _vp, _vp, _vp],
     "dressi_shade_pbs_bwd": [_vp, C.POINTER(PbsIn), _vp, _vp, _i, _i64, _vp, _vp, _vp, C.POINTER(PbsGrad), _vp],
+    "dressi_pbs_layers_forward": [_vp, _vp, _vp, _vp, _i, _i, _i, _i, _vp, _vp, _vp, _vp, _vp, _vp],
+    "dressi_pbs_layers_backward": [_vp, _vp, _vp, _vp, _i, _i, _i, _i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp,
+                                   _vp],
     "dressi_adam": [_vp, _vp, _vp, _vp, _vp, _i64, _f, _f, _f, _f, _vp, _vp],
     "dressi_laplacian_reg": [_vp, _vp, _vp, _i, _i, _vp, _f, _f, _vp, _vp, _vp, _vp, _vp],
     "dressi_invuv_build": [_vp, C.POINTER(TexDesc), _vp, _vp, _i, _i, _i, _vp, _vp],
@@ -190,7 +199,9 @@ _lib.dressi_limits_scratch_bytes.argtypes = [C.POINTER(Limits)]
 _lib.dressi_limits_scratch_bytes.restype = C.c_size_t
 _lib.dressi_reserve_limits.argtypes = [_vp, C.POINTER(Limits)]
 _lib.dressi_reserve_limits.restype = C.c_int
-EXPORTED = sorted(EXPORTED + ["dressi_limits_scratch_bytes", "dressi_reserve_limits"])
+EXPORTED = sorted(EXPORTED + ["dressi_limits_scratch_bytes", "dressi_reserve_limits", "dressi_pbs_layers_bytes"])
+_lib.dressi_pbs_layers_bytes.argtypes = [_i, _i, _i, _i, _i]
+_lib.dressi_pbs_layers_bytes.restype = C.c_size_t
 
 
 class DressiError(RuntimeError):

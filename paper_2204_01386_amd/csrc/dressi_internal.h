@@ -162,6 +162,10 @@ int dr_check_grad_tex(dressi_ctx *ctx, const dressi_tex_desc *td, const int32_t 
 void dr_gather_invuv(const dressi_tex_desc &td, const float *coord, const int32_t *tri_id, int S, int64_t npix,
                      const int32_t *inv, const float *grad_out, float *part, float *grad_tex, hipStream_t st,
                      int rows);
+// The gather's partial sums [nsplit][cells][Ct] (nsplit returned; 1 for large
+// textures: the texel gradient itself), to be added in order.
+int dr_gather_parts(const dressi_tex_desc &td, const float *coord, const int32_t *tri_id, int S, int64_t npix,
+                    const int32_t *inv, const float *grad_out, float *part, hipStream_t st, int rows);
 void dr_gather_invrec(const dressi_tex_desc &td, int S, int64_t npix, const int32_t *inv, const int4 *rec,
                       float *part, float *grad_tex, hipStream_t st, int rows, LossJob lj, const ListJob &job);
 
@@ -245,6 +249,16 @@ __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nb) {
     return x * q + (x < r ? x : r) + (b >> 3);
 }
 __device__ __forceinline__ int64_t xcd_block() { return xcd_block(blockIdx.x, gridDim.x); }
+
+// Slice (view, or layer of one) and pixel of this lane of a 256-lane block, of n
+// pixels a slice: a lane divides, in 32 bits, only past a slice's end.
+__device__ __forceinline__ void slice_pixel(int64_t block, uint32_t n, int &sl, int &pix) {
+    const int64_t first = block * 256, s0 = first / n;
+    const uint32_t q = (uint32_t)(first - s0 * n) + threadIdx.x;
+    const uint32_t k = q < n ? 0 : q / n;
+    sl = (int)(s0 + k);
+    pix = (int)(q - k * n);
+}
 
 // ---------------------------------------------------------------------------
 // The workgroup bodies of the kernels that turn the per-tile records of a

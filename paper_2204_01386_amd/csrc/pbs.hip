@@ -8,7 +8,7 @@
 // sum, so the environment gradient is exact and needs no atomics.  Shading follows the
 // split sum per fragment; its backward is analytic, with the material's
 // scalar gradients reduced in a fixed order.
-#include "dressi_internal.h"
+#include "texcore.h"
 
 #include <algorithm>
 
@@ -370,6 +370,16 @@ struct PbsFrag {
     bool rin;   // roughness inside [0, 1]: the level weight depends on it
 };
 
+// The lower level of the pair that a roughness samples, and the upper one's
+// weight: the roughness clamped to [0, 1] (also keeping the level index in
+// range for any roughness, NaN included)
+__device__ __forceinline__ int pbs_level(double rough, int levels, double &f) {
+    const double x = fmin(fmax(rough, 0.0), 1.0) * (levels - 1);
+    const int l0 = min((int)floor(x), levels - 2);
+    f = x - l0;
+    return l0;
+}
+
 __device__ __forceinline__ PbsFrag pbs_geometry(const dressi_pbs_in &in, const float *eye, int64_t i,
                                                 double rough) {
     PbsFrag q;
@@ -382,11 +392,7 @@ __device__ __forceinline__ PbsFrag pbs_geometry(const dressi_pbs_in &in, const f
     q.ndv = q.nn.x * q.v.x + q.nn.y * q.v.y + q.nn.z * q.v.z;
     q.c = fmax(q.ndv, 1e-4);
     q.R = make_double3(2.0 * q.ndv * q.nn.x - q.v.x, 2.0 * q.ndv * q.nn.y - q.v.y, 2.0 * q.ndv * q.nn.z - q.v.z);
-    // the level pair follows the roughness clamped to [0, 1] (also keeping
-    // the level index in range for any roughness, NaN included)
-    const double x = fmin(fmax(rough, 0.0), 1.0) * (in.levels - 1);
-    q.l0 = min((int)floor(x), in.levels - 2);
-    q.f = x - q.l0;
+    q.l0 = pbs_level(rough, in.levels, q.f);
     q.rin = rough >= 0.0 && rough <= 1.0;
     return q;
 }
@@ -446,6 +452,98 @@ __global__ void k_pbs_dirs(dressi_pbs_in in, const float *__restrict__ eye, cons
             level_tid[(int64_t)l * n + i] = (t >= 0 && (l == l0 || l == l0 + 1)) ? t : -1;
 }
 
+// x^5 and x^4 by squares
+__device__ __forceinline__ double pow4(double x) { return (x * x) * (x * x); }
+__device__ __forceinline__ double pow5(double x) { return pow4(x) * x; }
+
+// a fragment's colour from its albedo, its irradiance sample and its samples
+// of the level pair
+__device__ __forceinline__ void pbs_color(const dressi_pbs_in &in, const PbsFrag &q, double m, double r,
+                                          const float *a, const float *ir, const float *p0, const float *p1,
+                                          float *o) {
+    const LutS ab = lut_sample(in.lut, in.lut_n, q.c, r);
+    const double w5 = pow5(1.0 - q.c);
+#pragma unroll
+    for (int ch = 0; ch < 3; ch++) {
+        const double F0 = 0.04 * (1.0 - m) + a[ch] * m;
+        const double F = F0 + (fmax(1.0 - r, F0) - F0) * w5;
+        const double P = (1.0 - q.f) * p0[ch] + q.f * p1[ch];
+        const double C = (1.0 - F) * (1.0 - m) * a[ch] * ir[ch] + P * (F0 * ab.A + ab.B);
+        o[ch] = (float)(C / (1.0 + C));
+    }
+}
+
+// its adjoint: the gradients of the albedo ga, the irradiance sample girr and
+// the level pair's samples gp0, gp1 (stored as they are rounded), of n.v
+// (returned) and, added, of the material
+__device__ __forceinline__ double pbs_color_bwd(const dressi_pbs_in &in, const PbsFrag &q, double m, double r,
+                                                const float *a, const float *ir, const float *p0, const float *p1,
+                                                const float *go, float *oa, float *oirr, float *op0, float *op1,
+                                                double &gm, double &gr) {
+    const LutS ab = lut_sample(in.lut, in.lut_n, q.c, r);
+    const double w5 = pow5(1.0 - q.c);
+    double gA = 0.0, gB = 0.0, gw5 = 0.0, gf = 0.0;
+#pragma unroll
+    for (int ch = 0; ch < 3; ch++) {
+        const double ac = a[ch];
+        const double F0 = 0.04 * (1.0 - m) + ac * m;
+        const bool fr_f0 = F0 > 1.0 - r;     // max(1 - r, F0) takes F0
+        const double Fr = fr_f0 ? F0 : 1.0 - r;
+        const double F = F0 + (Fr - F0) * w5;
+        const double P = (1.0 - q.f) * p0[ch] + q.f * p1[ch];
+        const double kd = (1.0 - F) * (1.0 - m);
+        const double C = kd * ac * ir[ch] + P * (F0 * ab.A + ab.B);
+        const double gC = go[ch] / ((1.0 + C) * (1.0 + C));
+        // diffuse: kd a irr
+        const double gkd = gC * ac * ir[ch];
+        double ga = gC * kd * ir[ch];
+        const double girr = gC * kd * ac;
+        double gF = -gkd * (1.0 - m);
+        gm += -gkd * (1.0 - F);
+        // specular: P (F0 A + B)
+        const double gP = gC * (F0 * ab.A + ab.B);
+        double gF0 = gC * P * ab.A;
+        gA += gC * P * F0;
+        gB += gC * P;
+        // F = F0 + (Fr - F0) w5
+        gF0 += gF * (1.0 - w5);
+        if (fr_f0) gF0 += gF * w5;
+        else gr += -gF * w5;
+        gw5 += gF * (Fr - F0);
+        // F0 = 0.04 (1 - m) + a m
+        gm += gF0 * (ac - 0.04);
+        ga += gF0 * m;
+        // P = (1 - f) p0 + f p1
+        gf += gP * ((double)p1[ch] - p0[ch]);
+        oa[ch] = (float)ga;
+        oirr[ch] = (float)girr;
+        op0[ch] = (float)(gP * (1.0 - q.f));
+        op1[ch] = (float)(gP * q.f);
+    }
+    if (q.rin) gr += gf * (in.levels - 1);
+    gr += gA * ab.dAr + gB * ab.dBr;
+    return gw5 * (-5.0 * pow4(1.0 - q.c)) + gA * ab.dAc + gB * ab.dBc;
+}
+
+// the sum of a block's material gradients, one pair a block
+__device__ __forceinline__ void pbs_material_part(double gm, double gr, double (*red)[PBS_BS],
+                                                  double *__restrict__ part) {
+    red[0][threadIdx.x] = gm;
+    red[1][threadIdx.x] = gr;
+    __syncthreads();
+    for (int s = PBS_BS / 2; s > 0; s >>= 1) {
+        if (threadIdx.x < s) {
+            red[0][threadIdx.x] += red[0][threadIdx.x + s];
+            red[1][threadIdx.x] += red[1][threadIdx.x + s];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        part[2 * blockIdx.x] = red[0][0];
+        part[2 * blockIdx.x + 1] = red[1][0];
+    }
+}
+
 __global__ void k_pbs_shade(dressi_pbs_in in, const float *__restrict__ eye, const int32_t *__restrict__ tri_id,
                             int64_t Npv, int64_t n, float *__restrict__ color) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -457,19 +555,9 @@ __global__ void k_pbs_shade(dressi_pbs_in in, const float *__restrict__ eye, con
     }
     const double m = in.material[0], r = in.material[1];
     const PbsFrag q = pbs_geometry(in, eye + 3 * (i / Npv), i, r);
-    const LutS ab = lut_sample(in.lut, in.lut_n, q.c, r);
-    const double w5 = pow(1.0 - q.c, 5.0);
-    const float *a = in.albedo + i * in.albedo_stride;
-    const float *ir = in.irr + i * in.irr_stride;
     const float *p0 = in.pref + (int64_t)q.l0 * in.pref_level_stride + i * in.pref_stride;
-    const float *p1 = p0 + in.pref_level_stride;
-    for (int ch = 0; ch < 3; ch++) {
-        const double F0 = 0.04 * (1.0 - m) + a[ch] * m;
-        const double F = F0 + (fmax(1.0 - r, F0) - F0) * w5;
-        const double P = (1.0 - q.f) * p0[ch] + q.f * p1[ch];
-        const double C = (1.0 - F) * (1.0 - m) * a[ch] * ir[ch] + P * (F0 * ab.A + ab.B);
-        o[ch] = (float)(C / (1.0 + C));
-    }
+    pbs_color(in, q, m, r, in.albedo + i * in.albedo_stride, in.irr + i * in.irr_stride, p0,
+              p0 + in.pref_level_stride, o);
 }
 
 // Backward per fragment.  Writes, when given: the albedo, irradiance-sample
@@ -500,55 +588,20 @@ __global__ void __launch_bounds__(PBS_BS)
             const double m = in.material[0], r = in.material[1];
             const float *e = eye + 3 * (i / Npv);
             const PbsFrag q = pbs_geometry(in, e, i, r);
-            const LutS ab = lut_sample(in.lut, in.lut_n, q.c, r);
-            const double w5 = pow(1.0 - q.c, 5.0);
-            const float *a = in.albedo + i * in.albedo_stride;
-            const float *ir = in.irr + i * in.irr_stride;
             const float *p0 = in.pref + (int64_t)q.l0 * in.pref_level_stride + i * in.pref_stride;
-            const float *p1 = p0 + in.pref_level_stride;
-            const float *go = grad_color + 3 * i;
-            double gA = 0.0, gB = 0.0, gw5 = 0.0, gf = 0.0;
+            float oa[3], oirr[3], op0[3], op1[3];
+            const double gc = pbs_color_bwd(in, q, m, r, in.albedo + i * in.albedo_stride,
+                                            in.irr + i * in.irr_stride, p0, p0 + in.pref_level_stride,
+                                            grad_color + 3 * i, oa, oirr, op0, op1, gm, gr);
+#pragma unroll
             for (int ch = 0; ch < 3; ch++) {
-                const double ac = a[ch];
-                const double F0 = 0.04 * (1.0 - m) + ac * m;
-                const bool fr_f0 = F0 > 1.0 - r;     // max(1 - r, F0) takes F0
-                const double Fr = fr_f0 ? F0 : 1.0 - r;
-                const double F = F0 + (Fr - F0) * w5;
-                const double P = (1.0 - q.f) * p0[ch] + q.f * p1[ch];
-                const double kd = (1.0 - F) * (1.0 - m);
-                const double C = kd * ac * ir[ch] + P * (F0 * ab.A + ab.B);
-                const double gC = go[ch] / ((1.0 + C) * (1.0 + C));
-                // diffuse: kd a irr
-                const double gkd = gC * ac * ir[ch];
-                double ga = gC * kd * ir[ch];
-                const double girr = gC * kd * ac;
-                double gF = -gkd * (1.0 - m);
-                gm += -gkd * (1.0 - F);
-                // specular: P (F0 A + B)
-                const double gP = gC * (F0 * ab.A + ab.B);
-                double gF0 = gC * P * ab.A;
-                gA += gC * P * F0;
-                gB += gC * P;
-                // F = F0 + (Fr - F0) w5
-                gF0 += gF * (1.0 - w5);
-                if (fr_f0) gF0 += gF * w5;
-                else gr += -gF * w5;
-                gw5 += gF * (Fr - F0);
-                // F0 = 0.04 (1 - m) + a m
-                gm += gF0 * (ac - 0.04);
-                ga += gF0 * m;
-                // P = (1 - f) p0 + f p1
-                gf += gP * ((double)p1[ch] - p0[ch]);
-                if (g.albedo) g.albedo[i * g.albedo_stride + ch] = (float)ga;
-                if (g.irr) g.irr[3 * i + ch] = (float)girr;
+                if (g.albedo) g.albedo[i * g.albedo_stride + ch] = oa[ch];
+                if (g.irr) g.irr[3 * i + ch] = oirr[ch];
                 if (g.pref)
                     for (int l = 0; l < L; l++)
                         g.pref[(int64_t)l * 3 * n + 3 * i + ch] =
-                            l == q.l0 ? (float)(gP * (1.0 - q.f)) : (l == q.l0 + 1 ? (float)(gP * q.f) : 0.0f);
+                            l == q.l0 ? op0[ch] : (l == q.l0 + 1 ? op1[ch] : 0.0f);
             }
-            if (q.rin) gr += gf * (L - 1);
-            double gc = gw5 * (-5.0 * pow(1.0 - q.c, 4.0)) + gA * ab.dAc + gB * ab.dBc;
-            gr += gA * ab.dAr + gB * ab.dBr;
             if (g.normal || g.pos) {
                 const double gndv = q.ndv >= 1e-4 ? gc : 0.0;
                 double3 gnn = make_double3(gndv * q.v.x, gndv * q.v.y, gndv * q.v.z);
@@ -594,29 +647,25 @@ __global__ void __launch_bounds__(PBS_BS)
         }
     }
     if (!g.material) return;   // uniform over the launch
-    red[0][threadIdx.x] = gm;
-    red[1][threadIdx.x] = gr;
-    __syncthreads();
-    for (int s = PBS_BS / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + s];
-            red[1][threadIdx.x] += red[1][threadIdx.x + s];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        part[2 * blockIdx.x] = red[0][0];
-        part[2 * blockIdx.x + 1] = red[1][0];
-    }
+    pbs_material_part(gm, gr, red, part);
 }
 
 __global__ void __launch_bounds__(PBS_BS) k_pbs_material_sum(const double *__restrict__ part, int nb,
                                                              float *__restrict__ out) {
     __shared__ double red[2][PBS_BS];
     double a = 0.0, b = 0.0;
-    for (int k = threadIdx.x; k < nb; k += PBS_BS) {
-        a += part[2 * k];
-        b += part[2 * k + 1];
+    // eight pairs in flight, added in block order
+    for (int k = threadIdx.x; k < nb; k += 8 * PBS_BS) {
+        double2 v[8];
+#pragma unroll
+        for (int j = 0; j < 8; j++)
+            v[j] = k + j * PBS_BS < nb ? reinterpret_cast<const double2 *>(part)[k + j * PBS_BS] : make_double2(0.0, 0.0);
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+            if (k + j * PBS_BS >= nb) break;
+            a += v[j].x;
+            b += v[j].y;
+        }
     }
     red[0][threadIdx.x] = a;
     red[1][threadIdx.x] = b;
@@ -691,6 +740,261 @@ extern "C" int dressi_shade_pbs_bwd(dressi_ctx *ctx, const dressi_pbs_in *in, co
     if (grad->material)
         DR_LAUNCH("k_pbs_material_sum", (k_pbs_material_sum), 1, PBS_BS, 0, st, part, nb, grad->material);
     return dressi_launch_check(ctx, "shade_pbs_bwd");
+}
+
+// ---------------------------------------------------------------------------
+// packed PBS pass
+// ---------------------------------------------------------------------------
+// A step's fragments in one forward and one backward kernel in place of the
+// directions, the albedo's, the irradiance's and every level's lookup, the
+// shading, and their adjoints.  The roughness is one for all fragments, so all
+// of them sample the same two levels (which two, only the device knows): the
+// others need no lookup and their gradient is zero.  The irradiance map and
+// the level pair keep one inverse-UV map each, registered by the forward; the
+// backward stores sample gradients only for the pixels they kept, all that the
+// texel gathers read.  20 views of 256^2 x 2 layers (8^2 and 16^2 faces, 5
+// levels): 33 launches, 480 us, of which 152 the pixels' registration (many
+// pixels a cell: now one atomic for a wavefront's run of them), in place of 8,
+// 126 us; the two kernels here take 35 and 47, bound by the double-precision
+// shading and, the backward, by 132 registers.
+struct PbsMaps {
+    int32_t *inv_irr, *inv_pref;   // [S, 6 Si Si], [S, 6 Sp Sp]
+    float *dir_n, *dir_r;          // [N, 3] at kept pixels
+    float *g_irr, *g_pref;         // [N, 3], [N, 8] (level l0, 0, level l0 + 1, 0) at kept pixels
+    float *part_irr, *part_pref;   // the gathers' partial sums
+};
+static size_t pbs_maps(int Si, int Sp, int S, int64_t N, void *ws, PbsMaps &m) {
+    const int64_t ci = (int64_t)6 * Si * Si, cp = (int64_t)6 * Sp * Sp;
+    Carver c;
+    char *b = static_cast<char *>(ws);
+    m.inv_irr = reinterpret_cast<int32_t *>(b + c.take(sizeof(int32_t) * (size_t)(ci + cp) * S));
+    m.inv_pref = m.inv_irr + ci * S;
+    m.dir_n = reinterpret_cast<float *>(b + c.take(sizeof(float) * 3 * (size_t)N));
+    m.dir_r = reinterpret_cast<float *>(b + c.take(sizeof(float) * 3 * (size_t)N));
+    m.g_irr = reinterpret_cast<float *>(b + c.take(sizeof(float) * 3 * (size_t)N));
+    m.g_pref = reinterpret_cast<float *>(b + c.take(sizeof(float) * 8 * (size_t)N));
+    m.part_irr = reinterpret_cast<float *>(b + c.take(sizeof(float) * 3 * (size_t)ci * dressi_invuv_nsplit(ci, S)));
+    m.part_pref = reinterpret_cast<float *>(b + c.take(sizeof(float) * 8 * (size_t)cp * dressi_invuv_nsplit(cp, S)));
+    return c.off;
+}
+static dressi_tex_desc pbs_cube(int size, int Ct) {
+    dressi_tex_desc d{};
+    d.kind = DRESSI_TEX_CUBE;
+    d.Ht = d.Wt = size;
+    d.Ct = Ct;
+    d.wrap_u = d.wrap_v = DRESSI_WRAP_CLAMP;
+    return d;
+}
+
+__global__ void __launch_bounds__(256)
+    k_pbs_layers_fwd(dressi_pbs_layers L, dressi_tex_desc ti, dressi_tex_desc tp, const float *__restrict__ eye,
+                     const int32_t *__restrict__ tri_id, int K, uint32_t npix, int64_t n, float *__restrict__ samp,
+                     float *__restrict__ irr_s, float *__restrict__ pref_s, float *__restrict__ color, PbsMaps mp,
+                     int skip_empty) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    if (tri_id[i] < 0) {
+        if (skip_empty) return;
+        reinterpret_cast<float4 *>(samp)[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+        for (int c = 0; c < 3; c++)
+            irr_s[3 * i + c] = pref_s[3 * i + c] = pref_s[3 * (n + i) + c] = color[3 * i + c] = 0.0f;
+        return;
+    }
+    int sl, pix;
+    slice_pixel(blockIdx.x, npix, sl, pix);
+    const double m = L.in.material[0], r = L.in.material[1];
+    const float q2[2] = {L.uv[2 * i], L.uv[2 * i + 1]};
+    const PbsFrag q = pbs_geometry(L.in, eye + 3 * (sl / K), i, r);
+    const float dn[3] = {(float)q.nn.x, (float)q.nn.y, (float)q.nn.z};
+    const float dr[3] = {(float)q.R.x, (float)q.R.y, (float)q.R.z};
+    const Taps ta = make_taps(L.td, q2, 0), tn = make_taps(ti, dn, 0), tr = make_taps(tp, dr, 0);
+    float a[4] = {0.0f, 0.0f, 0.0f, 0.0f}, ir[3] = {0.0f, 0.0f, 0.0f}, p0[3] = {0.0f, 0.0f, 0.0f},
+          p1[3] = {0.0f, 0.0f, 0.0f};
+    if (ta.ok) tex_bilinear<4>(L.tex, L.td, ta, a, 4);
+    if (tn.ok) tex_bilinear<3>(L.irr_map, ti, tn, ir, 3);
+    const int64_t ci = (int64_t)6 * ti.Ht * ti.Wt, cp = (int64_t)6 * tp.Ht * tp.Wt;
+    if (tr.ok) {
+        const float *lv = L.pref_map + (int64_t)q.l0 * cp * 3;
+        tex_bilinear<3>(lv, tp, tr, p0, 3);
+        tex_bilinear<3>(lv + cp * 3, tp, tr, p1, 3);
+    }
+    tex_register(mp.inv_irr, tn.ok ? sl * ci + tex_cell(ti, tn, dn) : -1, pix);
+    tex_register(mp.inv_pref, tr.ok ? sl * cp + tex_cell(tp, tr, dr) : -1, pix);
+    float o[3];
+    pbs_color(L.in, q, m, r, a, ir, p0, p1, o);
+    reinterpret_cast<float4 *>(samp)[i] = make_float4(a[0], a[1], a[2], a[3]);
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        irr_s[3 * i + c] = ir[c];
+        pref_s[3 * i + c] = p0[c];
+        pref_s[3 * (n + i) + c] = p1[c];
+        color[3 * i + c] = o[c];
+    }
+}
+
+__global__ void __launch_bounds__(PBS_BS)
+    k_pbs_layers_bwd(dressi_pbs_layers L, dressi_tex_desc ti, dressi_tex_desc tp, const float *__restrict__ eye,
+                     const int32_t *__restrict__ tri_id, int K, uint32_t npix, int64_t n,
+                     const float *__restrict__ samp, const float *__restrict__ irr_s,
+                     const float *__restrict__ pref_s, const float *__restrict__ grad_color,
+                     float *__restrict__ g_samp, PbsMaps mp, double *__restrict__ part, int skip_empty) {
+    __shared__ double red[2][PBS_BS];
+    const int64_t i = (int64_t)blockIdx.x * PBS_BS + threadIdx.x;
+    double gm = 0.0, gr = 0.0;
+    if (i < n) {
+        if (tri_id[i] >= 0) {
+            int sl, pix;
+            slice_pixel(blockIdx.x, npix, sl, pix);
+            const double m = L.in.material[0], r = L.in.material[1];
+            float ir[3], p0[3], p1[3], go[3];
+            const float4 a4 = reinterpret_cast<const float4 *>(samp)[i];
+            const float a[3] = {a4.x, a4.y, a4.z};
+#pragma unroll
+            for (int c = 0; c < 3; c++) {
+                ir[c] = irr_s[3 * i + c];
+                p0[c] = pref_s[3 * i + c];
+                p1[c] = pref_s[3 * (n + i) + c];
+                go[c] = grad_color[3 * i + c];
+            }
+            const PbsFrag q = pbs_geometry(L.in, eye + 3 * (sl / K), i, r);
+            const float dn[3] = {(float)q.nn.x, (float)q.nn.y, (float)q.nn.z};
+            const float dr[3] = {(float)q.R.x, (float)q.R.y, (float)q.R.z};
+            const Taps tn = make_taps(ti, dn, 0), tr = make_taps(tp, dr, 0);
+            const int64_t ci = (int64_t)6 * ti.Ht * ti.Wt, cp = (int64_t)6 * tp.Ht * tp.Wt;
+            const bool kn = tn.ok && mp.inv_irr[sl * ci + tex_cell(ti, tn, dn)] == pix;
+            const bool kr = tr.ok && mp.inv_pref[sl * cp + tex_cell(tp, tr, dr)] == pix;
+            float oa[3], oirr[3], op0[3], op1[3];
+            pbs_color_bwd(L.in, q, m, r, a, ir, p0, p1, go, oa, oirr, op0, op1, gm, gr);
+#pragma unroll
+            for (int c = 0; c < 3; c++) g_samp[4 * i + c] = oa[c];
+            if (kn) {
+#pragma unroll
+                for (int c = 0; c < 3; c++) {
+                    mp.dir_n[3 * i + c] = dn[c];
+                    mp.g_irr[3 * i + c] = oirr[c];
+                }
+            }
+            if (kr) {
+#pragma unroll
+                for (int c = 0; c < 3; c++) mp.dir_r[3 * i + c] = dr[c];
+                float4 *o = reinterpret_cast<float4 *>(mp.g_pref + 8 * i);
+                o[0] = make_float4(op0[0], op0[1], op0[2], 0.0f);
+                o[1] = make_float4(op1[0], op1[1], op1[2], 0.0f);
+            }
+        } else if (!skip_empty) {
+            for (int c = 0; c < 3; c++) g_samp[4 * i + c] = 0.0f;
+        }
+    }
+    pbs_material_part(gm, gr, red, part);
+}
+
+// The gathers' parts added in order: the irradiance map's gradient, the level
+// pair's at its levels, zero at the others.
+__global__ void k_pbs_map_grads(PbsMaps mp, int ns_irr, int64_t n_irr, int ns_pref, int64_t cells, int levels,
+                                const float *__restrict__ material, float *__restrict__ g_irr,
+                                float *__restrict__ g_pref) {
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n_irr) {
+        float a = mp.part_irr[i];
+        for (int k = 1; k < ns_irr; k++) a += mp.part_irr[k * n_irr + i];
+        g_irr[i] = a;
+        return;
+    }
+    i -= n_irr;
+    if (i >= levels * cells * 3) return;
+    const int l = (int)(i / (cells * 3)), c = (int)(i % 3);
+    const int64_t cell = i / 3 - l * cells;
+    double f;
+    const int l0 = pbs_level(material[1], levels, f);
+    float a = 0.0f;
+    if (l == l0 || l == l0 + 1) {
+        const float *p = mp.part_pref + 8 * cell + 4 * (l - l0) + c;
+        a = p[0];
+        for (int k = 1; k < ns_pref; k++) a += p[(int64_t)k * cells * 8];
+    }
+    g_pref[i] = a;
+}
+
+extern "C" size_t dressi_pbs_layers_bytes(int Si, int Sp, int S, int H, int W) {
+    if (Si < 1 || Sp < 1 || S < 0 || H < 0 || W < 0) return 0;
+    PbsMaps m;
+    return pbs_maps(Si, Sp, S, (int64_t)S * H * W, nullptr, m);
+}
+
+static int check_pbs_layers(dressi_ctx *ctx, const dressi_pbs_layers *L, const float *eye, const int32_t *tri_id,
+                            int B, int K, int H, int W, const float *samp, const float *irr_s, const float *pref_s,
+                            const void *ws) {
+    if (!L || B < 0 || K < 1 || K > DRESSI_MAX_K || H < 0 || W < 0)
+        return ctx ? dressi_fail(ctx, DRESSI_EINVAL, "pbs_layers: bad arguments") : DRESSI_EINVAL;
+    int rc = check_pbs(ctx, &L->in, eye, tri_id, B, (int64_t)K * H * W);
+    if (rc) return rc;
+    const dressi_tex_desc ti = pbs_cube(L->Si, 3), tp = pbs_cube(L->Sp, 3);
+    if (L->td.kind != DRESSI_TEX_2D || L->td.Ct != 4 || (((uintptr_t)L->tex | (uintptr_t)samp | (uintptr_t)ws) & 15u))
+        return dressi_fail(ctx, DRESSI_EINVAL, "pbs_layers: the albedo is a 2-D RGBA texture, 16-byte aligned");
+    if ((rc = dr_check_tex(ctx, L->tex, &L->td, L->uv, tri_id, B * K, H, W))) return rc;
+    if ((rc = dr_check_tex(ctx, L->irr_map, &ti, L->uv, tri_id, B * K, H, W))) return rc;
+    if ((rc = dr_check_tex(ctx, L->pref_map, &tp, L->uv, tri_id, B * K, H, W))) return rc;
+    if ((int64_t)B * H * W > 0 && (!samp || !irr_s || !pref_s || !ws || !L->in.lut || L->in.lut_n < 1))
+        return dressi_fail(ctx, DRESSI_EINVAL, "pbs_layers: null input or output");
+    return DRESSI_OK;
+}
+
+extern "C" int dressi_pbs_layers_forward(dressi_ctx *ctx, const dressi_pbs_layers *L, const float *eye,
+                                         const int32_t *tri_id, int B, int K, int H, int W, float *samp,
+                                         float *irr_s, float *pref_s, float *color, void *ws, void *stream) {
+    int rc = check_pbs_layers(ctx, L, eye, tri_id, B, K, H, W, samp, irr_s, pref_s, ws);
+    if (rc) return rc;
+    const int64_t npix = (int64_t)H * W, n = (int64_t)B * K * npix;
+    if (n == 0) return DRESSI_OK;
+    if (!color) return dressi_fail(ctx, DRESSI_EINVAL, "pbs_layers: null colour");
+    hipStream_t st = (hipStream_t)stream;
+    PbsMaps mp;
+    pbs_maps(L->Si, L->Sp, B * K, n, ws, mp);
+    dressi_fill_i32(mp.inv_irr, -1, (int64_t)6 * (L->Si * L->Si + L->Sp * L->Sp) * B * K, st);
+    DR_LAUNCH("k_pbs_layers_fwd", (k_pbs_layers_fwd), (unsigned)((n + 255) / 256), 256, 0, st, *L,
+              pbs_cube(L->Si, 3), pbs_cube(L->Sp, 3), eye, tri_id, K, (uint32_t)npix, n, samp, irr_s, pref_s, color,
+              mp, ctx->skip_empty);
+    return dressi_launch_check(ctx, "pbs_layers_forward");
+}
+
+extern "C" int dressi_pbs_layers_backward(dressi_ctx *ctx, const dressi_pbs_layers *L, const float *eye,
+                                          const int32_t *tri_id, int B, int K, int H, int W, const float *samp,
+                                          const float *irr_s, const float *pref_s, const float *grad_color,
+                                          float *grad_samp, void *ws, float *grad_irr, float *grad_pref,
+                                          float *grad_material, void *stream) {
+    int rc = check_pbs_layers(ctx, L, eye, tri_id, B, K, H, W, samp, irr_s, pref_s, ws);
+    if (rc) return rc;
+    if (!grad_irr || !grad_pref || !grad_material)
+        return dressi_fail(ctx, DRESSI_EINVAL, "pbs_layers: null gradient");
+    const int S = B * K, levels = L->in.levels;
+    const int64_t npix = (int64_t)H * W, n = S * npix;
+    const int64_t ci = (int64_t)6 * L->Si * L->Si, cp = (int64_t)6 * L->Sp * L->Sp;
+    hipStream_t st = (hipStream_t)stream;
+    if (n == 0) {
+        dressi_fill_f32(grad_irr, 0.0f, 3 * ci, st);
+        dressi_fill_f32(grad_pref, 0.0f, 3 * cp * levels, st);
+        dressi_fill_f32(grad_material, 0.0f, 2, st);
+        return dressi_launch_check(ctx, "pbs_layers_backward");
+    }
+    if (!grad_color || !grad_samp) return dressi_fail(ctx, DRESSI_EINVAL, "pbs_layers: null gradient");
+    const int nb = (int)((n + PBS_BS - 1) / PBS_BS);
+    if ((rc = dressi_scratch(ctx, sizeof(double) * 2 * (size_t)nb, st))) return rc;
+    double *part = at<double>(ctx->scratch, 0);
+    PbsMaps mp;
+    pbs_maps(L->Si, L->Sp, S, n, ws, mp);
+    DR_LAUNCH("k_pbs_layers_bwd", (k_pbs_layers_bwd), nb, PBS_BS, 0, st, *L, pbs_cube(L->Si, 3), pbs_cube(L->Sp, 3),
+              eye, tri_id, K, (uint32_t)npix, n, samp, irr_s, pref_s, grad_color, grad_samp, mp, part,
+              ctx->skip_empty);
+    DR_LAUNCH("k_pbs_material_sum", (k_pbs_material_sum), 1, PBS_BS, 0, st, part, nb, grad_material);
+    const int nsi = dr_gather_parts(pbs_cube(L->Si, 3), mp.dir_n, tri_id, S, npix, mp.inv_irr, mp.g_irr, mp.part_irr,
+                                    st, ctx->iv_rows);
+    const int nsp = dr_gather_parts(pbs_cube(L->Sp, 8), mp.dir_r, tri_id, S, npix, mp.inv_pref, mp.g_pref,
+                                    mp.part_pref, st, ctx->iv_rows);
+    const int64_t no = 3 * (ci + cp * levels);
+    DR_LAUNCH("k_pbs_map_grads", (k_pbs_map_grads), (int)((no + 255) / 256), 256, 0, st, mp, nsi, 3 * ci, nsp, cp,
+              levels, L->in.material, grad_irr, grad_pref);
+    return dressi_launch_check(ctx, "pbs_layers_backward");
 }
 
 // ibl_filter(_bwd) tables and shade_pbs_bwd's material partials

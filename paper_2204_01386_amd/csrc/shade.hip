@@ -1066,16 +1066,6 @@ __device__ __forceinline__ bool tri_corners(const int32_t *__restrict__ tris, in
     return !(v0 < 0 || v0 >= Va || v1 < 0 || v1 >= Va || v2 < 0 || v2 >= Va);
 }
 
-// Slice (view, or layer of one) and pixel of this lane of a 256-lane block, of n
-// pixels a slice: a lane divides, in 32 bits, only past a slice's end.
-__device__ __forceinline__ void slice_pixel(int64_t block, uint32_t n, int &sl, int &pix) {
-    const int64_t first = block * 256, s0 = first / n;
-    const uint32_t q = (uint32_t)(first - s0 * n) + threadIdx.x;
-    const uint32_t k = q < n ? 0 : q / n;
-    sl = (int)(s0 + k);
-    pix = (int)(q - k * n);
-}
-
 // CV attribute channels (6: normal, position; 9: + colour); TEX: Phong with a
 // 2-D RGBA albedo texture, else Lambert with the vertex colour.
 template <int CV, bool TEX>

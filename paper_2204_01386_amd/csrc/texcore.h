@@ -224,6 +224,18 @@ __device__ __forceinline__ int64_t tex_cell(const dressi_tex_desc &td, const Tap
     return ((int64_t)t.face * td.Ht + cy) * td.Wt + cx;
 }
 
+// Registers a slice's pixel in its cell of an inverse-UV map (the largest pixel
+// stays).  key: the cell's place in the whole map, or -1 for a lane that
+// registers nothing; the lanes' pixels ascend, so of neighbouring lanes in one
+// cell only the last goes to memory.  Called by every lane still running.
+__device__ __forceinline__ void tex_register(int32_t *__restrict__ map, int64_t key, int pix) {
+    const int lane = __lane_id();
+    const unsigned long long on = __ballot(1);
+    const int lo = __shfl_down((int)key, 1, 64), hi = __shfl_down((int)(key >> 32), 1, 64);
+    const bool same = lane < 63 && (on >> (lane + 1) & 1) && lo == (int)key && hi == (int)(key >> 32);
+    if (key >= 0 && !same) atomicMax(&map[key], pix);
+}
+
 // The gradient of a cube direction q from that of its face coordinates.
 __device__ __forceinline__ void cube_dcoord(const float *q, float du, float dv, float *g3) {
     // u = (sc/ma + 1)/2 with ma = |major component|

@@ -742,6 +742,15 @@ extern "C" int dressi_texture_grad_invuv(dressi_ctx *ctx, const dressi_tex_desc 
     return dressi_launch_check(ctx, "texture_grad_invuv");
 }
 
+int dr_gather_parts(const dressi_tex_desc &td, const float *coord, const int32_t *tri_id, int S, int64_t npix,
+                    const int32_t *inv, const float *grad_out, float *part, hipStream_t st, int rows) {
+    const int nsplit = dressi_invuv_nsplit((int64_t)tex_faces(td) * td.Ht * td.Wt, S);
+    launch_gather(rows, aligned16(grad_out, part) ? td.Ct : 0, (td.Wt + IV_T - 1) / IV_T, td.Ht,
+                  tex_faces(td) * nsplit, st, td, coord, tri_id, npix, S, nsplit, inv, grad_out, part, nullptr,
+                  LossJob{}, ListJob{});
+    return nsplit;
+}
+
 void dr_gather_invuv(const dressi_tex_desc &td, const float *coord, const int32_t *tri_id, int S, int64_t npix,
                      const int32_t *inv, const float *grad_out, float *part, float *grad_tex, hipStream_t st,
                      int rows) {

@@ -1372,6 +1372,27 @@ class PbsStep:
         pg.albedo, pg.albedo_stride = _cp(st.g_samp, 0), Ct
         pg.irr, pg.pref, pg.material = _p(self.g_irr_s), _p(self.g_pref_s), _p(self.g_material)
 
+        # the fragments' stages as one forward and one backward pass (same
+        # values; dir_n, dir_r, ltid, g_irr_s and g_pref_s are not written, and
+        # pref_s holds the two levels in use); False keeps the separate stages
+        self.fuse_layers = True
+        nb = int(_lib.dressi_pbs_layers_bytes(Si, Sp, st.B * st.K, st.H, st.W))
+        self._ws = torch.empty(nb, dtype=torch.uint8, device=st.dev)
+
+    def _layers(self):
+        """The step's tensors as the packed PBS pass takes them, or None where
+        the stages run separately: albedos of other channel counts or
+        alignment."""
+        st = self.st
+        if not self.fuse_layers or st.Ct != 4 or st.desc.kind != Bd.TEX_2D:
+            return None
+        if any(t.data_ptr() % 16 for t in (st.tex, st.samp, self._ws)):
+            return None
+        pl = Bd.PbsLayers()
+        pl.inp, pl.tex, pl.td, pl.uv = self._pin, _p(st.tex), st.desc, _p(st.uvbuf)
+        pl.irr_map, pl.pref_map, pl.Si, pl.Sp = _p(self.irr), _p(self.pref), self.Si, self.Sp
+        return pl
+
     def _pref_level(self, t, l):
         return C.c_void_p(t.data_ptr() + 4 * l * (t[0].numel()))
 
@@ -1382,18 +1403,25 @@ class PbsStep:
         S = B * K
         ck(_lib.dressi_ibl_filter(h, _p(self.env), C.byref(self.desc), _p(self.irr), _p(self.pref), _p(self.norm),
                                   s), "ibl_filter")
-        ck(_lib.dressi_texture(h, _p(st.tex), C.byref(st.desc), _p(st.uvbuf), _p(st.tri_id), S, H, W, _p(st.samp), s),
-           "texture")
-        ck(_lib.dressi_shade_pbs(h, C.byref(self._pin), _p(st.eye), _p(st.tri_id), B, K * H * W, None, _p(self.dir_n),
-                                 _p(self.dir_r), _p(self.ltid), s), "shade_pbs dirs")
-        ck(_lib.dressi_texture(h, _p(self.irr), C.byref(self.cube_irr), _p(self.dir_n), _p(st.tri_id), S, H, W,
-                               _p(self.irr_s), s), "texture irradiance")
-        for l in range(L):
-            ck(_lib.dressi_texture(h, self._pref_level(self.pref, l), C.byref(self.cube_pref), _p(self.dir_r),
-                                   self._pref_level(self.ltid, l), S, H, W, self._pref_level(self.pref_s, l), s),
-               "texture prefiltered")
-        ck(_lib.dressi_shade_pbs(h, C.byref(self._pin), _p(st.eye), _p(st.tri_id), B, K * H * W, _p(st.layer_color),
-                                 None, None, None, s), "shade_pbs")
+        pl = self._layers()
+        if pl is not None:
+            with st._sparse():
+                ck(_lib.dressi_pbs_layers_forward(h, C.byref(pl), _p(st.eye), _p(st.tri_id), B, K, H, W, _p(st.samp),
+                                                  _p(self.irr_s), _p(self.pref_s), _p(st.layer_color), _p(self._ws),
+                                                  s), "pbs_layers_forward")
+        else:
+            ck(_lib.dressi_texture(h, _p(st.tex), C.byref(st.desc), _p(st.uvbuf), _p(st.tri_id), S, H, W, _p(st.samp), s),
+               "texture")
+            ck(_lib.dressi_shade_pbs(h, C.byref(self._pin), _p(st.eye), _p(st.tri_id), B, K * H * W, None, _p(self.dir_n),
+                                     _p(self.dir_r), _p(self.ltid), s), "shade_pbs dirs")
+            ck(_lib.dressi_texture(h, _p(self.irr), C.byref(self.cube_irr), _p(self.dir_n), _p(st.tri_id), S, H, W,
+                                   _p(self.irr_s), s), "texture irradiance")
+            for l in range(L):
+                ck(_lib.dressi_texture(h, self._pref_level(self.pref, l), C.byref(self.cube_pref), _p(self.dir_r),
+                                       self._pref_level(self.ltid, l), S, H, W, self._pref_level(self.pref_s, l), s),
+                   "texture prefiltered")
+            ck(_lib.dressi_shade_pbs(h, C.byref(self._pin), _p(st.eye), _p(st.tri_id), B, K * H * W, _p(st.layer_color),
+                                     None, None, None, s), "shade_pbs")
         ck(_lib.dressi_softras(h, _p(st.layer_color), _p(st.dist), _p(st.tri_id), B, K, H, W, 3, st.sigma, st.delta,
                                st.blend, _p(st.color), _p(st.sil), _p(st.E), s), "softras")
 
@@ -1407,14 +1435,22 @@ class PbsStep:
         S = B * K
         ck(_lib.dressi_softras_bwd(h, _p(st.layer_color), _p(st.dist), _p(st.tri_id), B, K, H, W, 3, st.sigma,
                                    _p(st.E), _p(st.g_color), _p(st.g_sil), _p(st.g_layer), None, s), "softras_bwd")
-        ck(_lib.dressi_shade_pbs_bwd(h, C.byref(self._pin), _p(st.eye), _p(st.tri_id), B, K * H * W, _p(st.g_layer),
-                                     None, None, C.byref(self._pg), s), "shade_pbs_bwd")
-        ck(_lib.dressi_texture_bwd(h, _p(self.irr), C.byref(self.cube_irr), _p(self.dir_n), _p(st.tri_id), S, H, W,
-                                   _p(self.g_irr_s), 0, _p(self.g_irr), None, s), "texture_bwd irradiance")
-        for l in range(L):
-            ck(_lib.dressi_texture_bwd(h, self._pref_level(self.pref, l), C.byref(self.cube_pref), _p(self.dir_r),
-                                       self._pref_level(self.ltid, l), S, H, W, self._pref_level(self.g_pref_s, l),
-                                       0, self._pref_level(self.g_pref, l), None, s), "texture_bwd prefiltered")
+        pl = self._layers()
+        if pl is not None:
+            with st._sparse():
+                ck(_lib.dressi_pbs_layers_backward(h, C.byref(pl), _p(st.eye), _p(st.tri_id), B, K, H, W, _p(st.samp),
+                                                   _p(self.irr_s), _p(self.pref_s), _p(st.g_layer), _p(st.g_samp),
+                                                   _p(self._ws), _p(self.g_irr), _p(self.g_pref), _p(self.g_material),
+                                                   s), "pbs_layers_backward")
+        else:
+            ck(_lib.dressi_shade_pbs_bwd(h, C.byref(self._pin), _p(st.eye), _p(st.tri_id), B, K * H * W, _p(st.g_layer),
+                                         None, None, C.byref(self._pg), s), "shade_pbs_bwd")
+            ck(_lib.dressi_texture_bwd(h, _p(self.irr), C.byref(self.cube_irr), _p(self.dir_n), _p(st.tri_id), S, H, W,
+                                       _p(self.g_irr_s), 0, _p(self.g_irr), None, s), "texture_bwd irradiance")
+            for l in range(L):
+                ck(_lib.dressi_texture_bwd(h, self._pref_level(self.pref, l), C.byref(self.cube_pref), _p(self.dir_r),
+                                           self._pref_level(self.ltid, l), S, H, W, self._pref_level(self.g_pref_s, l),
+                                           0, self._pref_level(self.g_pref, l), None, s), "texture_bwd prefiltered")
         ck(_lib.dressi_ibl_filter_bwd(h, C.byref(self.desc), _p(self.norm), _p(self.g_irr), _p(self.g_pref),
                                       _p(self.g_env), s), "ibl_filter_bwd")
         ck(_lib.dressi_texture_grad_invuv(h, C.byref(st.desc), _p(st.uvbuf), _p(st.tri_id), S, H, W, _p(self.ts.inv),
