@@ -211,6 +211,14 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX)
         }
     }
     __syncthreads();
+    const int lg = record_lanes(nr);
+    if (lg > 0) {
+        const int r = p >> lg;
+        if (r < nr)
+            ib_record_part(vals, S, C, sfrag, fl.rec_start[base + r], r + 1 < nr ? fl.rec_start[base + r + 1] : nf,
+                           p & ((1 << lg) - 1), 1 << lg, partial + (base + r) * 3 * C);
+        return;
+    }
     for (int r = p; r < nr; r += DRESSI_TILE_PIX) {
         const int j0 = r == p ? rs0 : fl.rec_start[base + r];
         const int j1 = (r + 1 < nr) ? (r == p ? rs1 : fl.rec_start[base + r + 1]) : nf;

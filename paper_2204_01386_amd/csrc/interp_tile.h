@@ -145,3 +145,59 @@ __device__ __forceinline__ void ib_record(const float *vals, int S, int C, const
                 if (c0 + c < C) dst[i * C + c0 + c] = acc[i][c];
     }
 }
+
+// log2 of the lanes that sum a record of a tile's nr: one lane a record
+// takes as many dependent LDS reads as its triangle has fragments in the tile
+// while the lanes beyond nr idle, so with few records (large triangles) a
+// record's channels are spread over 8 or 16 lanes.  The geometry adjoint of
+// 1,280 triangles at 128^2 14.6 -> 10.7 us, of 24 instances 213 -> 158; six
+// views of 51,076 at 1024^2, its two kernels 82 + 61 -> 73 + 58.  Spreading 33 to 64
+// records over 4 lanes gains nothing (10.1 us for 81,920 triangles at 512^2, 9.6
+// with one lane) and 65 to 128 over 2 costs (11.0): the lanes read the weights
+// again for each channel.
+__device__ __forceinline__ int record_lanes(int nr) {
+    return nr > 32 ? 0 : nr > 16 ? 3 : 4;
+}
+
+// ib_record's channels g, g + G, ... (the same sums in the same order).
+__device__ __forceinline__ void ib_record_part(const float *vals, int S, int C, const uint16_t *frag, int j0, int j1,
+                                               int g, int G, float *__restrict__ dst) {
+    for (int c = g; c < C; c += G) {
+        float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f;
+#pragma unroll 4
+        for (int j = j0; j < j1; j++) {
+            const float *v = vals + (int)frag[j] * S;
+            const float w0 = v[0], w1 = v[1], w2 = 1.0f - w0 - w1, gc = v[2 + c];
+            a0 += w0 * gc;
+            a1 += w1 * gc;
+            a2 += w2 * gc;
+        }
+        dst[c] = a0;
+        dst[C + c] = a1;
+        dst[2 * C + c] = a2;
+    }
+}
+
+// The rasterization adjoint's record: the sum of its fragments' nine values.
+__device__ __forceinline__ void rb_record(const float *vals, const uint16_t *frag, int j0, int j1,
+                                          float *__restrict__ dst) {
+    float acc[9];
+#pragma unroll
+    for (int c = 0; c < 9; c++) acc[c] = 0.0f;
+    for (int j = j0; j < j1; j++) {
+        const float *v = vals + (int)frag[j] * 9;
+#pragma unroll
+        for (int c = 0; c < 9; c++) acc[c] += v[c];
+    }
+#pragma unroll
+    for (int c = 0; c < 9; c++) dst[c] = acc[c];
+}
+__device__ __forceinline__ void rb_record_part(const float *vals, const uint16_t *frag, int j0, int j1, int g, int G,
+                                               float *__restrict__ dst) {
+    for (int c = g; c < 9; c += G) {
+        float a = 0.0f;
+#pragma unroll 4
+        for (int j = j0; j < j1; j++) a += vals[(int)frag[j] * 9 + c];
+        dst[c] = a;
+    }
+}

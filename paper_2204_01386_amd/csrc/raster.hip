@@ -2136,20 +2136,18 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX)
         }
     }
     __syncthreads();
+    const int lg = record_lanes(nr);
+    if (lg > 0) {
+        const int r = p >> lg;
+        if (r < nr)
+            rb_record_part(vals, sfrag, fl.rec_start[base + r], r + 1 < nr ? fl.rec_start[base + r + 1] : nf,
+                           p & ((1 << lg) - 1), 1 << lg, partial + (base + r) * 9);
+        return;
+    }
     for (int r = p; r < nr; r += DRESSI_TILE_PIX) {
         const int j0 = fl.rec_start[base + r];
         const int j1 = (r + 1 < nr) ? fl.rec_start[base + r + 1] : nf;
-        float acc[9];
-#pragma unroll
-        for (int c = 0; c < 9; c++) acc[c] = 0.0f;
-        for (int j = j0; j < j1; j++) {
-            const float *v = vals + (int)sfrag[j] * 9;
-#pragma unroll
-            for (int c = 0; c < 9; c++) acc[c] += v[c];
-        }
-        float *dst = partial + (base + r) * 9;
-#pragma unroll
-        for (int c = 0; c < 9; c++) dst[c] = acc[c];
+        rb_record(vals, sfrag, j0, j1, partial + (base + r) * 9);
     }
 }
 
@@ -2322,6 +2320,7 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
     constexpr int S = (CC + 2) | 1;
     float *rvals = vals + DRESSI_TILE_PIX * S;
     __shared__ uint16_t sfrag[DRESSI_TILE_PIX];   // the tile's sorted fragment list
+    __shared__ int srec[DRESSI_TILE_PIX + 1];     // its records' starts, and its end
     const int bt = (int)blockIdx.x;
     const int tx = bt % ntx, ty = bt / ntx;
     const int p = threadIdx.x;
@@ -2335,7 +2334,6 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
     const int nr = fl.n_rec[bt];
     const uint16_t fr = fl.frag[base + p];   // into LDS before the barrier (its load overlaps the fragment's)
     const int rs0 = fl.rec_start[base + p];
-    const int rs1 = p + 1 < DRESSI_TILE_PIX ? fl.rec_start[base + p + 1] : 0;
     if (x < W && y < H) {
         // The fragment's loads in two rounds: its corners and viewport beside
         // its barycentrics, output gradient and incoming barycentric gradient;
@@ -2401,24 +2399,21 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
         }
     }
     sfrag[p] = fr;
+    if (p < nr) srec[p] = rs0;
+    if (p + 1 >= nr && p < nr) srec[nr] = nf;
     __syncthreads();
-    // one record per lane (a tile has at most 256)
-    if (p < nr) {
-        const int r = p;
-        const int j0 = rs0;
-        const int j1 = (r + 1 < nr) ? rs1 : nf;
-        ib_record(vals, S, CC, sfrag, j0, j1, ipart + (base + r) * 3 * CC);
-        float acc9[9];
-#pragma unroll
-        for (int c = 0; c < 9; c++) acc9[c] = 0.0f;
-        for (int j = j0; j < j1; j++) {
-            const float *v = rvals + (int)sfrag[j] * 9;
-#pragma unroll
-            for (int c = 0; c < 9; c++) acc9[c] += v[c];
-        }
-        float *dst = rpart + (base + r) * 9;
-#pragma unroll
-        for (int c = 0; c < 9; c++) dst[c] = acc9[c];
+    // one record per lane (a tile has at most 256), or a few lanes a record
+    const int lg = record_lanes(nr), r = p >> lg;
+    if (r >= nr) return;
+    const int j0 = srec[r], j1 = srec[r + 1];
+    float *di = ipart + (base + r) * 3 * CC, *dr = rpart + (base + r) * 9;
+    if (lg > 0) {
+        const int g = p & ((1 << lg) - 1);
+        ib_record_part(vals, S, CC, sfrag, j0, j1, g, 1 << lg, di);
+        rb_record_part(rvals, sfrag, j0, j1, g, 1 << lg, dr);
+    } else {
+        ib_record(vals, S, CC, sfrag, j0, j1, di);
+        rb_record(rvals, sfrag, j0, j1, dr);
     }
 }
 
