@@ -196,6 +196,14 @@ int dressi_rasterize(dressi_ctx *ctx, const float *pos_clip, const int32_t *tris
                      int B, int V, int T, int H, int W, int K, float r, int cull,
                      int32_t *tri_id, float *bary, float *dist, void *stream);
 
+/* dressi_rasterize with tile bins that have room for every triangle where
+ * those take at most 512 MiB: *full (host) is then 1 and no bin can overflow,
+ * so the caller need not read the device's status; otherwise 0, with the
+ * bins of dressi_rasterize. */
+int dressi_rasterize_full_bins(dressi_ctx *ctx, const float *pos_clip, const int32_t *tris, int B, int V, int T,
+                               int H, int W, int K, float r, int cull, int32_t *tri_id, float *bary, float *dist,
+                               int *full, void *stream);
+
 /* Edge-band form of dressi_rasterize for a HardSoftRas blend (§3.4.3): with
  * the blend's edge mask E (dressi_softras with the same delta and mode), the
  * image outside E is S^H C_1 and the silhouette S^H, so there only the front

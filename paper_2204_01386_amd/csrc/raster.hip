@@ -1363,9 +1363,13 @@ static int check_raster_args(dressi_ctx *ctx, const void *pos, const void *tris,
 
 // band: -2 = the full form; otherwise the edge-band form of a blend whose
 // edge mask is empty (-1) or the boundary of S^H dilated by band >= 0 pixels.
+// full: bins with room for every triangle, which cannot overflow, where they
+// take at most FULL_BINS_BYTES; *full tells whether they have it.
+#define FULL_BINS_BYTES ((int64_t)1 << 29)
 static int rasterize_impl(dressi_ctx *ctx, const float *pos_clip, const int32_t *tris, Viewports vp, int B,
                           int V, int T, int H, int W, int K, float r, int cull, int32_t *tri_id, float *bary,
-                          float *dist, void *stream, int band = -2) {
+                          float *dist, void *stream, int band = -2, int *full = nullptr) {
+    if (full) *full = 0;
     int rc = check_raster_args(ctx, pos_clip, tris, B, V, T, H, W, K, r);
     if (rc) return rc;
     if (!tri_id || !bary) return dressi_fail(ctx, DRESSI_EINVAL, "rasterize: null tri_id or bary");
@@ -1387,18 +1391,33 @@ static int rasterize_impl(dressi_ctx *ctx, const float *pos_clip, const int32_t 
                       vp, B, V, T, H, W, cull, zbuf, lg);
         DR_LAUNCH("k_raster_direct_resolve", (k_raster_direct_resolve), (int)((npx + 255) / 256), 256, 0, st, pc4,
                   tris, vp, B, V, T, H, W, cull, zbuf, tri_id, reinterpret_cast<float2 *>(bary));
+        if (full) *full = 1;
         return dressi_launch_check(ctx, "rasterize");
     }
     int ntx = tiles_x(W), nty = tiles_y(H), nt = ntx * nty;
     int margin = soft_margin(r, W);
     int cap = tile_capacity(ctx, B, T, nt, margin);
     const bool banded = soft && band >= -1;
-    Carver c;
-    size_t o[3];
-    raster_scratch(B, T, nt, cap, soft, c, o);
-    const size_t o_sten = banded ? c.take(dressi_edge_plane_bytes(B, H, W)) : 0;   // S^H and the edge mask
-    const size_t o_edge = banded ? c.take(dressi_edge_plane_bytes(B, H, W)) : 0;
-    rc = dressi_scratch(ctx, c.off, st);
+    size_t o[3], o_sten = 0, o_edge = 0;
+    const auto layout = [&](int n) {
+        Carver c;
+        raster_scratch(B, T, nt, n, soft, c, o);
+        if (banded) {   // S^H and the edge mask
+            o_sten = c.take(dressi_edge_plane_bytes(B, H, W));
+            o_edge = c.take(dressi_edge_plane_bytes(B, H, W));
+        }
+        return c.off;
+    };
+    if (full) {
+        if (cap >= T) {
+            *full = 1;
+        } else if ((int64_t)sizeof(int32_t) * B * nt * T <= FULL_BINS_BYTES &&
+                   dressi_scratch(ctx, layout(T), st) == DRESSI_OK) {
+            *full = 1;
+            cap = T;
+        }
+    }
+    rc = dressi_scratch(ctx, layout(cap), st);
     if (rc) return rc;
     rc = dressi_counters(ctx, (size_t)B * nt * (soft ? 3 : 1), st);   // soft: near, far, workgroups done
     if (rc) return rc;
@@ -1460,6 +1479,14 @@ extern "C" int dressi_rasterize(dressi_ctx *ctx, const float *pos_clip, const in
                                 int32_t *tri_id, float *bary, float *dist, void *stream) {
     return rasterize_impl(ctx, pos_clip, tris, Viewports{nullptr, nullptr}, B, V, T, H, W, K, r, cull, tri_id,
                           bary, dist, stream);
+}
+
+extern "C" int dressi_rasterize_full_bins(dressi_ctx *ctx, const float *pos_clip, const int32_t *tris, int B, int V,
+                                          int T, int H, int W, int K, float r, int cull, int32_t *tri_id,
+                                          float *bary, float *dist, int *full, void *stream) {
+    if (!full) return ctx ? dressi_fail(ctx, DRESSI_EINVAL, "rasterize_full_bins: null full") : DRESSI_EINVAL;
+    return rasterize_impl(ctx, pos_clip, tris, Viewports{nullptr, nullptr}, B, V, T, H, W, K, r, cull, tri_id,
+                          bary, dist, stream, -2, full);
 }
 
 extern "C" int dressi_rasterize_banded(dressi_ctx *ctx, const float *pos_clip, const int32_t *tris, int B,
