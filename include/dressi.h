@@ -596,6 +596,17 @@ int dressi_packed_backward(dressi_ctx *ctx, const dressi_packed_scene *scene, co
                            float *grad_samp, float *grad_bary_uv, int32_t *inv, void *inv_rec, float *grad_tex,
                            void *stream);
 
+/* dressi_interpolate_bwd of vattr [V,Cv] (Cv = 6 or 9, Ba = 1) over B views of
+ * one hard layer (K = 1), then dressi_rasterize_bwd (r = 0) from its
+ * grad_bary, the per-tile adjoints of both in one pass: the same values.
+ * frag_index and adj are required; under a capture whose arena is too small
+ * for both stages' records the two calls run in sequence. */
+int dressi_attr_raster_bwd(dressi_ctx *ctx, const float *vattr, int V, int Cv, const int32_t *tris, int T,
+                           const float *pos_clip, int B, int H, int W, int cull, const int32_t *tri_id,
+                           const float *bary, const float *grad_gbuf, const float *grad_bary_in,
+                           const void *frag_index, const int32_t *adj, float *grad_vattr, float *grad_bary,
+                           float *grad_pos_clip, void *stream);
+
 /* Inputs of the packed pass over the K layers of a soft image: s as in the
  * packed single-layer pass, with mode Lambert (Cv 9), Phong (Cv 6, td of 4
  * channels) or Phong with environment (Cv 9: normal, position, tangent; td

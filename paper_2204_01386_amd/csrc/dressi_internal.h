@@ -229,6 +229,8 @@ struct TriTiles {
 };
 // Per-tile interpolation adjoint (interp.hip): grad_bary and each tile's
 // per-triangle records of b_i g in `part` [B*nTiles*256*K][3][C].
+void dr_interp_bwd_vertices(int B, int Ba, int Va, int T, int K, int C, const TriTiles &tt, const float *part,
+                            const Adjacency &A, float *grad_attr, hipStream_t st);
 void dr_interp_bwd_tiles(const float *attr, int Ba, int Va, int C, const int32_t *attr_tris, int T,
                          const int32_t *tri_id, const float *bary, int B, int K, int H, int W, const FragLists &fl,
                          const float *grad_out, const float *grad_bary_in, float *grad_bary, float *part,

@@ -345,6 +345,26 @@ void dr_interp_bwd_tiles(const float *attr, int Ba, int Va, int C, const int32_t
     }
 }
 
+// The per-vertex sums of the records: the attribute gradient.
+void dr_interp_bwd_vertices(int B, int Ba, int Va, int T, int K, int C, const TriTiles &tt, const float *part,
+                            const Adjacency &A, float *grad_attr, hipStream_t st) {
+    const int64_t nv = (int64_t)Ba * Va, gv = (nv * IBV_LANES + 255) / 256;
+    if (C == 6)
+        DR_LAUNCH("k_interp_bwd_vertex", (k_interp_bwd_vertex_c<6>), (int)gv, 256, 0, st, B, Ba, Va, T, K, tt,
+                  part, A, grad_attr);
+    else if (C == 9)
+        DR_LAUNCH("k_interp_bwd_vertex", (k_interp_bwd_vertex_c<9>), (int)gv, 256, 0, st, B, Ba, Va, T, K, tt,
+                  part, A, grad_attr);
+    else if (C == 3)
+        DR_LAUNCH("k_interp_bwd_vertex", (k_interp_bwd_vertex_c<3>), (int)gv, 256, 0, st, B, Ba, Va, T, K, tt,
+                  part, A, grad_attr);
+    else {
+        int64_t ng = (int64_t)Ba * Va * C;
+        DR_LAUNCH("k_interp_bwd_vertex", (k_interp_bwd_vertex), (int)((ng * IBV_LANES + 255) / 256), 256, 0,
+                  st, B, Ba, Va, T, K, C, tt, part, A, grad_attr);
+    }
+}
+
 extern "C" int dressi_interpolate_bwd(dressi_ctx *ctx, const float *attr, int Ba, int Va, int C,
                                       const int32_t *attr_tris, int T, const int32_t *tri_id,
                                       const float *bary, int B, int K, int H, int W,
@@ -391,21 +411,7 @@ extern "C" int dressi_interpolate_bwd(dressi_ctx *ctx, const float *attr, int Ba
         float *part = at<float>(S, o_part);
         dr_interp_bwd_tiles(attr, Ba, Va, C, attr_tris, T, tri_id, bary, B, K, H, W, fl, grad_out, grad_bary_in,
                             grad_bary, part, ctx->skip_empty, st);
-        const int64_t nv = (int64_t)Ba * Va, gv = (nv * IBV_LANES + 255) / 256;
-        if (C == 6)
-            DR_LAUNCH("k_interp_bwd_vertex", (k_interp_bwd_vertex_c<6>), (int)gv, 256, 0, st, B, Ba, Va, T, K, tt,
-                      part, A, grad_attr);
-        else if (C == 9)
-            DR_LAUNCH("k_interp_bwd_vertex", (k_interp_bwd_vertex_c<9>), (int)gv, 256, 0, st, B, Ba, Va, T, K, tt,
-                      part, A, grad_attr);
-        else if (C == 3)
-            DR_LAUNCH("k_interp_bwd_vertex", (k_interp_bwd_vertex_c<3>), (int)gv, 256, 0, st, B, Ba, Va, T, K, tt,
-                      part, A, grad_attr);
-        else {
-            int64_t ng = (int64_t)Ba * Va * C;
-            DR_LAUNCH("k_interp_bwd_vertex", (k_interp_bwd_vertex), (int)((ng * IBV_LANES + 255) / 256), 256, 0,
-                      st, B, Ba, Va, T, K, C, tt, part, A, grad_attr);
-        }
+        dr_interp_bwd_vertices(B, Ba, Va, T, K, C, tt, part, A, grad_attr, st);
     } else if (grad_bary && n > 0) {
         DR_LAUNCH("k_interp_bwd_bary", (k_interp_bwd_bary), (int)((n + 255) / 256), 256, 0, st,
                   attr, Ba, Va, C, attr_tris, T, tri_id, (int64_t)K * H * W, n, grad_out,

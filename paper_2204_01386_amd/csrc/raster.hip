@@ -2323,19 +2323,22 @@ int64_t dr_tile_capacity(const dressi_limits &l) {
 // geometry adjoint of one image (B = 1, K = 1, hard): interpolation,
 // rasterization, transform and vertex-normal adjoints in three launches
 // ---------------------------------------------------------------------------
-// Per tile (B = K = 1): the interpolation adjoint of every fragment (its
+// Per tile (K = 1; VIEWS: of several views, each XCD whole views): the
+// interpolation adjoint of every fragment (its
 // barycentric gradient and staged row, as k_interp_bwd_tile), then, from that
 // barycentric gradient, the rasterization adjoint of the same fragment (as
 // k_rast_bwd_tile); after one barrier each triangle record sums both in the
-// tile's sorted order.  The same values as the two kernels in sequence.
-template <int CC>
+// tile's sorted order.  The same values as the two kernels in sequence, which
+// read the fragments, their corners and the tile's lists twice: six views of
+// 1024^2 (51,076 triangles, nine channels) 73 + 58 us, here 102.
+template <int CC, bool VIEWS>
 __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_per_eu(5)))
     k_geo_tile(const float *__restrict__ attr, int Va, const int32_t *__restrict__ tris, int T,
                const float4 *__restrict__ pos_clip, Viewports vp, int H, int W, int cull,
                const int32_t *__restrict__ tri_id, const float2 *__restrict__ bary, int ntx, FragLists fl,
                const float *__restrict__ grad_out, const float2 *__restrict__ gb_in, float2 *__restrict__ grad_bary,
                float *__restrict__ ipart, float *__restrict__ rpart, int skip_empty, ListJob lj, LossJob loss,
-               int nmain) {
+               int nmain, int nt) {
     extern __shared__ float vals[];   // [256][ib_stride(CC)] interpolation rows, then [256][9]
     // workgroups past the tiles run a list-building job of the step, and the
     // last one its loss's sum
@@ -2348,8 +2351,9 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
     float *rvals = vals + DRESSI_TILE_PIX * S;
     __shared__ uint16_t sfrag[DRESSI_TILE_PIX];   // the tile's sorted fragment list
     __shared__ int srec[DRESSI_TILE_PIX + 1];     // its records' starts, and its end
-    const int bt = (int)blockIdx.x;
-    const int tx = bt % ntx, ty = bt / ntx;
+    const int bt = VIEWS ? (int)xcd_block(blockIdx.x, nmain) : (int)blockIdx.x;
+    const int view = VIEWS ? bt / nt : 0, tile = VIEWS ? bt - view * nt : bt;
+    const int tx = tile % ntx, ty = tile / ntx;
     const int p = threadIdx.x;
     const int x = tx * DRESSI_TILE + (p & (DRESSI_TILE - 1));
     const int y = ty * DRESSI_TILE + p / DRESSI_TILE;
@@ -2367,7 +2371,7 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
         // then the corners' attribute rows beside their clip-space positions
         // (row 0 for an invalid corner, then unused).  The arithmetic is that
         // of ib_fragment and dr_setup.
-        const int64_t o = (int64_t)y * W + x;
+        const int64_t o = ((int64_t)view * H + y) * W + x;
         const int t = tri_id[o];
         const bool tri = t >= 0 && t < T;
         int v0 = -1, v1 = -1, v2 = -1;
@@ -2396,9 +2400,10 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
             ld_row<CC>(attr + (int64_t)c0 * CC, r0, CC);
             ld_row<CC>(attr + (int64_t)c1 * CC, r1, CC);
             ld_row<CC>(attr + (int64_t)c2 * CC, r2, CC);
-            P[0] = pos_clip[c0];
-            P[1] = pos_clip[c1];
-            P[2] = pos_clip[c2];
+            const float4 *pc = pos_clip + (int64_t)view * Va;
+            P[0] = pc[c0];
+            P[1] = pc[c1];
+            P[2] = pc[c2];
         }
         if (live) {
             ib_fragment_math<CC>(ok, t, w, gv, r0, r1, r2, vals + p * S, acc);
@@ -2501,11 +2506,11 @@ extern "C" int dressi_geometry_bwd(dressi_ctx *ctx, const float *pos, const floa
         const LossJob loss = dr_take_step_loss(ctx);
         const int ng = nt + lj.nb + (loss.loss ? 1 : 0);
         if (Cv == 6)
-            DR_LAUNCH("k_geo_tile", (k_geo_tile<6>), ng, DRESSI_TILE_PIX, lds, st, vattr, V, tris, T, pc4, vp, H, W,
-                      cull, tri_id, b2, ntx, fl, grad_gbuf, gbi, gbo, ipart, rpart, ctx->skip_empty, lj, loss, nt);
+            DR_LAUNCH("k_geo_tile", (k_geo_tile<6, false>), ng, DRESSI_TILE_PIX, lds, st, vattr, V, tris, T, pc4, vp, H, W,
+                      cull, tri_id, b2, ntx, fl, grad_gbuf, gbi, gbo, ipart, rpart, ctx->skip_empty, lj, loss, nt, nt);
         else
-            DR_LAUNCH("k_geo_tile", (k_geo_tile<9>), ng, DRESSI_TILE_PIX, lds, st, vattr, V, tris, T, pc4, vp, H, W,
-                      cull, tri_id, b2, ntx, fl, grad_gbuf, gbi, gbo, ipart, rpart, ctx->skip_empty, lj, loss, nt);
+            DR_LAUNCH("k_geo_tile", (k_geo_tile<9, false>), ng, DRESSI_TILE_PIX, lds, st, vattr, V, tris, T, pc4, vp, H, W,
+                      cull, tri_id, b2, ntx, fl, grad_gbuf, gbi, gbo, ipart, rpart, ctx->skip_empty, lj, loss, nt, nt);
     } else {
         dr_interp_bwd_tiles(vattr, 1, V, Cv, tris, T, tri_id, bary, 1, 1, H, W, fl, grad_gbuf, grad_bary_in,
                             grad_bary, ipart, ctx->skip_empty, st);
@@ -2518,6 +2523,66 @@ extern "C" int dressi_geometry_bwd(dressi_ctx *ctx, const float *pos, const floa
     dr_geo_vertex(Cv, pos, tris, pos_clip, vp, V, H, W, tt, ipart, rpart, adjacency_view(adj, V), mvp, vert_view,
                   grad_vattr, grad_pos_clip, gpos_t, gacc, grad_pos, st);
     return dressi_launch_check(ctx, "geometry_bwd");
+}
+
+// Several views of one hard layer: the per-tile adjoints of both stages in one
+// kernel, then the per-vertex sums of the two calls it stands for.
+extern "C" int dressi_attr_raster_bwd(dressi_ctx *ctx, const float *vattr, int V, int Cv, const int32_t *tris, int T,
+                                      const float *pos_clip, int B, int H, int W, int cull, const int32_t *tri_id,
+                                      const float *bary, const float *grad_gbuf, const float *grad_bary_in,
+                                      const void *frag_index, const int32_t *adj, float *grad_vattr,
+                                      float *grad_bary, float *grad_pos_clip, void *stream) {
+    int rc = check_raster_args(ctx, pos_clip, tris, B, V, T, H, W, 1, 0.0f);
+    if (rc) return rc;
+    if (Cv != 6 && Cv != 9) return dressi_fail(ctx, DRESSI_EINVAL, "attr_raster_bwd: Cv must be 6 or 9");
+    if (B == 0 || V == 0) return DRESSI_OK;
+    if (!vattr || !tri_id || !bary || !grad_gbuf || !frag_index || !adj || !grad_vattr || !grad_bary ||
+        !grad_pos_clip)
+        return dressi_fail(ctx, DRESSI_EINVAL, "attr_raster_bwd: null pointer");
+    hipStream_t st = (hipStream_t)stream;
+    const int ntx = tiles_x(W), nt = ntx * tiles_y(H), g = B * nt;
+    Carver c;
+    const size_t o_i = c.take(sizeof(float) * (size_t)g * DRESSI_TILE_PIX * 3 * Cv);
+    const size_t o_r = c.take(sizeof(float) * (size_t)g * DRESSI_TILE_PIX * 9);
+    const bool al8 = (((uintptr_t)vattr | (uintptr_t)grad_gbuf) & 7u) == 0;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (c.off > ctx->scratch_bytes) {
+        const hipError_t e = hipStreamIsCapturing(st, &cs);
+        if (e != hipSuccess) return dressi_hip_check(ctx, e, "hipStreamIsCapturing");
+    }
+    if ((Cv == 6 && !al8) || cs != hipStreamCaptureStatusNone) {
+        // rows of six floats are read in pairs; a capture keeps to the arena
+        // it has, and the two calls need less
+        rc = dressi_interpolate_bwd(ctx, vattr, 1, V, Cv, tris, T, tri_id, bary, B, 1, H, W, grad_gbuf, grad_bary_in,
+                                    frag_index, adj, grad_vattr, grad_bary, stream);
+        if (rc) return rc;
+        return dressi_rasterize_bwd(ctx, pos_clip, tris, B, V, T, H, W, 1, 0.0f, cull, tri_id, grad_bary, nullptr,
+                                    frag_index, adj, grad_pos_clip, stream);
+    }
+    if ((rc = dressi_scratch(ctx, c.off, st))) return rc;
+    float *ipart = at<float>(ctx->scratch, o_i), *rpart = at<float>(ctx->scratch, o_r);
+    FragLists fl;
+    TriTiles tt;
+    dressi_fragindex_view(const_cast<void *>(frag_index), B, 1, H, W, T, fl, tt);
+    const Viewports vp{nullptr, nullptr};
+    const float4 *pc4 = reinterpret_cast<const float4 *>(pos_clip);
+    const float2 *b2 = reinterpret_cast<const float2 *>(bary);
+    const float2 *gbi = reinterpret_cast<const float2 *>(grad_bary_in);
+    float2 *gbo = reinterpret_cast<float2 *>(grad_bary);
+    const size_t lds = sizeof(float) * DRESSI_TILE_PIX * (((Cv + 2) | 1) + 9);
+    if (Cv == 6)
+        DR_LAUNCH("k_geo_tile", (k_geo_tile<6, true>), g, DRESSI_TILE_PIX, lds, st, vattr, V, tris, T, pc4, vp, H, W,
+                  cull, tri_id, b2, ntx, fl, grad_gbuf, gbi, gbo, ipart, rpart, ctx->skip_empty, ListJob{},
+                  LossJob{}, g, nt);
+    else
+        DR_LAUNCH("k_geo_tile", (k_geo_tile<9, true>), g, DRESSI_TILE_PIX, lds, st, vattr, V, tris, T, pc4, vp, H, W,
+                  cull, tri_id, b2, ntx, fl, grad_gbuf, gbi, gbo, ipart, rpart, ctx->skip_empty, ListJob{},
+                  LossJob{}, g, nt);
+    const Adjacency A = adjacency_view(adj, V);
+    dr_interp_bwd_vertices(B, 1, V, T, 1, Cv, tt, ipart, A, grad_vattr, st);
+    DR_LAUNCH("k_rast_bwd_vertex", (k_rast_bwd_vertex), (int)(((int64_t)B * V * RBV_LANES + 255) / 256), 256, 0, st,
+              pc4, vp, B, V, T, H, W, 1, tt, rpart, A, reinterpret_cast<float4 *>(grad_pos_clip));
+    return dressi_launch_check(ctx, "attr_raster_bwd");
 }
 
 size_t dr_need_raster(const dressi_limits &l, int64_t cap) {

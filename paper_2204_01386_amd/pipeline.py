@@ -313,8 +313,10 @@ class Step(_TwoStreams):
         self.packed_geo = self.packed and B == 1
         self.hard_raster = None     # rasterization strategy chosen by autotune() (None: triangle-parallel)
         self.hybrid_weight = HYBRID_WEIGHT_DEFAULT
-        # one hard layer: the fragment index built in the rasterization's call
+        # one hard layer: the fragment index built in the rasterization's call,
+        # the attribute and rasterization adjoints' tiles in one pass
         self.fuse_index = True
+        self.fuse_tiles = True
         # one view, packed: the whole step as one call (dressi_packed_step)
         self.whole_step = True
         self._step_bufs = None
@@ -587,14 +589,20 @@ class Step(_TwoStreams):
         B, V, T, H, W, K = self.B, self.V, self.T, self.H, self.W, self.K
         ck = self._chk
         Cv = self.Cv
-        ck(_lib.dressi_interpolate_bwd(h, _p(self.vattr), 1, V, Cv, _p(self.tris), T, _p(self.tri_id),
-                                       _p(self.bary), B, K, H, W, _p(self.g_gbuf), _p(gb_in),
-                                       _p(self.frag_index), _p(self.adj), _p(self.g_vattr),
-                                       _p(self.g_bary), s), "interpolate_bwd")
-        ck(_lib.dressi_rasterize_bwd(h, _p(self.pos_clip), _p(self.tris), B, V, T, H, W, K, self.r, 0,
-                                     _p(self.tri_id), _p(self.g_bary), _p(self.g_dist),
-                                     _p(self.frag_index), _p(self.adj), _p(self.g_clip), s),
-           "rasterize_bwd")
+        if self.fuse_tiles and K == 1 and self.r == 0:
+            ck(_lib.dressi_attr_raster_bwd(h, _p(self.vattr), V, Cv, _p(self.tris), T, _p(self.pos_clip), B, H, W, 0,
+                                           _p(self.tri_id), _p(self.bary), _p(self.g_gbuf), _p(gb_in),
+                                           _p(self.frag_index), _p(self.adj), _p(self.g_vattr), _p(self.g_bary),
+                                           _p(self.g_clip), s), "attr_raster_bwd")
+        else:
+            ck(_lib.dressi_interpolate_bwd(h, _p(self.vattr), 1, V, Cv, _p(self.tris), T, _p(self.tri_id),
+                                           _p(self.bary), B, K, H, W, _p(self.g_gbuf), _p(gb_in),
+                                           _p(self.frag_index), _p(self.adj), _p(self.g_vattr),
+                                           _p(self.g_bary), s), "interpolate_bwd")
+            ck(_lib.dressi_rasterize_bwd(h, _p(self.pos_clip), _p(self.tris), B, V, T, H, W, K, self.r, 0,
+                                         _p(self.tri_id), _p(self.g_bary), _p(self.g_dist),
+                                         _p(self.frag_index), _p(self.adj), _p(self.g_clip), s),
+               "rasterize_bwd")
         ck(_lib.dressi_transform_bwd(h, _p(self.mvp), B, V, _p(self.g_clip), _p(self.g_pos_t), s),
            "transform_bwd")
         ck(_lib.dressi_vertex_attrs_bwd(h, _p(self.pos), _p(self.tris), V, T, Cv, _p(self.adj),
