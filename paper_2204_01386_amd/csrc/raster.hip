@@ -757,7 +757,9 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
 //  1. those whose box is at most RL_NEAR pixels away,
 //  2. the others, only while some pixel's K-th key leaves room, ring by ring
 //     of their distance from the quadrant; the rings come from a histogram,
-//     the first holds at least RS_RING triangles.
+//     the first holds at least RS_RING triangles, each later step 4 RS_RING
+//     more (every step reads the bin's rings again: 24, 96, 128, 144 give 6.58,
+//     5.96, 6.01, 5.97 ms and 347, 329, 326, 322 us for the first two below).
 // 0 and 1 read the near end of the tile's bin only; most quadrants end there.
 // A quadrant lists the triangles it wants by their 16-byte boxes before it
 // loads and stages their records, 256 at a time.
@@ -770,9 +772,9 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
 //
 // Measured (kernel; strips of 16 x 4 pixels walking the whole bin three times,
 // then 4 x 4 blocks evaluating four triangles a step, then this): 21.5, 12.4,
-// 6.7 ms for 8 views 2048^2, 1 M triangles, K = 3 (the pairs evaluated fell
-// from 2.0 G to 0.19 G); 1.40, 0.58, 0.34 ms for 16 views 512^2, 82 k triangles,
-// K = 3, banded (front pass 0.36 -> 0.14); 524, 146, 97 us for 2 views 640 x 480,
+// 6.0 ms for 8 views 2048^2, 1 M triangles, K = 3 (the pairs evaluated fell
+// from 2.0 G to 0.19 G); 1.40, 0.58, 0.33 ms for 16 views 512^2, 82 k triangles,
+// K = 3, banded (front pass 0.36 -> 0.14); 524, 146, 92 us for 2 views 640 x 480,
 // 20 k triangles, K = 2; 197, 55, 42 us for 6 views 256^2, 5 k triangles, banded.
 // What is left is latency: the chain bin -> boxes -> records of each list.
 //
@@ -783,7 +785,7 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
 #define RS_LIST 1536   // listed triangles
 #define RS_SEGMENT 1024   // bin entries a scan takes at once where a list may not hold all it wants
 #define RS_QUEUE 320   // queued pairs of a wavefront: fewer than 64 waiting, 4 pixels x 64 triangles
-#define RS_RING 24
+#define RS_RING 128
 #define RS_RINGS 4096  // bin entries whose ring is kept in LDS
 #define RS_NEAR2 ((float)(RL_NEAR * DRESSI_SUBPIX) * (float)(RL_NEAR * DRESSI_SUBPIX))
 
