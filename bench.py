@@ -139,11 +139,11 @@ def scene_for(cfg):
 FETCH_SCALE, WRITE_SCALE = 262144.0 / 131083.5, 1.0
 TRAFFIC = {
     "k_invuv_gather": {"src": "paper_2204_01386_amd/csrc/texture.hip",
-                       "sha": "c152c7215b4175a8581336317d50255a6df16017110a081b438998f3ec178ce4",
-                       "fetch_kib": 10434.1875, "write_kib": 16384.03125},
+                       "sha": "41a2d7e22cd5df873e11e06bed63b3d98d39b62c3613dd5bf50b9701eb4976ec",
+                       "fetch_kib": 10436.0, "write_kib": 16384.03125},
     "k_packed_bwd": {"src": "paper_2204_01386_amd/csrc/shade.hip",
-                     "sha": "d294fd08a604b8564d2e85916e3fd85935d080b02776a2876d1a9dbe346b2797",
-                     "fetch_kib": 10422.375, "write_kib": 7253.0},
+                     "sha": "3460729556cfd8363bc4986e4d4ce65edfc3c28e7f040bf9b521adfb5526855b",
+                     "fetch_kib": 10567.25, "write_kib": 7252.96875},
 }
 
 
@@ -179,7 +179,10 @@ class Shapes:
         self.uvadj = (self.Vuv + 1 + 3 * st.T) * 4
         # the packed single-layer pass replaces the per-fragment stages
         self.packed = bool(getattr(st, "packed", False))
-        # its texel gather reads one 32-byte record per kept pixel
+        # several layers or a soft blend: one pass before the blend, one after it
+        layer_scene = getattr(st, "_layer_scene", None)
+        self.layers = bool(self.Ct) and not self.packed and layer_scene is not None and layer_scene() is not None
+        # the packed pass's texel gather reads one 32-byte record per kept pixel
         self.rec = self.packed and bool(getattr(st, "gather_rec", False)) and getattr(st, "inv_rec", None) is not None
 
     def touched(self, cells, C):
@@ -254,6 +257,27 @@ def call_bytes(z: Shapes):
         out["shade_bwd env"] = sh_in + c * 12 + c * 12
         out["texture_bwd env"] = (N * 4 + c * (12 + 12) + z.touched(z.ecells, 3) + c * 12
                                   + z.S * z.ecells * 4 * 2 + c * 4 + ewin * (12 + 12) + z.ecells * 12)
+    if z.layers:
+        # interpolation, lookups and shading as one pass, their adjoints as
+        # another: each reads its inputs once and writes what leaves it
+        for k in ("interpolate", "interpolate uv", "texture", "shade dir", "texture env", "shade", "shade_bwd",
+                  "shade_bwd env", "texture_bwd", "texture_bwd env", "interpolate_bwd uv"):
+            out.pop(k, None)
+        win = min(c, z.S * z.cells)
+        tex_in = z.Vuv * 8 + T * 12 + z.touched(z.cells, z.Ct)
+        kept = Cv * 4 + 8 + z.Ct * 4                      # G-buffer, coordinates, samples
+        fwd_in, bwd = V * Cv * 4 + T * 12 + tex_in, tex_in + z.S * z.cells * 4
+        g_out = g_geo + z.Ct * 4 + 8 + 4                  # their gradients and the registration
+        if z.env:
+            kept += 12 + 12
+            fwd_in += z.touched(z.ecells, 3)
+            bwd += z.touched(z.ecells, 3) + z.S * z.ecells * 4
+            g_out += 12 + 4
+            ewin = min(c, z.S * z.ecells)
+            out["texture_grad env"] = z.S * z.ecells * 4 + ewin * (12 + 12) + z.ecells * 12
+        out["layers_forward"] = N * 4 + c * 8 + fwd_in + B * 12 + c * (kept + 12)
+        out["layers_backward"] = N * 4 + c * (kept + 12) + bwd + B * 12 + c * g_out
+        out["texture_grad"] = z.S * z.cells * 4 + win * (8 + z.Ct * 4) + z.cells * z.Ct * 4
     return out
 
 
@@ -266,7 +290,9 @@ def kernel_bytes(name, z: Shapes):
     if z.packed and name in ("k_interp", "k_tex_fwd", "k_shade", "k_shade_bwd", "k_blend", "k_blend_bwd",
                              "k_loss_l2", "k_tex_bwd_pixel"):
         return None
-    if name in ("k_raster", "k_raster_list"):
+    if z.layers and name in ("k_interp", "k_tex_fwd", "k_shade", "k_shade_bwd", "k_tex_bwd_pixel"):
+        return None
+    if name in ("k_raster", "k_raster_list", "k_raster_soft"):
         return cb["rasterize"] - B * V * 16 - T * 12
     if name == "k_setup_bin":
         return B * V * 16 + T * 12
@@ -278,6 +304,10 @@ def kernel_bytes(name, z: Shapes):
         return z.S * z.cells * 4 + min(c, z.S * z.cells) * _win_bytes(z) + z.cells * z.Ct * 4
     if name == "k_tex_bwd_pixel" and not z.env:
         return N * 4 + c * (8 + z.Ct * 4) + z.touched(z.cells, z.Ct) + c * 8 + c * 4
+    if name == "k_layers_fwd":
+        return cb.get("layers_forward")
+    if name == "k_layers_bwd":       # the maps are cleared by a launch of their own
+        return cb["layers_backward"] - z.S * (z.cells + z.ecells) * 4 if z.layers else None
     if name == "k_packed_fwd":
         return cb.get("packed_forward")
     if name == "k_packed_bwd":
@@ -297,7 +327,7 @@ def kernel_bytes(name, z: Shapes):
     if name == "k_rast_bwd_tile":
         return B * V * 16 + T * 12 + N * 4 + c * (8 + d)
     if name == "k_geo_tile":          # both per-tile adjoints: one read of the fragments
-        return (N * 4 + c * (8 + Cv * 4) + V * Cv * 4 + T * 12 + (c * 8 if z.Ct else 0) + c * 8
+        return (N * 4 + c * (8 + Cv * 4 + d) + V * Cv * 4 + T * 12 + (c * 8 if z.Ct else 0) + c * 8
                 + B * V * 16)
     if name == "k_geo_vertex":        # both vertex sums, the transform and normal-sum adjoints
         return z.adj + V * 12 + T * 12 + B * V * 16 + B * 64 + V * Cv * 4 + B * V * 16
