@@ -757,9 +757,11 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
 //  1. those whose box is at most RL_NEAR pixels away,
 //  2. the others, only while some pixel's K-th key leaves room, ring by ring
 //     of their distance from the quadrant; the rings come from a histogram,
-//     the first holds at least RS_RING triangles, each later step 4 RS_RING
-//     more (every step reads the bin's rings again: 24, 96, 128, 144 give 6.58,
-//     5.96, 6.01, 5.97 ms and 347, 329, 326, 322 us for the first two below).
+//     the first holds at least RS_RING triangles, each later step 8 RS_RING
+//     more, which a list still holds (every step reads the bin's rings again:
+//     24 and 4 x 24, 128 and 4 x 128, 128 and 8 x 128 give 6.58, 6.01, 5.72 ms
+//     and 347, 322, 328 us for the first two below; RL_NEAR = 3, 4, 6 instead
+//     of 2: 6.30, 6.70, 7.42 ms with 4 x 128).
 // 0 and 1 read the near end of the tile's bin only; most quadrants end there.
 // A quadrant lists the triangles it wants by their 16-byte boxes before it
 // loads and stages their records, 256 at a time.
@@ -772,7 +774,7 @@ __global__ void __launch_bounds__(DRESSI_TILE_PIX) __attribute__((amdgpu_waves_p
 //
 // Measured (kernel; strips of 16 x 4 pixels walking the whole bin three times,
 // then 4 x 4 blocks evaluating four triangles a step, then this): 21.5, 12.4,
-// 6.0 ms for 8 views 2048^2, 1 M triangles, K = 3 (the pairs evaluated fell
+// 5.7 ms for 8 views 2048^2, 1 M triangles, K = 3 (the pairs evaluated fell
 // from 2.0 G to 0.19 G); 1.40, 0.58, 0.33 ms for 16 views 512^2, 82 k triangles,
 // K = 3, banded (front pass 0.36 -> 0.14); 524, 146, 92 us for 2 views 640 x 480,
 // 20 k triangles, K = 2; 197, 55, 42 us for 6 views 256^2, 5 k triangles, banded.
@@ -1203,7 +1205,7 @@ __global__ void __launch_bounds__(256)
                 const int upto = __shfl(cum, min(hi, 63), 64);
                 visit(W2{}, m, done + 1, hi, upto - (done < 0 ? 0 : __shfl(cum, min(done, 63), 64)));
                 done = hi;
-                goal = upto + 4 * RS_RING;
+                goal = upto + 8 * RS_RING;
                 __syncthreads();
                 far = widest();
             }
